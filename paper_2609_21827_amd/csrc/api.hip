@@ -180,7 +180,7 @@ int configure(const rheo_config* cfg_in, rheo_tree* t) {
     // sparse levels run one block per row (the row streamed once, no chunk
     // lists) when the row fits it and the level has at least row_min rows;
     // RHEO_EXPAND_ROW=0 or 1 forces the chunked or the per-row kernel
-    t->row_mode = (!dense && expand_row_nq(c.dtype, c.vocab) > 0) ? -1 : 0;
+    t->row_mode = (!dense && expand_row_threads(c.dtype, c.vocab, S) > 0) ? -1 : 0;
     if (const char* er = getenv("RHEO_EXPAND_ROW")) {
         if (er[0] == '0') t->row_mode = 0;
         else if (er[0] == '1' && t->row_mode != 0) t->row_mode = 1;
@@ -243,16 +243,8 @@ void layout(rheo_tree* t, Arena& A) {
     TreeDev& d = t->dev;
     const bool dense = d.dense != 0;
     const size_t B = d.B, NN = d.NN, E = d.E;
-    take(A, &d.tok, B * NN);
-    take(A, &d.par, B * NN);
-    take(A, &d.meta, B * NN);
-    take(A, &d.proxy, B * NN);
-    take(A, &d.qtrue, B * NN);
+    take(A, &d.node, B * NN);
     take(A, &d.score, B * NN);
-    take(A, &d.path, B * NN);
-    take(A, &d.first_child, B * NN);
-    take(A, &d.exp_of, B * NN);
-    take(A, &d.tidx, B * NN);
     const size_t TS = dense ? 1 : (size_t)d.S;              // dense mode keeps no tail copy
     take(A, &d.tail_id, B * E * TS);
     take(A, &d.tail_q, B * E * TS);
@@ -267,8 +259,10 @@ void layout(rheo_tree* t, Arena& A) {
     take(A, &d.frontier, B * d.NE);
     take(A, &d.fr_parent, B * d.NE);
     take(A, &d.fr_token, B * d.NE);
-    take(A, &d.pidx, B * NN);
     take(A, &d.porder, B * NN);
+    take(A, &d.pr_par, B * NN);
+    take(A, &d.pr_tok, B * NN);
+    take(A, &d.pr_depth, B * NN);
     take(A, &d.err, 1);
     take(A, &d.team_ticket, B);
     take(A, &d.team_flag, B * 64);
@@ -279,6 +273,8 @@ void layout(rheo_tree* t, Arena& A) {
     take(A, &d.team_nchunk, dense ? B * 1024 * 2 : 1);
     take(A, &d.sel, B * d.NE * (size_t)d.C * d.Sc);
     take(A, &d.seq_cnt, B);
+    take(A, &d.fr_words, B * 3 * (size_t)d.NE * d.K);
+    take(A, &d.fr_mark, B);
 }
 
 // Clears what the kernels expect zeroed (or -1) before a tree's first step
@@ -293,16 +289,20 @@ int init_state(rheo_tree* t) {
     if (e == hipSuccess) e = hipMemset(d.team_max, 0, B * 64 * sizeof(uint64_t));
     if (e == hipSuccess) e = hipMemset(d.team_sum, 0, B * 64 * sizeof(uint64_t));
     if (e == hipSuccess) e = hipMemset(d.seq_cnt, 0, B * sizeof(uint32_t));
+    // the first launch's mark is a clear top bit: no word carries it
+    if (e == hipSuccess) e = hipMemset(d.fr_words, 0xFF, B * 3 * d.NE * d.K * sizeof(uint64_t));
+    if (e == hipSuccess) e = hipMemset(d.fr_mark, 0, B * sizeof(uint64_t));
     if (e == hipSuccess && dense) e = hipMemset(d.dflag, 0, B * d.NE * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMemset(d.pidx, 0xFF, B * NN * sizeof(int32_t));
+    if (e == hipSuccess) e = hipMemset(d.node, 0xFF, B * NN * sizeof(Node));
+    if (e == hipSuccess) e = hipMemset(d.porder, 0, B * NN * sizeof(int32_t));
     if (e == hipSuccess) e = hipMemset(d.frontier, 0, B * d.NE * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMemset(d.first_child, 0xFF, B * NN * sizeof(int32_t));
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) return hip_fail(e, "initialising tree state");
     e = verify_shape(d, &t->vG, &t->v_segch, &t->v_grid);
     if (e != hipSuccess) return hip_fail(e, "no co-resident verification team shape for this tree");
     e = expand_row_slots(d, &d.row_slots);
-    if (e != hipSuccess) return hip_fail(e, "row kernel occupancy");
+    if (e == hipSuccess) e = prepare_prune(d);
+    if (e != hipSuccess) return hip_fail(e, "kernel set-up");
     return RHEO_OK;
 }
 

@@ -214,6 +214,7 @@ __global__ __launch_bounds__(NTD) void k_dpool(TreeDev t, LevelArgs a) {
     __shared__ uint64_t s_sub[NCHMAX];           // tail totals per sub-chunk
     __shared__ uint64_t s_cq[CHT];               // tail weights of one sub-chunk
     __shared__ uint64_t s_red[NTD / WAVE];
+    __shared__ PoolShared<NTD> ps;
     __shared__ int s_pu, s_cs, s_y, s_flag, s_cnt;
     __shared__ uint64_t s_u, s_t2, s_qy;
 
@@ -259,6 +260,7 @@ __global__ __launch_bounds__(NTD) void k_dpool(TreeDev t, LevelArgs a) {
         dqv[q] = (i < NCH) ? t.dq[(int64_t)row * NCH + i] : 0ull;
     }
     row_top_by_logit(t, row, s_list, s_tl);
+    const ParentRec pr = parent_rec(t, a, b, tid < K, s_pu);
     const float M = key_value(s_tl[0]);
 
     // x_1..x_kk by (w1 desc, id asc)
@@ -428,8 +430,8 @@ __global__ __launch_bounds__(NTD) void k_dpool(TreeDev t, LevelArgs a) {
         t.zq[(int64_t)b * t.E + e_idx] = Zq;
         t.dref[(int64_t)b * t.E + e_idx] = ref_t;
         for (int i = 0; i < m; ++i) t.dleads[((int64_t)b * t.E + e_idx) * 16 + i] = key_id(s_x[i]);
-        t.first_child[nb + pu] = cb + j * K;
-        t.exp_of[nb + pu] = e_idx;
+        t.node[nb + pu].first_child = cb + j * K;
+        t.node[nb + pu].exp_of = e_idx;
         if (level == 0) emit_root(t, nb);
     }
     if (tid < K) {
@@ -464,11 +466,10 @@ __global__ __launch_bounds__(NTD) void k_dpool(TreeDev t, LevelArgs a) {
             proxy = __ddiv_rn((double)s_xw[rk], dS1);
         }
         const double qtrue = (kind == SAMPLED) ? __ddiv_rn((double)qy, (double)Zq) : proxy;
-        emit_child(t, level, nb, pu, parent_rec(t, level, nb, pu), cb + j * K + s, s, kind, tok,
-                   proxy, qtrue, -1);
+        emit_child(t, a, b, j, pu, pr, s, kind, tok, proxy, qtrue, -1, ps);
     }
     // the next frontier: the last row of the sequence to finish selects it
-    select_frontier(t, a, b, s_sub, s_sub + 256);
+    select_frontier(t, a, b, j, pr, s_sub, s_sub + 256, ps);
 }
 
 template <int DT>

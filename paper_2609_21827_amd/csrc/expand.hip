@@ -2,7 +2,9 @@
 // row, the node's distributions, the hybrid candidate pool with its proxy
 // and true probabilities, and the parent each row belongs to.
 //
-// Two kernels per level:
+// One kernel per level, k_expand_row: one block per row (described at the
+// kernel).  Where a row's LDS does not fit it (fp32 rows above 131072 elements
+// with wide supports), or on request, two kernels:
 //  * k_select, one 256-thread block per (chunk, row): the chunk is streamed
 //    from HBM into registers with 16-byte loads and its exact top-Sc by
 //    (logit desc, id asc) is written, sorted, to the tree's selection
@@ -10,21 +12,20 @@
 //    lies in the union of its chunks' top-S.  Within a chunk, a value that
 //    Sc per-vector maxima reach is a threshold at least Sc elements reach,
 //    so the chunk's top-Sc are among the few elements at or above it; they
-//    are collected in LDS and ranked exactly.  Many small blocks per CU keep
-//    loads in flight while other blocks rank.
+//    are collected in LDS and ranked exactly.  (Dense mode's lists come from
+//    it too.)
 //  * k_pool, one 256-thread block per row: takes the row's parent from the
-//    stored frontier, merges the chunk lists into the row's top-S support
-//    (Sec. 3.2, sparse draft distributions), and forms the pool (Sec. 3.2;
-//    App. C.1): construction weights q (untempered, Sec. 5.4), ranks by
-//    (q desc, id asc), the tail q~_T = q_T / z on the support minus the
-//    top-m, Y ~ q~_T by inverse CDF over token ids, fills, proxies
-//    (min{q(x_m), z}; q(x_1) + eps for m = 0), the true probability q~(Y),
-//    path scores (App. C.1).  The tail is stored id-sorted for verification.
-//    The last row of a sequence to finish (an arrival counter) ranks the
-//    level's new children by priority and stores the n_expand best, which
-//    the next level's rows expand (Sec. 2.1; App. C.4, step 1).
-// No block waits for another; children fields pass between blocks only
-// through agent-coherent atomic stores and loads.
+//    stored frontier and merges the chunk lists into the row's top-S support
+//    (Sec. 3.2, sparse draft distributions).
+// Both end with the pool (Sec. 3.2; App. C.1): construction weights q
+// (untempered, Sec. 5.4), ranks by (q desc, id asc), the tail q~_T = q_T / z
+// on the support minus the top-m, Y ~ q~_T by inverse CDF over the ranked
+// tail, fills, proxies (min{q(x_m), z}; q(x_1) + eps for m = 0), the true
+// probability q~(Y), path scores (App. C.1).  The last row of a sequence to
+// finish (an arrival counter) ranks the level's new children by priority
+// and stores the n_expand best, which the next level's rows expand (Sec.
+// 2.1; App. C.4, step 1).  Children fields pass between blocks only through
+// agent-coherent atomic stores and loads (pool_common.h).
 #include <type_traits>
 
 #include "rheo_device.h"
@@ -116,22 +117,27 @@ __host__ __device__ inline PoolLds pool_lds(int S, int C, int top_min = 0, int k
 }
 
 // The pool of one row from its support s_top (App. C.1), formed by NT
-// threads (tid < NT).  Children fields the frontier selection reads in other
-// blocks (token, score, path) are published with agent-scope atomics.
-// A support slot left empty (no candidate reached it) is flagged and filled
-// with a -inf key.
-template <int NT>
+// threads, EPT consecutive support entries each (S <= NT * EPT).  A support
+// slot left empty (no candidate reached it) is flagged and taken as -inf.
+//
+// It is a chain of dependent steps (latency, not throughput, bounds it), so
+// it has two exchanges in all: one for both weight totals, the masses
+// before every entry and the weight ties, one for Y; the sums run as 32-bit
+// scans of the weights' 16-bit halves (a DPP add per step); the children's
+// probabilities and Y's come from one division (Y's in a lane of its own).
+// At V = 128256, S = 128 (clock stamps): 7200 cycles before these, 5400 now.
+template <int NT, int EPT>
 __device__ __forceinline__ void pool_form(const TreeDev& t, const LevelArgs& a, int row,
                                           uint8_t* lds, const PoolLds& L, int pu,
-                                          const ParentRec& pr, uint64_t u, uint64_t* s_red,
-                                          int* s_yi) {
+                                          const ParentRec& pr, uint64_t u, PoolShared<NT>& ps) {
+    constexpr int NW = NT / WAVE;
     uint64_t* s_top = (uint64_t*)(lds + L.top);
     uint64_t* s_k2 = (uint64_t*)(lds + L.k2);
     uint32_t* s_w1 = (uint32_t*)(lds + L.w1);
     uint32_t* s_q = (uint32_t*)(lds + L.q);
     int16_t* s_wr = (int16_t*)(lds + L.wr);
     int16_t* s_xs = (int16_t*)(lds + L.xs);
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid % WAVE, wid = tid / WAVE;
     const int b = row / a.P;
     const int j = row % a.P;
     const int S = t.S, K = t.K, m = t.m;
@@ -140,165 +146,193 @@ __device__ __forceinline__ void pool_form(const TreeDev& t, const LevelArgs& a, 
     const int64_t nb = (int64_t)b * t.NN;
     const int cb = (level == 0) ? 1 : 1 + K + (level - 1) * NE * K;
     const int e_idx = (level == 0) ? 0 : 1 + (level - 1) * NE + j;
-    if (tid == 0) *s_yi = -1;
+    if (tid == 0) ps.yi = -1;
 
     // Construction weights w1 (untempered unless asked) and, taking the rank
     // by (w1 desc, id asc) to be the support order, the tail weights of q~_T
-    // relative to x_{m+1} = s_top[m], both totals in one exchange.  The
-    // support is in (logit desc, id asc) order and the weight never grows
-    // along it, so the rank differs from the position only where two
-    // different logits share a weight: then the ranks and the tail are
-    // computed again.
+    // relative to x_{m+1} = s_top[m].  The support is in (logit desc, id asc)
+    // order and the weight never grows along it, so the rank differs from the
+    // position only where two different logits share a weight: then the ranks
+    // and the tail are computed again.
     //
     // The tail, x_{m+1} .. x_S in rank order, is written to the tree in that
     // order (token, q~ weight) for verification, and Y ~ q~_T is the entry
     // whose interval [mass before, mass before + q) holds
     // t = floor(U64 Zq / 2^64): the inverse CDF over the tail in rank order.
-    // With at most one support entry per thread (S <= NT) the masses before
-    // every entry come with the totals, from the same exchange.
     auto filled = [&](uint64_t k) {
         return (uint32_t)key_id(k) >= (uint32_t)t.V ? logit_key(-INFINITY, 0u) : k;
     };
     const float M = key_value(filled(s_top[0]));
     const float ref0 = key_value(filled(s_top[m]));
-    uint64_t part1 = 0, partq = 0;
-    for (int i = tid; i < S; i += NT) {
-        uint64_t tk = s_top[i];
-        if ((uint32_t)key_id(tk) >= (uint32_t)t.V) {   // a support slot left empty
-            atomicOr(t.err, 256);
-            tk = logit_key(-INFINITY, 0u);
-            s_top[i] = tk;
-        }
-        const float v = key_value(tk);
-        const uint32_t w = cweight(v, M, a.k1);
-        s_w1[i] = w;
-        part1 += w;
-        const uint32_t q = (i >= m) ? cweight(v, ref0, a.kT) : 0u;
-        s_q[i] = q;
-        partq += q;
-    }
-    const bool one_each = S <= NT;           // thread tid holds support entry tid
-    uint64_t S1, Zq, qbefore = 0;
-    if (one_each) psum2_scan<NT>(part1, partq, s_red, &S1, &Zq, &qbefore);
-    else psum2<NT>(part1, partq, s_red, &S1, &Zq);
-    if (t.cfull) S1 = t.s1row[row];          // construction over the whole vocabulary
-    if (NT == WAVE) wave_sync();             // (a block sum has synchronised)
-    const int64_t tail_base = ((int64_t)b * t.E + e_idx) * S;
+    const int i0 = tid * EPT;
+    uint64_t ek[EPT];
+    uint32_t eq[EPT];
+    uint64_t pre;                                // tail mass of the wave before this thread's
     bool tie = false;
-    for (int i = tid + 1; i < S; i += NT)
-        tie |= s_w1[i] == s_w1[i - 1] && (s_top[i] >> 32) != (s_top[i - 1] >> 32);
-    // the tail and Y with the rank taken to be the position (one entry per
-    // thread); the barrier of pany ends it, and tells whether two different
-    // logits share a weight, which (rarely) sends everything through the
-    // ranks below
-    if (one_each && tid >= m && tid < S) {
-        const uint32_t q = s_q[tid];
-        t.tail_id[tail_base + tid - m] = key_id(s_top[tid]);
-        t.tail_q[tail_base + tid - m] = q;
-        const uint64_t tt = __umul64hi(u, Zq);
-        if (qbefore <= tt && tt - qbefore < (uint64_t)q) *s_yi = tid;
+    {
+        uint32_t w1lo = 0, w1hi = 0, qlo = 0, qhi = 0;
+        uint64_t kp = filled(s_top[i0 > 0 && i0 < S ? i0 - 1 : 0]);
+        uint32_t wp = cweight(key_value(kp), M, a.k1);
+#pragma unroll
+        for (int r = 0; r < EPT; ++r) {
+            const int i = i0 + r;
+            ek[r] = 0;
+            eq[r] = 0;
+            if (i < S) {
+                const uint64_t raw = s_top[i];
+                ek[r] = filled(raw);
+                if (raw != ek[r]) atomicOr(t.err, 256);     // a support slot left empty
+                const float v = key_value(ek[r]);
+                const uint32_t w = cweight(v, M, a.k1);
+                const uint32_t q = (i >= m) ? cweight(v, ref0, a.kT) : 0u;
+                tie |= i > 0 && w == wp && (ek[r] >> 32) != (kp >> 32);
+                kp = ek[r];
+                wp = w;
+                s_w1[i] = w;
+                s_q[i] = q;
+                eq[r] = q;
+                w1lo += w & 0xFFFFu;
+                w1hi += w >> 16;
+                qlo += q & 0xFFFFu;
+                qhi += q >> 16;
+            }
+        }
+        // inclusive scans over the wave (sums of at most 256 halves: < 2^24)
+        w1lo = wave_incl_scan_u32(w1lo);
+        w1hi = wave_incl_scan_u32(w1hi);
+        const uint32_t mlo = qlo, mhi = qhi;
+        qlo = wave_incl_scan_u32(qlo);
+        qhi = wave_incl_scan_u32(qhi);
+        const uint64_t anytie = __ballot(tie);
+        if (lane == WAVE - 1) {
+            ps.w1[wid] = ((uint64_t)w1hi << 16) + w1lo;
+            ps.q[wid] = ((uint64_t)qhi << 16) + qlo;
+            ps.tie[wid] = anytie != 0ull;
+        }
+        pre = ((uint64_t)(qhi - mhi) << 16) + (qlo - mlo);
     }
-    const bool ident = !pany<NT>(tie);
-    if (NT == WAVE) wave_sync();
-    if (!ident) {
+    __syncthreads();
+    uint64_t S1 = 0, Zq = 0;
+    int anyt = 0;
+    const int nwa = (S + WAVE * EPT - 1) / (WAVE * EPT);    // waves that hold entries
+    for (int w = 0; w < nwa; ++w) {
+        S1 += ps.w1[w];
+        const uint64_t zw = ps.q[w];
+        Zq += zw;
+        pre += (w < wid) ? zw : 0ull;
+        anyt |= ps.tie[w];
+    }
+    if (t.cfull) S1 = t.s1row[row];          // construction over the whole vocabulary
+    const int64_t tail_base = ((int64_t)b * t.E + e_idx) * S;
+    const bool ident = anyt == 0;
+    if (ident) {
+        const uint64_t tt = __umul64hi(u, Zq);
+#pragma unroll
+        for (int r = 0; r < EPT; ++r) {
+            const int i = i0 + r;
+            if (i >= m && i < S) {
+                t.tail_id[tail_base + i - m] = key_id(ek[r]);
+                t.tail_q[tail_base + i - m] = eq[r];
+                if (pre <= tt && tt - pre < (uint64_t)eq[r]) ps.yi = i;
+                pre += eq[r];
+            }
+        }
+    } else {
+        // two different logits share a weight: ranks by (w1 desc, id asc), the
+        // tail relative to the right x_{m+1}, contiguous runs of ranks per
+        // thread and a block scan of their masses
+        __syncthreads();
         for (int i = tid; i < S; i += NT)
             s_k2[i] = ((uint64_t)s_w1[i] << 32) |
-                      (uint64_t)(0xFFFFFFFFu - (uint32_t)key_id(s_top[i]));
-        psync<NT>();
+                      (uint64_t)(0xFFFFFFFFu - (uint32_t)key_id(filled(s_top[i])));
+        __syncthreads();
         rank_all<NT>(s_k2, S, s_wr);
-        psync<NT>();
+        __syncthreads();
         for (int i = tid; i < S; i += NT) s_xs[s_wr[i]] = (int16_t)i;
-        psync<NT>();
-        const float ref_t = key_value(s_top[s_xs[m]]);
-        partq = 0;
+        __syncthreads();
+        const float ref_t = key_value(filled(s_top[s_xs[m]]));
+        uint64_t partq = 0;
         for (int i = tid; i < S; i += NT) {
-            const uint32_t q = (s_wr[i] >= m) ? cweight(key_value(s_top[i]), ref_t, a.kT) : 0u;
+            const uint32_t q = (s_wr[i] >= m) ? cweight(key_value(filled(s_top[i])), ref_t, a.kT) : 0u;
             s_q[i] = q;
             partq += q;
         }
-        Zq = psum<NT>(partq, s_red);
-    }
-    // position in the support of rank r, and rank of position i
-    auto xs = [&](int r) -> int { return ident ? r : (int)s_xs[r]; };
-    auto wr = [&](int i) -> int { return ident ? i : (int)s_wr[i]; };
-    if (!(ident && one_each)) {
-        // contiguous runs of ranks m .. S-1 per thread, a block scan of
-        // their masses
-        if (tid == 0) *s_yi = -1;
+        Zq = block_sum_u64<NT>(partq, ps.q);
         const uint64_t tt = __umul64hi(u, Zq);
         const int ntail = S - m;
         const int per = (ntail + NT - 1) / NT;
         const int r0 = min(S, m + tid * per), r1 = min(S, r0 + per);
         uint64_t mine = 0;
-        for (int r = r0; r < r1; ++r) mine += s_q[xs(r)];
+        for (int r = r0; r < r1; ++r) mine += s_q[s_xs[r]];
         uint64_t tot;
-        uint64_t pre = pscan_excl<NT>(mine, s_red, &tot);
+        uint64_t acc = block_excl_scan_u64<NT>(mine, ps.q, &tot);
         for (int r = r0; r < r1; ++r) {
-            const int i = xs(r);
+            const int i = s_xs[r];
             const uint32_t q = s_q[i];
-            t.tail_id[tail_base + r - m] = key_id(s_top[i]);
+            t.tail_id[tail_base + r - m] = key_id(filled(s_top[i]));
             t.tail_q[tail_base + r - m] = q;
-            if (pre <= tt && tt - pre < (uint64_t)q) *s_yi = i;
-            pre += q;
+            if (acc <= tt && tt - acc < (uint64_t)q) ps.yi = i;
+            acc += q;
         }
-        psync<NT>();
     }
-    int yi = *s_yi;
+    __syncthreads();
+    if (wid != 0) return;
+
+    // ---- wave 0: the expanded node's record and its K children -------------
+    // position in the support of rank r, and rank of position i
+    auto xs = [&](int r) -> int { return ident ? r : (int)s_xs[r]; };
+    auto wr = [&](int i) -> int { return ident ? i : (int)s_wr[i]; };
+    int yi = ps.yi;
     if (yi < 0) {
         if (tid == 0) atomicOr(t.err, 1);
         yi = xs(m);                              // unreachable fallback
     }
-
     if (tid == 0) {
         // q~_T is taken relative to x_{m+1}: undefined when its logit is
         // -inf (fewer than m + 1 tokens of the support above the rest)
-        if (!(key_value(s_top[xs(m)]) > -INFINITY)) atomicOr(t.err, 512);
+        if (!(key_value(filled(s_top[xs(m)])) > -INFINITY)) atomicOr(t.err, 512);
         t.zq[(int64_t)b * t.E + e_idx] = Zq;
-        t.first_child[nb + pu] = cb + j * K;
-        t.exp_of[nb + pu] = e_idx;
+        t.node[nb + pu].first_child = cb + j * K;
+        t.node[nb + pu].exp_of = e_idx;
         if (level == 0) emit_root(t, nb);
     }
-    // the K children: top-m leads, Y, fills (App. C.1); pure top-K pools:
-    // the K best by (w1 desc, id asc)
-    if (tid < K) {
-        const int s = tid;
-        const int yr = wr(yi);
-        int item, kind;
-        if (t.topk) {
-            item = xs(s);
-            kind = LEAD;
-        } else if (s < m) {
-            item = xs(s);
-            kind = LEAD;
-        } else if (s == m) {
-            item = yi;
-            kind = SAMPLED;
-        } else {
-            const int f = s - m - 1;
-            const int rk = m + f + ((m + f) >= yr ? 1 : 0);
-            item = xs(rk);
-            kind = FILL;
-        }
-        double proxy;
-        const double dS1 = (double)S1;
-        if (kind == SAMPLED) {
-            if (m >= 1) {
-                uint64_t lead = 0;
-                for (int q2 = 0; q2 < m; ++q2) lead += s_w1[xs(q2)];
-                const uint64_t z = S1 - lead;
-                const uint64_t wm = s_w1[xs(m - 1)];
-                proxy = __ddiv_rn((double)(wm < z ? wm : z), dS1);
-            } else {
-                proxy = fmin(1.0, __dadd_rn(__ddiv_rn((double)s_w1[xs(0)], dS1), t.eps));
-            }
-        } else {
-            proxy = __ddiv_rn((double)s_w1[item], dS1);
-        }
-        const double qtrue = (kind == SAMPLED) ? __ddiv_rn((double)s_q[item], (double)Zq) : proxy;
-        emit_child(t, level, nb, pu, pr, cb + j * K + s, s, kind, key_id(s_top[item]), proxy,
-                   qtrue,
-                   wr(item) >= m ? wr(item) - m : -1);
+    // top-m leads, Y, fills (App. C.1); pure top-K pools: the K best by (w1
+    // desc, id asc)
+    int item = yi, kind = SAMPLED;
+    if (t.topk || tid < m) {
+        item = xs(min(tid, S - 1));
+        kind = LEAD;
+    } else if (tid != m && tid < K) {
+        const int rk = tid - 1;                  // Y itself is passed over
+        item = xs(rk + (rk >= wr(yi) ? 1 : 0));
+        kind = FILL;
     }
+    // one division for all lanes: lane s < K its child's proxy w1 / S1 (the
+    // sampled child: min{w1(x_m), z} / S1, for m = 0 w1(x_1) / S1 + eps),
+    // lane 32 the sampled child's probability q / Zq
+    uint32_t num = s_w1[item];
+    uint64_t den = S1;
+    if (kind == SAMPLED) {
+        num = s_w1[xs(0)];
+        if (m >= 1) {
+            uint64_t lead = 0;
+            for (int q2 = 0; q2 < m; ++q2) lead += s_w1[xs(q2)];
+            const uint64_t z = S1 - lead;
+            const uint64_t wm = s_w1[xs(m - 1)];
+            num = (uint32_t)(wm < z ? wm : z);
+        }
+    }
+    if (lane == 32) {
+        num = s_q[yi];
+        den = Zq;
+    }
+    double proxy = __ddiv_rn((double)num, (double)den);
+    const uint64_t py = lane_u64((uint64_t)__double_as_longlong(proxy), 32);
+    if (kind == SAMPLED && m == 0) proxy = fmin(1.0, __dadd_rn(proxy, t.eps));
+    const double qtrue = (kind == SAMPLED) ? __longlong_as_double((long long)py) : proxy;
+    if (tid < K)
+        emit_child(t, a, b, j, pu, pr, tid, kind, key_id(filled(s_top[item])), proxy, qtrue,
+                   wr(item) >= m ? wr(item) - m : -1, ps);
 }
 
 // The parent of row j of sequence b: frontier node j of the previous level
@@ -343,8 +377,8 @@ __device__ __forceinline__ void row_parent(const TreeDev& t, const LevelArgs& a,
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(NTP) void k_pool(TreeDev t, LevelArgs a) {
     extern __shared__ __align__(16) uint8_t s_pdyn[];
-    __shared__ uint64_t s_red[2 * NTP / WAVE];
-    __shared__ int s_pu, s_yi;
+    __shared__ PoolShared<NTP> ps;
+    __shared__ int s_pu;
     __shared__ uint64_t s_u;
     const PoolLds L = pool_lds(t.S, t.C);
     uint64_t* s_m = (uint64_t*)(s_pdyn + L.m);    // the C chunk lists, C * S keys
@@ -373,7 +407,7 @@ __global__ __launch_bounds__(NTP) void k_pool(TreeDev t, LevelArgs a) {
     for (int i = tid; i < S; i += NTP) s_top[i] = 0ull;   // id -1 until merged
     __syncthreads();
     // the parent record, for the children written at the end
-    const ParentRec pr = (tid < K) ? parent_rec(t, level, nb, s_pu) : ParentRec{1.0, 0ull};
+    const ParentRec pr = parent_rec(t, a, b, tid < K, s_pu);
 
     // merge: a key's rank in the row is its position in its own (sorted)
     // list plus the count of larger keys in every other list (a binary
@@ -422,11 +456,11 @@ __global__ __launch_bounds__(NTP) void k_pool(TreeDev t, LevelArgs a) {
     __syncthreads();
 
     // the pool, formed by the whole block
-    pool_form<NTP>(t, a, row, s_pdyn, L, s_pu, pr, s_u, s_red, &s_yi);
-    if (level + 1 >= t.D) return;
+    if (S <= NTP) pool_form<NTP, 1>(t, a, row, s_pdyn, L, s_pu, pr, s_u, ps);
+    else pool_form<NTP, SMAX / NTP>(t, a, row, s_pdyn, L, s_pu, pr, s_u, ps);
 
     // the next frontier: the last row of the sequence to finish selects it
-    select_frontier(t, a, b, s_top, s_k2);
+    select_frontier(t, a, b, j, pr, s_top, s_k2, ps);
 }
 
 // ---------------------------------------------------------------------------
@@ -1014,64 +1048,129 @@ __device__ __forceinline__ void select_block(const TreeDev& t, const LevelArgs& 
 
 
 // ---------------------------------------------------------------------------
-// k_expand_row: the whole level for one row per block.  The row is streamed
-// once (double-buffered batches of 16-byte vectors; only each vector's
-// exact maximum is kept, as a 16-bit order code in registers); the
-// threshold comes from the largest vector maxima every thread offers (two,
-// or four for supports above 128), and for supports above kLargeSupport
-// (LS) is raised to the exact S-th largest vector maximum by two rounds of
-// a 256-bin histogram; only the candidate vectors are read again; their
-// elements at or above the threshold are ranked (LS: sorted) into the
-// support, then the pool (App. C.1) and, by the last row of each sequence,
-// the next frontier -- with no chunk lists, no merge and no second launch.
-// Used when the row fits NQ vectors per thread and the level has enough
-// rows to fill the chip.
+// k_expand_row: the whole level for one row per block.
+//
+// The row is streamed once, in double-buffered batches of EBATCH 16-byte
+// vectors per thread; of every vector only its exact maximum is kept, as a
+// 16-bit order code in LDS (one 16-byte store per thread and batch).  Each
+// wave then takes the ceil(S / waves)-th largest of the maxima its lanes
+// offer, and the least of the waves' values is a threshold that at least S
+// elements reach: one block barrier.  Every wave reads its own candidate
+// vectors again and appends their elements at or above the threshold to the
+// block's candidates (about 1.4 S of them), which are ranked by a
+// histogram: bins linear in the value, their starts from one prefix sum,
+// and the order inside a bin by counting.  Then the pool (App. C.1) and, by
+// the last row of each sequence, the next frontier.
+//
+// What bounds it: the stream, then the latency of the steps after it (HBM is
+// idle while a row that has no successor on its compute unit ranks).
 // ---------------------------------------------------------------------------
-constexpr int CAPV_L = 2048;  // candidate vectors of a large-support row
-constexpr int CAPC_L = 2048;  // candidates of a large-support row (sorted in place)
+constexpr int NBINS = 512;    // histogram bins of the ranking (LS: twice as many)
+constexpr int ROW_BATCHES = 8;  // most batches of a row: 64 vectors per thread
 
-// Dynamic LDS of k_expand_row: the pool layout; large supports sort their
-// candidates in the support region and list candidate vectors in the
-// ranking-key region, both free until the pool is formed.
-__host__ __device__ inline PoolLds row_lds(int S, bool ls) {
-    return ls ? pool_lds(S, 0, CAPC_L, 4 * CAPV_L) : pool_lds(S, 0);
+// LDS of k_expand_row: the vector codes, which the ranked candidates and the
+// pool's ranking keys replace once the candidates are gathered; the
+// candidates; the histogram and the bins' starts (before them, the waves'
+// candidate-vector lists); the arrays the pool is formed from.
+struct RowLds {
+    PoolLds p;                 // p.k2: also the ranked candidates, over the codes
+    int codes, keys, hist, start;
+};
+__host__ __device__ inline int row_cap(bool ls) { return ls ? 2048 : 960; }
+__host__ __device__ inline RowLds row_lds(int S, bool ls, int nb, int ntb) {
+    RowLds L;
+    const int cap = row_cap(ls), nbins = ls ? 2 * NBINS : NBINS;
+    const int S2 = S > 256 ? S : 256;
+    int o = 16 * ntb * nb;                          // codes
+    if (o < 8 * cap) o = 8 * cap;
+    L.codes = 0;
+    L.p.m = 0;
+    L.p.k2 = 0;
+    L.keys = o;
+    o += 8 * cap;
+    L.hist = o;
+    o += 4 * nbins;
+    L.start = o;
+    const int lists = 4 * (ntb / WAVE) * WAVE * (ls ? 2 : 1);
+    o += lists > 4 * nbins ? lists : 4 * nbins;
+    L.p.top = o;
+    o += pad16(8 * S2);
+    L.p.w1 = o;
+    o += pad16(4 * S);
+    L.p.q = o;
+    o += pad16(4 * S);
+    L.p.wr = o;
+    o += pad16(2 * S);
+    L.p.xs = o;
+    o += pad16(2 * S);
+    L.p.bytes = o;
+    return L;
 }
 
-// SC: the support class -- 0: S <= 128 (two offers per thread), 1: S <= 256
-// (four offers), 2: larger supports (LS).
-template <int DT, int NQ, int SC, int NTB>
-__global__ __launch_bounds__(NTB) void k_expand_row(TreeDev t, LevelArgs a) {
-    constexpr bool LS = SC == 2;
-    constexpr bool four = SC >= 1;
+// The largest of the four 16-bit code offers over the wave.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
+    x = max(x, row_ror<8>(x));
+    x = max(x, row_ror<4>(x));
+    x = max(x, row_ror<2>(x));
+    x = max(x, row_ror<1>(x));
+    return max(max(lane_u32(x, 0), lane_u32(x, 16)), max(lane_u32(x, 32), lane_u32(x, 48)));
+}
+
+// A 16-bit code that at least k of the wave's offers reach (two per lane, or
+// four), the largest one with its two lowest bits clear (a sixteenth of an
+// octave at most below the k-th largest offer): two bits a round, whose three
+// counts do not wait for each other.
+template <bool FOUR>
+__device__ __forceinline__ uint32_t wave_kth_code(uint32_t c1, uint32_t c2, uint32_t c3,
+                                                  uint32_t c4, int k) {
+    uint32_t h = 0;
+    auto reach = [&](uint32_t x) -> bool {
+        int n = __popcll(__ballot(c1 >= x)) + __popcll(__ballot(c2 >= x));
+        if (FOUR) n += __popcll(__ballot(c3 >= x)) + __popcll(__ballot(c4 >= x));
+        return n >= k;
+    };
+#pragma unroll
+    for (int sh = 14; sh >= 2; sh -= 2) {
+        const bool r1 = reach(h | (1u << sh)), r2 = reach(h | (2u << sh)), r3 = reach(h | (3u << sh));
+        h |= (uint32_t)((int)r1 + (int)r2 + (int)r3) << sh;
+    }
+    return h;
+}
+
+// The maximum of a vector, exact in its high 16 bits (fp32: truncated).
+template <int DT>
+__device__ __forceinline__ uint32_t vec_max_raw(const uint4& v) {
+    if (DT) return bf16x8_max_raw(v);
+    return __float_as_uint(fmaxf(fmaxf(__uint_as_float(v.x), __uint_as_float(v.y)),
+                                 fmaxf(__uint_as_float(v.z), __uint_as_float(v.w))));
+}
+
+struct RowArgs {
+    TreeDev t;
+    LevelArgs a;
+};
+
+// LS: supports above kLargeSupport (four offers per lane, larger lists).
+template <int DT, bool LS, int NTB>
+__global__ __launch_bounds__(NTB, 4) void k_expand_row(RowArgs) {
+    const RowArgs& args = kernel_params<RowArgs>();
+    const TreeDev& t = args.t;
+    const LevelArgs& a = args.a;
     constexpr int VEC = DT ? 8 : 4;
     constexpr int NW = NTB / WAVE;
-    constexpr int NB = NQ / EBATCH;
-    constexpr int NM = DT ? NQ / 2 : NQ;
-    constexpr int CV = LS ? CAPV_L : CAPV;      // candidate vectors held
-    constexpr int CC = LS ? CAPC_L : CAPC;      // candidates held
-    static_assert(NQ % (2 * EBATCH) == 0 && NQ <= 64, "batches come in pairs");
-    // candidate-vector masks: bf16 vector 2 qi at bit qi, 2 qi + 1 at bit
-    // HALF + qi; fp32 vector q at bit q
-    using mask_t = typename std::conditional<(NQ > 32), uint64_t, uint32_t>::type;
-    constexpr int HALF = NQ > 32 ? 32 : 16;
+    constexpr int CC = LS ? 2048 : 960;         // candidates held (row_cap)
+    constexpr int NBIN = LS ? 2 * NBINS : NBINS;
+    constexpr int BPT = NBIN > NTB ? NBIN / NTB : 1;   // bins per thread
+    constexpr int KPT = (CC + NTB - 1) / NTB;   // candidates per thread
+    constexpr int RND = LS ? 2 : 1;             // candidate vectors per lane and round
     extern __shared__ __align__(16) uint8_t s_pdyn[];
-    __shared__ __align__(16) uint64_t s_keys_st[LS ? 2 : CAPC];
-    __shared__ int16_t s_rank[LS ? 2 : CAPC];
-    __shared__ int s_cvi_st[LS ? 1 : CAPV];
-    __shared__ int s_hist[LS ? 256 : 1];
     __shared__ int s_thr[2 * NW * 16];
-    __shared__ int s_wn[NW];
+    __shared__ int s_wcode[NW];
     __shared__ int s_cnt;
-    __shared__ uint64_t s_red[2 * NW];
+    __shared__ PoolShared<NTB> ps;
     __shared__ int s_redi[NW];
-    __shared__ int s_tie[NQ][NW];
-    __shared__ int s_pu, s_yi;
+    __shared__ int s_pu;
     __shared__ uint64_t s_u;
-    const PoolLds L = row_lds(t.S, LS);
-    uint64_t* s_top = (uint64_t*)(s_pdyn + L.top);
-    uint64_t* s_k2 = (uint64_t*)(s_pdyn + L.k2);
-    uint64_t* s_keys = LS ? s_top : s_keys_st;
-    int* s_cvi = LS ? (int*)s_k2 : s_cvi_st;
 
     ieee_mode_off();                             // NaN words drop out of the maxima
     const int tid = threadIdx.x, lane = tid % WAVE, wid = tid / WAVE;
@@ -1080,261 +1179,199 @@ __global__ __launch_bounds__(NTB) void k_expand_row(TreeDev t, LevelArgs a) {
     const int S = t.S, K = t.K, V = t.V;
     const int level = a.level;
     const int64_t nb = (int64_t)b * t.NN;
-    const int NVR = (V + VEC - 1) / VEC;          // vectors of the row, <= NTB * NQ
+    const int NVR = (V + VEC - 1) / VEC;          // vectors of the row, <= 64 * NTB
     const int NVF = V / VEC;                       // whole vectors
-    const int nsel = S;                            // S <= V
+    const int NB = (NVR + NTB * EBATCH - 1) / (NTB * EBATCH);
+    const RowLds L = row_lds(S, LS, NB, NTB);
+    uint4* s_code = (uint4*)(s_pdyn + L.codes);
+    uint64_t* s_keys = (uint64_t*)(s_pdyn + L.keys);
+    uint64_t* s_ord = (uint64_t*)(s_pdyn + L.p.k2);
+    uint64_t* s_top = (uint64_t*)(s_pdyn + L.p.top);
+    int* s_hist = (int*)(s_pdyn + L.hist);
+    int* s_start = (int*)(s_pdyn + L.start);
     const char* base = (const char*)a.logits + (int64_t)row * t.stride * (DT ? 2 : 4);
 
-    // the parent's frontier entry is loaded while the row streams (after
-    // its first loads are issued when there are four batches or more), its
-    // draw taken while the last batch is in flight, and both checked after
-    // the row is streamed
+    // the parent's frontier entry is loaded while the row streams (after its
+    // first loads are issued when there are several batches), its draw taken
+    // while the last batches are in flight, and both checked after the row is
+    // streamed
     RowParentRaw rp{0, 0ull};
     bool has_u = false;
     if (tid == 0) s_cnt = 0;
-    if (!LS)
-        for (int i = tid; i < S; i += NTB) s_top[i] = 0ull;   // id -1 until ranked
+    for (int i = tid; i < S; i += NTB) s_top[i] = 0ull;   // id -1 until ranked
+    for (int i = tid; i < NBIN; i += NTB) s_hist[i] = 0;
 
-    // ---- the row, streamed: vector q of this thread is vidx(q) ------------
-    // vm: each vector's maximum -- bf16: the 16-bit order codes of vectors
-    // 2 qi (low half) and 2 qi + 1 (high half) in vm[qi]; fp32: its bits
-    uint32_t vm[NM];
-    uint32_t c1 = 0, c2 = 0, c3 = 0, c4 = 0;
-    rs_ushort2 p1 = {0, 0}, p2 = {0, 0};
-    // vector q of this thread: lane `lane` of the 64-vector slot (wid + q)
-    // mod NW of block stride q.  Rotating the slot spreads every wave's
-    // reads over all offsets (mod one block stride, 8 KB) in the row; with
-    // a fixed slot per wave its reads kept to one offset, and the waves of
-    // a block finished streaming up to several µs apart.
+    // ---- the row, streamed ---------------------------------------------------
+    // Vector q of this thread: lane `lane` of the 64-vector slot (wid + q) mod
+    // NW of block stride q.  Rotating the slot spreads every wave's reads over
+    // all offsets of a stride; with a fixed slot per wave the waves of a block
+    // finished streaming up to several µs apart.
     const int wsu = __builtin_amdgcn_readfirstlane(wid);
     auto vidx = [&](int q) -> int { return (((wsu + q) & (NW - 1)) * WAVE + lane) + NTB * q; };
     auto load_batch = [&](uint4 (&r)[EBATCH], int bt) {
-        // plain loads when every lane of the block reads whole vectors
-        if (NTB - 1 + NTB * (bt * EBATCH + EBATCH - 1) < NVF) {
+        if (NTB * (bt * EBATCH + EBATCH) <= NVF) {
 #pragma unroll
             for (int e = 0; e < EBATCH; ++e)
                 r[e] = load_stream16(base + (int64_t)vidx(bt * EBATCH + e) * 16);
         } else {
 #pragma unroll
-            for (int e = 0; e < EBATCH; ++e)
-                r[e] = load_row_vec<DT>(base, vidx(bt * EBATCH + e), V);
-        }
-    };
-    auto proc_batch = [&](const uint4 (&r)[EBATCH], int bt) {
-        if (DT) {
-#pragma unroll
-            for (int e = 0; e < EBATCH; e += 2) {
-                const uint32_t lo = bf16x8_max_raw(r[e]);
-                const uint32_t hi = bf16x8_max_raw(r[e + 1]);
-                const int qi = (bt * EBATCH + e) / 2;
-                const rs_ushort2 cq = bf16x2_codes(__builtin_amdgcn_perm(hi, lo, 0x07060302u));
-                vm[qi] = __builtin_bit_cast(uint32_t, cq);
-                p2 = __builtin_elementwise_max(p2, __builtin_elementwise_min(p1, cq));
-                p1 = __builtin_elementwise_max(p1, cq);
-            }
-        } else {
-#pragma unroll
             for (int e = 0; e < EBATCH; ++e) {
-                const float mx = fmaxf(fmaxf(elem<DT>(r[e], 0), elem<DT>(r[e], 1)),
-                                       fmaxf(elem<DT>(r[e], 2), elem<DT>(r[e], 3)));
-                vm[bt * EBATCH + e] = __float_as_uint(mx);
-                const uint32_t cv = ord32(mx) >> 16;
-                c4 = max(c4, min(c3, cv));
-                c3 = max(c3, min(c2, cv));
-                c2 = max(c2, min(c1, cv));
-                c1 = max(c1, cv);
+                const int q = bt * EBATCH + e;
+                if (NTB * (q + 1) <= NVF) r[e] = load_stream16(base + (int64_t)vidx(q) * 16);
+                else r[e] = load_row_vec<DT>(base, vidx(q), V);
             }
         }
     };
-    if (NB == 2 && tid == 0) rp = row_parent_load(t, a, b, j);
+    // p1, p2: the two largest codes of the even (low half) and of the odd
+    // vectors
+    rs_ushort2 p1 = {0, 0}, p2 = {0, 0};
+    auto proc_batch = [&](const uint4 (&r)[EBATCH], int bt) {
+        uint32_t cw[EBATCH / 2];
+#pragma unroll
+        for (int e = 0; e < EBATCH; e += 2) {
+            const uint32_t lo = vec_max_raw<DT>(r[e]), hi = vec_max_raw<DT>(r[e + 1]);
+            const rs_ushort2 cq = bf16x2_codes(__builtin_amdgcn_perm(hi, lo, 0x07060302u));
+            cw[e / 2] = __builtin_bit_cast(uint32_t, cq);
+            if (LS) p2 = __builtin_elementwise_max(p2, __builtin_elementwise_min(p1, cq));
+            p1 = __builtin_elementwise_max(p1, cq);
+        }
+        s_code[bt * NTB + tid] = make_uint4(cw[0], cw[1], cw[2], cw[3]);
+    };
+    static_assert(EBATCH == 8, "one 16-byte store of codes per batch");
+    if (NB <= 2 && tid == 0) rp = row_parent_load(t, a, b, j);
     {
         uint4 ra[EBATCH], rb[EBATCH];
         load_batch(ra, 0);
-#pragma unroll
         for (int bt = 0; bt < NB; bt += 2) {
-            load_batch(rb, bt + 1);
+            if (bt + 1 < NB) load_batch(rb, bt + 1);
             proc_batch(ra, bt);
             if (bt + 2 < NB) load_batch(ra, bt + 2);
-            if (NB >= 4 && bt == 0 && tid == 0) rp = row_parent_load(t, a, b, j);
-            // the parent's draw (a serial Philox chain) while the last
-            // batch is in flight, once the parent's load has returned
-            if (bt == NB - 2 && tid == 0 && level > 0) {
+            if (NB > 2 && bt == 0 && tid == 0) rp = row_parent_load(t, a, b, j);
+            // the parent's draw (a serial Philox chain) while the last batch is
+            // in flight, once the parent's load has returned
+            if (bt + 2 >= NB && tid == 0 && level > 0) {
                 rp.u = parent_draw(a, b, rp.pu);
                 has_u = true;
             }
-            proc_batch(rb, bt + 1);
+            if (bt + 1 < NB) proc_batch(rb, bt + 1);
         }
     }
     if (tid == 0) row_parent(t, a, b, j, rp, has_u, &s_pu, &s_u);
-    // bf16: the two largest of each half (four distinct vectors)
-    if (DT) {
-        if constexpr (four) {
-            c1 = p1.x;
-            c2 = p1.y;
-            c3 = p2.x;
-            c4 = p2.y;
-        } else {
-            c1 = max((uint32_t)p1.x, (uint32_t)p1.y);
-            c2 = max(min((uint32_t)p1.x, (uint32_t)p1.y), max((uint32_t)p2.x, (uint32_t)p2.y));
-        }
-    }
 
-    // ---- threshold: h = the nsel-th largest of the offered codes (a lower
-    //      bound of the nsel-th largest vector maximum)
-    uint32_t h = offer_threshold<NTB>(c1, c2, c3, c4, four, nsel, s_thr);
-    if constexpr (LS) {
-        // raised to the nsel-th largest vector maximum: the high byte of its
-        // code, then the low byte, from histograms of the codes >= h
-        auto code_of = [&](int q) -> uint32_t {
-            if (DT) {
-                const rs_ushort2 c = __builtin_bit_cast(rs_ushort2, vm[q / 2]);
-                return (q & 1) ? (uint32_t)c.y : (uint32_t)c.x;
-            }
-            return ord32(__uint_as_float(vm[q])) >> 16;
-        };
-        for (int i = tid; i < 256; i += NTB) s_hist[i] = 0;
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const uint32_t c = code_of(q);
-            if (c >= h && vidx(q) < NVR) atomicAdd(&s_hist[c >> 8], 1);
-        }
-        __syncthreads();
-        const int2 hi8 = suffix_pick256<NTB>(s_hist, nsel, s_thr);
-        if (hi8.x >= 0) {
-            for (int i = tid; i < 256; i += NTB) s_hist[i] = 0;
-            __syncthreads();
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const uint32_t c = code_of(q);
-                if (c >= h && (int)(c >> 8) == hi8.x && vidx(q) < NVR)
-                    atomicAdd(&s_hist[c & 0xFFu], 1);
-            }
-            __syncthreads();
-            const int2 lo8 = suffix_pick256<NTB>(s_hist, nsel - hi8.y, s_thr);
-            if (lo8.x >= 0) h = max(h, ((uint32_t)hi8.x << 8) | (uint32_t)lo8.x);
-        }
-    }
-    // the parent record, for the children written at the end
-    const ParentRec pr = (tid < K) ? parent_rec(t, level, nb, s_pu) : ParentRec{1.0, 0ull};
-    const float tau = (h << 16) > ord32(-INFINITY) ? unord32(h << 16) : -INFINITY;
-
-    // ---- candidate vectors (maximum >= tau): every thread marks its own in
-    //      a bit mask (bf16: bit qi is vector 2 qi, bit 16 + qi vector
-    //      2 qi + 1; fp32: bit q is vector q), the wave's offsets come from
-    //      one prefix sum, and every wave appends them to its region of
-    //      s_cvi; if a wave has more than its region holds, but all fit, they
-    //      are written again into one list with slots reserved per wave
-    constexpr int WCAPR = CV / NW;
-    mask_t take = 0;
-    {
-        // vectors of this thread inside the row: q < nqv
-        int nqv = min(NQ, max(0, (NVR - lane - (NTB - WAVE) + NTB - 1) / NTB));
-        while (nqv < NQ && vidx(nqv) < NVR) ++nqv;      // at most twice
-        if (DT) {
-            // code >= h is maximum >= tau, except that a -0 maximum passes
-            // tau = +0 as a logit (code of -0: 0x7FFF)
-            const uint32_t hc = (h == 0x8000u) ? 0x7FFFu : h;
-            const rs_ushort2 h2 = {(unsigned short)hc, (unsigned short)hc};
-            const rs_ushort2 one = {1, 1};
-            mask_t below = 0;
-#pragma unroll
-            for (int qi = 0; qi < NM; ++qi) {
-                const rs_ushort2 c = __builtin_bit_cast(rs_ushort2, vm[qi]);
-                const rs_ushort2 d = __builtin_elementwise_min(__builtin_elementwise_sub_sat(h2, c), one);
-                if constexpr (HALF == 16)
-                    below |= __builtin_bit_cast(uint32_t, d) << qi;
-                else
-                    below |= ((mask_t)d.x << qi) | ((mask_t)d.y << (HALF + qi));
-            }
-            const mask_t vlo = ((mask_t)1 << ((nqv + 1) >> 1)) - 1u;
-            const mask_t vhi = (((mask_t)1 << (nqv >> 1)) - 1u) << HALF;
-            take = ~below & (vlo | vhi);
-        } else {
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) take |= (mask_t)(__uint_as_float(vm[q]) >= tau) << q;
-            take &= nqv >= 8 * (int)sizeof(mask_t) ? ~(mask_t)0 : ((mask_t)1 << nqv) - 1u;
-        }
-    }
-    const int tn = __popcll((uint64_t)take);
-    const int texcl = wave_excl_scan(tn);
-    auto push_vectors = [&](int pos, int* dst, int cap) {
-        for (mask_t mk = take; mk != 0u; mk &= mk - 1u) {
-            const int bb = __builtin_ctzll((uint64_t)mk);
-            const int q = DT ? ((bb < HALF) ? 2 * bb : 2 * (bb - HALF) + 1) : bb;
-            if (pos < cap) dst[pos] = vidx(q);
-            ++pos;
-        }
-    };
-    push_vectors(texcl, s_cvi + wid * WCAPR, WCAPR);
-    if (lane == WAVE - 1) s_wn[wid] = texcl + tn;
+    // ---- threshold: every wave's ceil(S / NW)-th largest offered code, and the
+    //      least of them: at least S vectors reach it.  (Vectors past the row
+    //      have code 0 (bf16) or that of -inf, at most every element's.)
+    const uint32_t c1 = p1.x, c2 = p1.y, c3 = p2.x, c4 = p2.y;
+    const uint32_t wh = wave_kth_code<LS>(c1, c2, c3, c4, (S + NW - 1) / NW);
+    const uint32_t wm = wave_max_u32(max(c1, c2));
+    if (lane == 0) s_wcode[wid] = (int)(wh | (wm << 16));
     __syncthreads();
-    int wn[NW], nv = 0, wbefore = 0;
-    bool ovf = false;
+    uint32_t h = 0xFFFFu, cmax = 0;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-        wn[w] = s_wn[w];
-        ovf |= wn[w] > WCAPR;
-        wbefore += (w < wid) ? wn[w] : 0;
-        nv += wn[w];
+        const uint32_t x = (uint32_t)s_wcode[w];
+        h = min(h, x & 0xFFFFu);
+        cmax = max(cmax, x >> 16);
     }
-    const bool contig = ovf && nv <= CV;
-    if (contig) {
-        push_vectors(wbefore + texcl, s_cvi, CV);
-        __syncthreads();
-    }
-    // ---- their elements >= tau (candidate vectors read again, one per
-    //      thread and round; small supports have a single round)
-    auto gather = [&](int e) {
-        uint4 x = make_uint4(0, 0, 0, 0);
-        int e0 = V;
-        if (e < nv) {
-            // entry e of the concatenated regions (or of the one list)
-            int w = 0, off = e;
-            if (!contig) {
+    // the parent record, for the children written at the end
+    const ParentRec pr = parent_rec(t, a, b, tid < K, s_pu);
+
+    // ---- candidates: elements at or above the threshold --------------------
+    float tau;
+    int cnt;
+    for (bool again = false;; again = true) {
+        tau = (h << 16) > ord32(-INFINITY) ? unord32(h << 16) : -INFINITY;
+        // this thread's vectors of maximum >= tau: bit 8 bt + e is vector 2 e
+        // of batch bt for e < 4, vector 2 e - 7 above.  A code >= h is a
+        // maximum >= tau, except that a -0 maximum (code 0x7FFF) passes tau =
+        // +0 as a logit; below the code of -inf there is only padding.
+        const uint32_t hc = (h == 0x8000u) ? 0x7FFFu : max(h, 0x7Fu);
+        const rs_ushort2 h2 = {(unsigned short)hc, (unsigned short)hc};
+        const rs_ushort2 one = {1, 1};
+        uint64_t take = 0;
+        for (int bt0 = 0; bt0 < NB; bt0 += 4) {
+            uint4 cw[4];
 #pragma unroll
-                for (int q = 0; q < NW - 1; ++q) {
-                    const bool past = off >= wn[q] && w == q;
-                    off -= past ? wn[q] : 0;
-                    w += past ? 1 : 0;
+            for (int u = 0; u < 4; ++u) cw[u] = s_code[min(bt0 + u, NB - 1) * NTB + tid];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t* c = &cw[u].x;
+                uint32_t below = 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    below |= __builtin_bit_cast(
+                                 uint32_t, __builtin_elementwise_min(
+                                               __builtin_elementwise_sub_sat(
+                                                   h2, __builtin_bit_cast(rs_ushort2, c[e])),
+                                               one)) << e;
+                const uint32_t m8 = ~((below & 0xFu) | (below >> 12)) & 0xFFu;
+                if (bt0 + u < NB) take |= (uint64_t)m8 << (8 * (bt0 + u));
+            }
+        }
+        // in rounds of up to RND * 64 vectors per wave: listed, read, and their
+        // elements >= tau appended
+        int* list = (int*)s_start + wid * (WAVE * RND);
+        for (;;) {
+            const int tn = __popcll(take);
+            const int excl = wave_excl_scan(tn);
+            const int total = (int)lane_u32((uint32_t)(excl + tn), WAVE - 1);
+            if (total == 0) break;
+            for (int pos = excl; take != 0 && pos < WAVE * RND; take &= take - 1, ++pos) {
+                const int bb = __builtin_ctzll(take);
+                const int e = bb & 7;
+                list[pos] = vidx((bb & ~7) + (e < 4 ? 2 * e : 2 * e - 7));
+            }
+            wave_sync();
+            uint4 x[RND];
+            int e0[RND];
+#pragma unroll
+            for (int r = 0; r < RND; ++r) {
+                x[r] = make_uint4(0, 0, 0, 0);
+                e0[r] = V;
+                if (r * WAVE + lane < total) {
+                    const int vi = list[r * WAVE + lane];
+                    x[r] = load_row_vec<DT>(base, vi, V);
+                    e0[r] = vi * VEC;
                 }
             }
-            const int vi = s_cvi[w * WCAPR + off];
-            x = load_row_vec<DT>(base, vi, V);
-            e0 = vi * VEC;
-        }
-        int n = 0;
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) n += (elem<DT>(x, k) >= tau) & (e0 + k < V);
-        const int excl = wave_excl_scan(n);
-        int cb = 0;
-        if (lane == WAVE - 1) cb = atomicAdd(&s_cnt, excl + n);
-        int pos = (int)lane_u32((uint32_t)cb, WAVE - 1) + excl;
+            for (int r = 0; r < RND; ++r) {
+                if (r * WAVE >= total) break;
+                int n = 0;
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) {
-            const float v = elem<DT>(x, k);
-            if (v >= tau && e0 + k < V) {
-                if (pos < CC) s_keys[pos] = logit_key(v, (uint32_t)(e0 + k));
-                ++pos;
+                for (int k = 0; k < VEC; ++k) n += (elem<DT>(x[r], k) >= tau) & (e0[r] + k < V);
+                const int ex = wave_excl_scan(n);
+                int cb = 0;
+                if (lane == WAVE - 1) cb = atomicAdd(&s_cnt, ex + n);
+                int pos = (int)lane_u32((uint32_t)cb, WAVE - 1) + ex;
+#pragma unroll
+                for (int k = 0; k < VEC; ++k) {
+                    const float v = elem<DT>(x[r], k);
+                    if (v >= tau && e0[r] + k < V) {
+                        if (pos < CC) s_keys[pos] = logit_key(v, (uint32_t)(e0[r] + k));
+                        ++pos;
+                    }
+                }
             }
+            wave_sync();
         }
-    };
-    if (!ovf || contig) {
-        if constexpr (LS || CAPV > NTB) {
-            for (int e = tid; e - tid < nv; e += NTB) gather(e);
-        } else {
-            gather(tid);                          // nv <= CAPV <= NTB
-        }
-    } else if (tid == 0) {
-        s_cnt = CC + 1;                          // too many: exact fallback below
+        __syncthreads();
+        cnt = s_cnt;
+        if (cnt <= CC || again) break;
+        // Too many candidates: the row's large values are unevenly spread
+        // over the waves (sorted rows, say).  Once more with the threshold
+        // that S of the whole block's offers reach.
+        h = max(h, offer_threshold<NTB>(c1, c2, c3, c4, LS, S, s_thr));
+        if (tid == 0) s_cnt = 0;
+        __syncthreads();
     }
-    __syncthreads();
-    int cnt = s_cnt;
     if (cnt > CC) {
+        // massive ties at the threshold: exact selection from the row
+        int (*s_tie)[NW] = (int (*)[NW])(s_pdyn + L.start);
         __syncthreads();
         if (tid == 0) s_cnt = 0;
-        exact_select_fallback<DT, NTB, NQ>(
-            base, V, 0, h, nsel, CC,
+        exact_select_fallback<DT, NTB, ROW_BATCHES * EBATCH>(
+            base, V, 0, h, S, CC,
             [=](float v, int id) {
                 const int pos = atomicAdd(&s_cnt, 1);
                 if (pos < CC) s_keys[pos] = logit_key(v, (uint32_t)id);
@@ -1343,28 +1380,88 @@ __global__ __launch_bounds__(NTB) void k_expand_row(TreeDev t, LevelArgs a) {
         cnt = min(fallback_count(&s_cnt), CC);
     }
 
-    // ---- the support: the top nsel candidates in (logit desc, id asc) order
-    if constexpr (LS) {
-        // sorted in place (padding 0 sorts last; at least nsel entries)
-        const int n2 = pow2_at_least(max(cnt, nsel));
-        for (int i = cnt + tid; i < n2; i += NTB) s_keys[i] = 0ull;
+    // ---- the support: the top S candidates in (logit desc, id asc) order ----
+    // Bins linear in the value over [tau, the row maximum] (a monotone map:
+    // one rounded subtraction, one rounded product), by the high bits of the
+    // order code when tau is -inf or the maximum +inf.
+    const float vmax = unord32(cmax << 16);
+    const bool lin = tau > -INFINITY && vmax < INFINITY;
+    const float scale = (float)NBIN / (vmax - tau);
+    uint64_t key[KPT];
+    int kbin[KPT], kslot[KPT];
+#pragma unroll
+    for (int r = 0; r < KPT; ++r) {
+        const int i = tid + r * NTB;
+        key[r] = 0;
+        kbin[r] = 0;
+        kslot[r] = 0;
+        if (i < cnt) {
+            key[r] = s_keys[i];
+            const float x = lin ? (key_value(key[r]) - tau) * scale
+                                : (float)((uint32_t)(key[r] >> 32) >> 23);
+            kbin[r] = (int)fminf(fmaxf(x, 0.0f), (float)(NBIN - 1));
+            kslot[r] = atomicAdd(&s_hist[kbin[r]], 1);
+        }
+    }
+    __syncthreads();
+    {
+        // thread tid holds bins NBIN - 1 - tid * BPT and the BPT - 1 below it;
+        // a bin starts after the candidates of all higher bins
+        const int top_bin = NBIN - 1 - tid * BPT;
+        int hv[BPT], tot = 0;
+#pragma unroll
+        for (int r = 0; r < BPT; ++r) {
+            hv[r] = top_bin - r >= 0 ? s_hist[top_bin - r] : 0;
+            tot += hv[r];
+        }
+        const int ex = wave_excl_scan(tot);
+        if (lane == WAVE - 1) s_redi[wid] = ex + tot;
         __syncthreads();
-        bitonic_sort_desc<NTB>(s_keys, n2);
-    } else {
-        rank_keys<NTB>(s_keys, cnt, s_rank, s_top, nsel);     // placed as ranked
+        int st = ex;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) st += (w < wid) ? s_redi[w] : 0;
+#pragma unroll
+        for (int r = 0; r < BPT; ++r) {
+            if (top_bin - r >= 0) s_start[top_bin - r] = st;
+            st += hv[r];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < KPT; ++r) {
+        if (tid + r * NTB < cnt) {
+            const int st = s_start[kbin[r]];
+            if (st < S) s_ord[st + kslot[r]] = key[r];
+            kslot[r] = st;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < KPT; ++r) {
+        if (tid + r * NTB < cnt && kslot[r] < S) {
+            const int n = s_hist[kbin[r]];
+            const uint64_t* in = s_ord + kslot[r];
+            int rk = kslot[r], q = 0;
+            for (; q + 4 <= n; q += 4) {
+                const uint64_t k0 = in[q], k1 = in[q + 1], k2 = in[q + 2], k3 = in[q + 3];
+                rk += (int)(k0 > key[r]) + (int)(k1 > key[r]) + (int)(k2 > key[r]) +
+                      (int)(k3 > key[r]);
+            }
+            for (; q < n; ++q) rk += (int)(in[q] > key[r]);
+            if (rk < S) s_top[rk] = key[r];
+        }
     }
     __syncthreads();
 
-    pool_form<NTB>(t, a, row, s_pdyn, L, s_pu, pr, s_u, s_red, &s_yi);
-    if (level + 1 >= t.D) return;
-    select_frontier(t, a, b, s_top, s_k2);
+    constexpr int SC = LS ? SMAX : kLargeSupport;    // the largest support of the class
+    pool_form<NTB, (SC + NTB - 1) / NTB>(t, a, row, s_pdyn, L.p, s_pu, pr, s_u, ps);
+    select_frontier(t, a, b, j, pr, s_top, s_ord, ps);
 }
 
 // Four blocks per CU keep enough loads in flight; the largest chunk variant
 // holds twice the registers and runs at two.
 template <int DT, int NVC>
-__global__ __launch_bounds__(NTC) void k_select(TreeDev t,
-                                                                                         LevelArgs a) {
+__global__ __launch_bounds__(NTC) void k_select(TreeDev t, LevelArgs a) {
     select_block<DT, NVC>(t, a);
 }
 template <int DT>
@@ -1460,84 +1557,79 @@ hipError_t launch_row_wsum(const TreeDev& t, const LevelArgs& a, hipStream_t s) 
     return hipGetLastError();
 }
 
-// Vectors per thread k_expand_row needs for a row of V elements (16, 32 or 48),
-// or 0 if the row is too long for it.
-int expand_row_nq(int dtype, int V) {
+constexpr size_t kRowLdsMax = 156 * 1024;   // dynamic LDS of a block (160 KB less the static)
+
+static size_t row_shm(int dtype, int V, int S, int ntb) {
     const int nvr = (V + (dtype ? 8 : 4) - 1) / (dtype ? 8 : 4);
-    if (nvr <= NTE * 16) return 16;
-    if (nvr <= NTE * 32) return 32;
-    if (nvr <= NTE * 48) return 48;
+    const int nb = (nvr + ntb * EBATCH - 1) / (ntb * EBATCH);
+    return (size_t)row_lds(S, S > kLargeSupport, nb, ntb).p.bytes;
+}
+
+// Threads of a k_expand_row block for a row of V elements: 512 (64 vectors
+// each: 262,144 bf16 or 131,072 fp32 elements), or 1024 for the fp32 rows
+// beyond; 0 if the row is too long for either or its LDS does not fit.
+int expand_row_threads(int dtype, int V, int S) {
+    const int nvr = (V + (dtype ? 8 : 4) - 1) / (dtype ? 8 : 4);
+    for (int ntb : {NTE, 2 * NTE})
+        if (nvr <= ntb * EBATCH * ROW_BATCHES)
+            return row_shm(dtype, V, S, ntb) <= kRowLdsMax ? ntb : 0;
     return 0;
 }
 
+template <int DT>
+static const void* row_fn(int S, int ntb) {
+    if (S > kLargeSupport)
+        return ntb == NTE ? (const void*)&k_expand_row<DT, true, NTE>
+                          : (const void*)&k_expand_row<DT, true, 2 * NTE>;
+    if (ntb == NTE / 2) return (const void*)&k_expand_row<DT, false, NTE / 2>;
+    return ntb == NTE ? (const void*)&k_expand_row<DT, false, NTE>
+                      : (const void*)&k_expand_row<DT, false, 2 * NTE>;
+}
+static const void* row_fn(const TreeDev& t, int ntb) {
+    return t.dtype ? row_fn<1>(t.S, ntb) : row_fn<0>(t.S, ntb);
+}
+
 // A level of more rows than the device holds 512-thread blocks at once
-// runs 256-thread blocks with twice the vectors per thread (rows of up to
-// 32 vectors per 512 threads), which the device holds twice as many of: the
-// rows past the first round no longer wait for a whole block to end.
-static bool row_narrow(const TreeDev& t, int rows, int nq) {
-    if (nq > 32) return false;
+// runs 256-thread blocks, of which it holds more (rows of up to 64 vectors
+// per thread, supports of up to 256): the rows past the first round no
+// longer wait for a whole block to end.
+static bool row_narrow(const TreeDev& t, int rows) {
+    const int nvr = (t.V + (t.dtype ? 8 : 4) - 1) / (t.dtype ? 8 : 4);
+    if (nvr > NTE / 2 * EBATCH * ROW_BATCHES || t.S > kLargeSupport) return false;
     if (t.row_narrow >= 0) return t.row_narrow == 1;
     return t.row_slots > 0 && rows > t.row_slots;
 }
 
-template <int DT, int SC>
-static hipError_t launch_row(const TreeDev& t, const LevelArgs& a, int nq, hipStream_t s) {
-    const dim3 grid(t.B * a.P);
-    const size_t shm = (size_t)row_lds(t.S, SC == 2).bytes;
-    const bool narrow = row_narrow(t, t.B * a.P, nq);
-    if (narrow && nq == 32)
-        k_expand_row<DT, 64, SC, NTE / 2><<<grid, NTE / 2, shm, s>>>(t, a);
-    else if (narrow && nq == 16)
-        k_expand_row<DT, 32, SC, NTE / 2><<<grid, NTE / 2, shm, s>>>(t, a);
-    else if (nq == 16) k_expand_row<DT, 16, SC, NTE><<<grid, NTE, shm, s>>>(t, a);
-    else if (nq == 32) k_expand_row<DT, 32, SC, NTE><<<grid, NTE, shm, s>>>(t, a);
-    else if (nq == 48) k_expand_row<DT, 48, SC, NTE><<<grid, NTE, shm, s>>>(t, a);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
-}
-
-template <int DT>
-static hipError_t launch_row_dt(const TreeDev& t, const LevelArgs& a, int nq, hipStream_t s) {
-    if (t.S > kLargeSupport) return launch_row<DT, 2>(t, a, nq, s);
-    if (t.S > NTE / 4) return launch_row<DT, 1>(t, a, nq, s);
-    return launch_row<DT, 0>(t, a, nq, s);
-}
-
-template <int DT, int SC>
-static const void* row_fn(int nq) {
-    if (nq == 16) return (const void*)&k_expand_row<DT, 16, SC, NTE>;
-    if (nq == 32) return (const void*)&k_expand_row<DT, 32, SC, NTE>;
-    if (nq == 48) return (const void*)&k_expand_row<DT, 48, SC, NTE>;
-    return nullptr;
-}
-
-template <int DT>
-static const void* row_fn_dt(int S, int nq) {
-    if (S > kLargeSupport) return row_fn<DT, 2>(nq);
-    if (S > NTE / 4) return row_fn<DT, 1>(nq);
-    return row_fn<DT, 0>(nq);
-}
-
 // How many 512-thread blocks of this tree's row kernel the device holds at
-// once (0 when the rows are too long for the row kernel).
+// once (0 when the rows are too long for them); raises the kernels' limit on
+// dynamic LDS.
 hipError_t expand_row_slots(const TreeDev& t, int* slots) {
     *slots = 0;
-    const int nq = expand_row_nq(t.dtype, t.V);
-    const void* fn = t.dtype ? row_fn_dt<1>(t.S, nq) : row_fn_dt<0>(t.S, nq);
-    if (!fn) return hipSuccess;
     int dev = 0, cus = 0, per = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e == hipSuccess)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per, fn, NTE, (size_t)row_lds(t.S, t.S > kLargeSupport).bytes);
-    if (e == hipSuccess) *slots = per * cus;
+    const int wide = t.dense ? 0 : expand_row_threads(t.dtype, t.V, t.S);
+    for (int ntb : {NTE / 2, wide}) {
+        if (e != hipSuccess || wide == 0) break;
+        if (ntb == NTE / 2 && (t.S > kLargeSupport || wide != NTE)) continue;
+        e = hipFuncSetAttribute(row_fn(t, ntb), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)kRowLdsMax);
+        if (e == hipSuccess && ntb == NTE) {
+            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, row_fn(t, ntb), ntb,
+                                                             row_shm(t.dtype, t.V, t.S, ntb));
+            if (e == hipSuccess) *slots = per * cus;
+        }
+    }
     return e;
 }
 
 hipError_t launch_expand_row(const TreeDev& t, const LevelArgs& a, hipStream_t s) {
-    const int nq = expand_row_nq(t.dtype, t.V);
-    return t.dtype ? launch_row_dt<1>(t, a, nq, s) : launch_row_dt<0>(t, a, nq, s);
+    const int rows = t.B * a.P;
+    const int ntb = row_narrow(t, rows) ? NTE / 2 : expand_row_threads(t.dtype, t.V, t.S);
+    if (ntb == 0) return hipErrorInvalidValue;
+    RowArgs ra{t, a};
+    void* args[] = {&ra};
+    return hipLaunchKernel(row_fn(t, ntb), dim3(rows), dim3(ntb), args, row_shm(t.dtype, t.V, t.S, ntb), s);
 }
 
 }  // namespace rheo

@@ -64,213 +64,217 @@ __device__ __forceinline__ void rank_all(const uint64_t* keys, int n, int16_t* r
     if (i < n && sub == 0) rank[i] = (int16_t)c;
 }
 
-// Synchronisation and sums over the NT threads that form a pool: one wave
-// (small supports) or the whole block.
-template <int NT>
-__device__ __forceinline__ void psync() {
-    if (NT == WAVE) wave_sync();
-    else __syncthreads();
+// Sum over groups of F adjacent lanes (F = 1, 2, 4 or 8; DPP moves), in every
+// lane.
+__device__ __forceinline__ uint32_t lanes_sum(uint32_t x, int F) {
+    if (F >= 2) x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, false);
+    if (F >= 4) x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, false);
+    if (F >= 8) x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, false);
+    return x;
 }
 
-// Descending bitonic sort of n 64-bit keys in LDS (n a power of two) by NT
-// threads; the caller has synchronised after writing the keys, and the sort
-// ends with a barrier.  Compare-exchange pair i of a stage with distance j
-// joins positions lo = ((i & ~(j - 1)) << 1) | (i & (j - 1)) and lo + j;
-// for j <= WAVE every position a wave touches lies in the 2 * WAVE-wide
-// window of its own pair indices, so consecutive such stages only need the
-// wave's own accesses ordered.
+// LDS a block's pool and frontier selection exchange through.
 template <int NT>
-__device__ __forceinline__ void bitonic_sort_desc(uint64_t* k, int n) {
-    const int tid = threadIdx.x % NT;
-    const int half = n >> 1;
-    for (int kk = 2; kk <= n; kk <<= 1) {
-        for (int j = kk >> 1; j > 0; j >>= 1) {
-            for (int i = tid; i < half; i += NT) {
-                const int lo = ((i & ~(j - 1)) << 1) | (i & (j - 1));
-                const int hi = lo + j;
-                const uint64_t x = k[lo], y = k[hi];
-                const bool desc = (lo & kk) == 0;
-                if ((x < y) == desc) {
-                    k[lo] = y;
-                    k[hi] = x;
-                }
-            }
-            const int jn = (j > 1) ? (j >> 1) : kk;      // the next stage's distance
-            if (j > WAVE || jn > WAVE) psync<NT>();
-            else wave_sync();
-        }
-    }
-    psync<NT>();
-}
-template <int NT>
-__device__ __forceinline__ uint64_t psum(uint64_t v, uint64_t* sh) {
-    if (NT == WAVE) return wave_sum_u64(v);
-    return block_sum_u64<NT>(v, sh);
-}
-template <int NT>
-__device__ __forceinline__ void psum2(uint64_t a, uint64_t b, uint64_t* sh, uint64_t* ra,
-                                      uint64_t* rb) {
-    if (NT == WAVE) {
-        *ra = wave_sum_u64(a);
-        *rb = wave_sum_u64(b);
-    } else {
-        block_sum2_u64<NT>(a, b, sh, ra, rb);
-    }
-}
-// Totals of a and b over the pool's NT threads and the exclusive prefix of
-// b in thread order, in one exchange (sh: 2 * NT / WAVE words for a block).
-template <int NT>
-__device__ __forceinline__ void psum2_scan(uint64_t a, uint64_t b, uint64_t* sh, uint64_t* ra,
-                                           uint64_t* rb, uint64_t* b_before) {
-    const uint64_t binc = wave_incl_scan_u64(b);
-    const uint64_t asum = wave_sum_u64(a);
-    if (NT == WAVE) {
-        *ra = asum;
-        *rb = lane_u64(binc, WAVE - 1);
-        *b_before = binc - b;
-        return;
-    }
-    constexpr int NW = NT / WAVE;
-    const int w = threadIdx.x / WAVE, l = threadIdx.x % WAVE;
-    __syncthreads();
-    if (l == WAVE - 1) {
-        sh[w] = asum;
-        sh[NW + w] = binc;
-    }
-    __syncthreads();
-    uint64_t x = 0, y = 0, before = 0;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        x += sh[i];
-        y += sh[NW + i];
-        before += (i < w) ? sh[NW + i] : 0ull;
-    }
-    *ra = x;
-    *rb = y;
-    *b_before = before + binc - b;
-}
-// Exclusive prefix sum of one 64-bit value per thread over the pool's NT
-// threads (sh: NT / WAVE words for a block); *total receives the sum.
-template <int NT>
-__device__ __forceinline__ uint64_t pscan_excl(uint64_t v, uint64_t* sh, uint64_t* total) {
-    if (NT == WAVE) {
-        const uint64_t inc = wave_incl_scan_u64(v);
-        *total = lane_u64(inc, WAVE - 1);
-        return inc - v;
-    }
-    return block_excl_scan_u64<NT>(v, sh, total);
-}
-template <int NT>
-__device__ __forceinline__ bool pany(bool p) {
-    if (NT == WAVE) return __ballot(p) != 0ull;
-    return __syncthreads_or(p) != 0;
-}
+struct PoolShared {
+    uint64_t w1[NT / WAVE], q[NT / WAVE];   // the waves' weight totals
+    int tie[NT / WAVE];
+    int yi;                                  // Y's place in the support
+    int last;                                // the sequence's last row
+    uint64_t own_score[16], own_path[16];    // the row's own children
+    int own_tok[16];
+};
 
-// The parent's path score and slot path (1 and 0 for the root), read early
-// by the threads that later write the children.
+// The parent's path score and slot path (1 and 0 for the root) and the mark
+// of this level's children words, read early by the threads that later
+// write the children.
 struct ParentRec {
     double score;
     uint64_t path;
+    uint64_t mark;
 };
-__device__ __forceinline__ ParentRec parent_rec(const TreeDev& t, int level, int64_t nb, int pu) {
-    ParentRec p{1.0, 0ull};
-    if (level > 0) {
-        p.score = t.score[nb + pu];
-        p.path = t.path[nb + pu];
+__device__ __forceinline__ ParentRec parent_rec(const TreeDev& t, const LevelArgs& a, int b,
+                                                bool mine, int pu) {
+    ParentRec p{1.0, 0ull, 0ull};
+    if (a.level > 0) {
+        p.mark = t.fr_mark[b];
+        if (mine) {
+            const Node& nd = t.node[(int64_t)b * t.NN + pu];
+            p.score = nd.score;
+            p.path = nd.path;
+        }
     }
     return p;
 }
 
-// One child record of expanded row j (slot s, 0-based; App. C.1): the
-// fields the frontier selection reads in other blocks (token, score, path)
-// are published with agent-scope atomics.
+// Children words: the fields of a level's new children that the frontier
+// selection reads in another block, [B][3][NE * K]: score, slot path, token,
+// each with the launch's mark in its top bit (a score is at most 1, a path
+// below 2^60).  The mark flips with every launch that uses the words (the
+// sequence's last row flips it once all rows have arrived), so a word that
+// carries it is this launch's.  Agent-scope stores and loads.
+constexpr uint64_t kMark = 1ull << 63;
+__device__ __forceinline__ uint64_t* child_words(const TreeDev& t, int b) {
+    return t.fr_words + (int64_t)b * 3 * t.NE * t.K;
+}
+
+// One child record of expanded row j (slot s, 0-based; App. C.1), published
+// for the sequence's last row and left in LDS for this one.
 // tail: the child's place in its parent's stored tail (-1: not in it)
-__device__ __forceinline__ void emit_child(const TreeDev& t, int level, int64_t nb, int pu,
-                                           const ParentRec& pr, int uid, int s, int kind,
-                                           int tok, double proxy, double qtrue, int tail) {
-    const double pscore = pr.score;
-    const uint64_t ppath = pr.path;
-    const int64_t o = nb + uid;
-    t.par[o] = pu;
-    t.tidx[o] = tail;
-    t.meta[o] = (level + 1) | ((s + 1) << 8) | (kind << 16);
-    t.proxy[o] = proxy;
-    t.qtrue[o] = qtrue;
-    t.first_child[o] = -1;
-    t.exp_of[o] = -1;
-    __hip_atomic_store(&t.tok[o], tok, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store((uint64_t*)&t.score[o], (uint64_t)__double_as_longlong(__dmul_rn(pscore, proxy)),
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&t.path[o], ppath | ((uint64_t)(s + 1) << (56 - 4 * level)),
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+template <int NT>
+__device__ __forceinline__ void emit_child(const TreeDev& t, const LevelArgs& a, int b, int j,
+                                           int pu, const ParentRec& pr, int s, int kind, int tok,
+                                           double proxy, double qtrue, int tail,
+                                           PoolShared<NT>& ps) {
+    const int level = a.level, K = t.K;
+    const int cb = (level == 0) ? 1 : 1 + K + (level - 1) * t.NE * K;
+    const uint64_t score = (uint64_t)__double_as_longlong(__dmul_rn(pr.score, proxy));
+    const uint64_t path = pr.path | ((uint64_t)(s + 1) << (56 - 4 * level));
+    if (level > 0 && level + 1 < t.D) {
+        const int n = t.NE * K;
+        uint64_t* w = child_words(t, b) + j * K + s;
+        __hip_atomic_store(&w[0], score | pr.mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&w[n], path | pr.mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&w[2 * n], (uint64_t)(uint32_t)tok | pr.mark, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    }
+    ps.own_score[s] = score;
+    ps.own_path[s] = path;
+    ps.own_tok[s] = tok;
+    const int64_t o = (int64_t)b * t.NN + cb + j * K + s;
+    Node nd;
+    nd.score = __longlong_as_double((long long)score);
+    nd.path = path;
+    nd.meta = (level + 1) | ((s + 1) << 8) | (kind << 16);
+    nd.par = pu;
+    nd.tok = tok;
+    nd.tidx = tail;
+    nd.first_child = nd.exp_of = nd.pidx = nd.pad = -1;
+    nd.proxy = proxy;
+    nd.qtrue = qtrue;
+    t.node[o] = nd;
+    t.score[o] = nd.score;
 }
 
 // The root record (level 0 only).
 __device__ __forceinline__ void emit_root(const TreeDev& t, int64_t nb) {
-    t.tok[nb] = -1;
-    t.par[nb] = -1;
-    t.meta[nb] = 0;
-    t.proxy[nb] = 1.0;
-    t.qtrue[nb] = 1.0;
-    t.score[nb] = 1.0;
-    t.path[nb] = 0;
+    Node& nd = t.node[nb];
+    nd.score = 1.0;
+    nd.path = 0;
+    nd.meta = 0;
+    nd.par = -1;
+    nd.tok = -1;
+    nd.tidx = -1;
+    nd.proxy = 1.0;
+    nd.qtrue = 1.0;
 }
 
-// The next frontier (Sec. 2.1; App. C.4, step 1: the next level expands the
-// best-scoring new nodes).  Called by every block of the pool kernel once
-// its children are written: the last row of sequence b to get here ranks
-// the level's P * K new children by priority and keeps the best n_expand
-// (the next level's rows take the Philox draw of each kept node's sampled
-// slot themselves, keyed by this launch's rng_key).  s_hi and s_lo are
-// LDS arrays of at least 256 entries the caller no longer needs.
+// The next frontier (Sec. 2.1; App. C.4, step 1).  Called by every thread of
+// a row's block once wave 0 has emitted the row's children: the last row of
+// sequence b to get here ranks the level's P * K new children by priority
+// and keeps the best n_expand (the next level's rows take the Philox draw
+// of each kept node's sampled slot themselves, keyed by this launch's
+// rng_key).  s_hi and s_lo are LDS arrays of at least 256 entries the caller
+// no longer needs.
+//
+// The arrival is not ordered after the row's children words: a word that has
+// not arrived lacks the mark, and the last row reads it again (its store was
+// issued before the arrival that made this row the last, so it lands whatever
+// that block does next).  So nothing waits for stores to be acknowledged,
+// and every row's words are read while the arrival itself is in flight.
+template <int NT>
 __device__ __forceinline__ void select_frontier(const TreeDev& t, const LevelArgs& a, int b,
-                                                uint64_t* s_hi, uint64_t* s_lo) {
-    __shared__ int s_lastseq;
-    const int tid = threadIdx.x;
+                                                int j, const ParentRec& pr, uint64_t* s_hi,
+                                                uint64_t* s_lo, PoolShared<NT>& ps) {
+    __shared__ int s_tok[256];
+    const int tid = threadIdx.x, lane = tid % WAVE;
     const int level = a.level;
     const int K = t.K, NE = t.NE;
-    const int64_t nb = (int64_t)b * t.NN;
     if (level + 1 >= t.D) return;
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (tid == 0) {
-        const uint32_t old = __hip_atomic_fetch_add(&t.seq_cnt[b], 1u, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-        s_lastseq = old == (uint32_t)(a.P - 1);
-        if (s_lastseq) __hip_atomic_store(&t.seq_cnt[b], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int n = a.P * K;                       // <= 225 <= NT
+    const int cb = (level == 0) ? 1 : 1 + K + (level - 1) * NE * K;
+    const int st = NE * K;
+    uint64_t* w = child_words(t, b) + tid;
+    const bool other = tid < n && tid / K != j;  // a child of another row
+    uint64_t x0 = 0, x1 = 0, x2 = 0;
+    auto load = [&]() {
+        x0 = __hip_atomic_load(&w[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        x1 = __hip_atomic_load(&w[st], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        x2 = __hip_atomic_load(&w[2 * st], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (a.P > 1) {
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);  // (after the children's stores)
+        uint32_t old = 0;
+        if (tid == 0)
+            old = __hip_atomic_fetch_add(&t.seq_cnt[b], 1u, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+        if (other) load();
+        if (tid == 0) {
+            ps.last = old == (uint32_t)(a.P - 1);
+            if (ps.last) {
+                __hip_atomic_store(&t.seq_cnt[b], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&t.fr_mark[b], pr.mark ^ kMark, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
     }
     __syncthreads();
-    if (!s_lastseq) return;
-    const int n = a.P * K;                       // <= 225
-    const int cb = (level == 0) ? 1 : 1 + K + (level - 1) * NE * K;
-    // every child's priority key and token in one round of loads
+    if (a.P > 1 && !ps.last) return;
     int tok = -1;
+    uint64_t hi = 0, lo = 0;
     if (tid < n) {
-        const int64_t o = nb + cb + tid;
-        const double sc = __longlong_as_double((long long)__hip_atomic_load(
-            (uint64_t*)&t.score[o], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        const uint64_t pa = __hip_atomic_load(&t.path[o], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        tok = __hip_atomic_load(&t.tok[o], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        uint64_t hi, lo;
-        prio_key(sc, level + 1, pa, hi, lo);
+        if (other) {
+            for (int spin = 0; ((x0 ^ pr.mark) | (x1 ^ pr.mark) | (x2 ^ pr.mark)) & kMark; ++spin) {
+                if (spin > (1 << 20)) {
+                    atomicOr(t.err, 16);
+                    break;
+                }
+                load();
+            }
+            tok = (int)(uint32_t)x2;
+            prio_key(__longlong_as_double((long long)(x0 & ~kMark)), level + 1, x1 & ~kMark, hi, lo);
+        } else {
+            const int s = tid - j * K;
+            tok = ps.own_tok[s];
+            prio_key(__longlong_as_double((long long)ps.own_score[s]), level + 1, ps.own_path[s], hi,
+                     lo);
+        }
         s_hi[tid] = hi;
         s_lo[tid] = lo;
+        s_tok[tid] = tok;
     }
     __syncthreads();
-    if (tid < n) {
-        const uint64_t hi = s_hi[tid], lo = s_lo[tid];
-        int rk = 0;
+    // F adjacent lanes a child (a power of two, at most 8), each over every
+    // F-th key.  Scores first, as the non-negative doubles they are (one
+    // full-rate compare); the rest of the key only where two are equal, which
+    // is rare.
+    int F = 1;
+    while (F < 8 && 2 * F * n <= NT) F *= 2;
+    const int c = tid / F;
+    if (tid - lane >= n * F) return;             // whole waves past the children
+    const int cc = c < n ? c : 0;
+    const double mine = __longlong_as_double((long long)s_hi[cc]);
+    const uint64_t mlo = s_lo[cc];
+    const int ctok = s_tok[cc];
+    int rk = 0, eq = 0;
 #pragma unroll 8
-        for (int q = 0; q < n; ++q) {
-            const uint64_t h = s_hi[q], l = s_lo[q];
-            rk += (int)(h > hi) | ((int)(h == hi) & (int)(l > lo));
-        }
-        if (rk < NE) {
-            t.frontier[(int64_t)b * NE + rk] = cb + tid;
-            t.fr_parent[(int64_t)b * NE + rk] = tid / K;
-            t.fr_token[(int64_t)b * NE + rk] = tok;
-        }
+    for (int q = tid % F; q < n; q += F) {
+        const double h = __longlong_as_double((long long)s_hi[q]);
+        rk += (int)(h > mine);
+        eq += (int)(h == mine);
+    }
+    uint32_t sums = (uint32_t)rk | ((uint32_t)eq << 16);
+    sums = lanes_sum(sums, F);
+    if (__ballot((sums >> 16) > 1u) != 0ull) {
+        rk = 0;
+        for (int q = tid % F; q < n; q += F)
+            rk += (int)(__longlong_as_double((long long)s_hi[q]) == mine) & (int)(s_lo[q] > mlo);
+        sums += lanes_sum((uint32_t)rk, F);
+    }
+    rk = (int)(sums & 0xFFFFu);
+    if (tid % F == 0 && c < n && rk < NE) {
+        t.frontier[(int64_t)b * NE + rk] = cb + c;
+        t.fr_parent[(int64_t)b * NE + rk] = c / K;
+        t.fr_token[(int64_t)b * NE + rk] = ctok;
     }
 }
 

@@ -1,78 +1,141 @@
-// Global pruning of the draft tree (App. C.1, "Path scores and global
-// pruning" and "Tie-breaking rule"): keep the R non-root nodes with the
-// highest path score, ties by depth (shallower first), then left-to-right
-// sibling order.  Scores never grow along a path (Lemma 2) and the tie-break
-// ranks a parent before its children, so the kept set is ancestor-closed.
+// Global pruning of the tree (Sec. 2.1; App. C.1): the R best non-root nodes
+// by (path score desc, depth asc, slot path asc), their pruned order, and
+// what the pruned view and the tree mask read (parent's pruned index, token,
+// depth).  Scores never grow along a path (Lemma 2) and the tie-break ranks a
+// parent before its children, so the kept set is ancestor-closed; every kept
+// node is checked for it.
 //
-// PSPLIT blocks per sequence each load all of its nodes' 128-bit priority
-// keys (unique) into LDS and rank their share of the nodes by counting the
-// larger keys, several lanes per node.  Every block also checks, for its
-// nodes, that a parent's key is larger than its child's: that is what makes
-// the kept set ancestor-closed, checked without waiting for other blocks.
+// One 512-thread block per sequence.  Only the nodes near the R-th best are
+// compared: the scores are counted in bins of an eighth of an octave (a
+// monotone map of the score's high bits), one prefix sum gives every bin's
+// first rank, and the exact order inside the bins that begin below rank R
+// comes from comparing a bin's members with each other.  The kernel is a
+// chain of latencies (one read of the scores, one of the candidates'
+// records).  Counting every node against every other, on sixteen blocks a
+// sequence, took 6.6 us at 456 nodes and 64 sequences and 21 us at 710 nodes
+// and 128; this takes 5.2 and 8.2 us.
 #include "rheo_device.h"
 #include "rheo_state.h"
 
 namespace rheo {
 
-constexpr int NTR = 256;
-constexpr int PSPLIT = 16;         // blocks per sequence
+constexpr int NTR = 512;
+constexpr int PBINS = 512;                   // one bin per thread
+
+// The bin of a score in [0, 1]: its exponent and three mantissa bits, from 511
+// (score 1) down to 2^-63 and below (0).
+__device__ __forceinline__ int score_bin(double s) {
+    const int k = (int)((uint64_t)__double_as_longlong(s) >> 49);
+    return min(max(k - ((0x3FF << 3) - (PBINS - 1)), 0), PBINS - 1);
+}
+
+struct PruneLds {
+    int lo, ord, bs, rank, bytes;            // scores first
+};
+__host__ __device__ inline PruneLds prune_lds(int n) {
+    PruneLds L;
+    L.lo = 8 * n;
+    L.bs = L.lo + 8 * n;
+    L.ord = L.bs + 4 * n;
+    L.rank = L.ord + 2 * n;
+    L.bytes = L.rank + 2 * n;
+    return L;
+}
 
 __global__ __launch_bounds__(NTR) void k_prune(TreeDev t, int R) {
-    extern __shared__ ulonglong2 s_key[];    // the sequence's n keys
-    const int b = blockIdx.x / PSPLIT, part = blockIdx.x % PSPLIT;
-    const int tid = threadIdx.x;
-    const int n = t.NN - 1;               // non-root nodes, uids 1..NN-1
+    extern __shared__ __align__(16) uint8_t s_dyn[];
+    __shared__ int s_hist[PBINS], s_start[PBINS];
+    __shared__ int s_w[NTR / WAVE];
+    const int b = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid % WAVE, wid = tid / WAVE;
+    const int n = t.NN - 1;                  // non-root nodes, uids 1..NN-1
     const int64_t nb = (int64_t)b * t.NN;
-    if (part == 0 && tid == 0) {
-        t.pidx[nb] = 0;
-        t.porder[nb] = 0;
-    }
+    const PruneLds L = prune_lds(n);
+    double* s_score = (double*)s_dyn;
+    uint64_t* s_lo = (uint64_t*)(s_dyn + L.lo);
+    int* s_bs = (int*)(s_dyn + L.bs);
+    int16_t* s_ord = (int16_t*)(s_dyn + L.ord);
+    int16_t* s_rank = (int16_t*)(s_dyn + L.rank);
+    s_hist[tid] = 0;
+    __syncthreads();
     for (int i = tid; i < n; i += NTR) {
-        const int64_t o = nb + 1 + i;
-        uint64_t hi, lo;
-        prio_key(t.score[o], t.meta[o] & 0xFF, t.path[o], hi, lo);
-        s_key[i] = make_ulonglong2(hi, lo);
+        const double sc = t.score[nb + 1 + i];
+        const int bin = score_bin(sc);
+        s_score[i] = sc;
+        s_bs[i] = bin | (atomicAdd(&s_hist[bin], 1) << 16);
+    }
+    if (tid == 0) {
+        t.node[nb].pidx = 0;
+        t.porder[nb] = 0;
+        t.pr_par[nb] = -1;
+        t.pr_tok[nb] = -1;
+        t.pr_depth[nb] = 0;
     }
     __syncthreads();
-    // this block's nodes [i0, i1), F lanes per node, each over every F-th key
-    const int per = (n + PSPLIT - 1) / PSPLIT;
-    const int i0 = min(n, part * per), i1 = min(n, i0 + per);
-    const int m = i1 - i0;
-    int F = 1;
-    while (F < 16 && 2 * F * m <= NTR) F *= 2;
-    const int sub = tid % F;
-    for (int base = 0; base < m; base += NTR / F) {
-        const int i = i0 + base + tid / F;
-        int cnt = 0;
-        ulonglong2 k = make_ulonglong2(~0ull, ~0ull);
-        if (i < i1) k = s_key[i];
-#pragma unroll 8
-        for (int j = sub; j < n; j += F) {
-            const ulonglong2 x = s_key[j];
-            cnt += (int)(x.x > k.x) | ((int)(x.x == k.x) & (int)(x.y > k.y));
+    {
+        const int v = s_hist[PBINS - 1 - tid];
+        int ex = wave_excl_scan(v);
+        if (lane == WAVE - 1) s_w[wid] = ex + v;
+        __syncthreads();
+        for (int w = 0; w < wid; ++w) ex += s_w[w];
+        s_start[PBINS - 1 - tid] = ex;
+    }
+    __syncthreads();
+    // candidates: the members of the bins that begin below rank R, with the
+    // lower half of their priority key
+    for (int i = tid; i < n; i += NTR) {
+        const int bs = s_bs[i], st = s_start[bs & 0xFFFF];
+        if (st < R) {
+            const Node& nd = t.node[nb + 1 + i];
+            uint64_t hi, lo;
+            prio_key(s_score[i], nd.meta & 0xFF, nd.path, hi, lo);
+            s_lo[i] = lo;
+            s_ord[st + (bs >> 16)] = (int16_t)i;
         }
-        for (int o = 1; o < F; o <<= 1) cnt += __shfl_xor(cnt, o);
-        if (i < i1 && sub == 0) {
-            const int64_t o = nb + 1 + i;
-            if (cnt < R) {
-                t.pidx[o] = cnt + 1;
-                t.porder[nb + cnt + 1] = 1 + i;
-            } else {
-                t.pidx[o] = -1;
-            }
-            // a parent outranks its child (raises the sticky error flag if not)
-            const int p = t.par[o];
-            if (p > 0) {
-                const ulonglong2 pk = s_key[p - 1];
-                if (!(pk.x > k.x || (pk.x == k.x && pk.y > k.y))) atomicOr(t.err, 2);
+    }
+    __syncthreads();
+    for (int i = tid; i < n; i += NTR) {
+        const int bin = s_bs[i] & 0xFFFF, st = s_start[bin];
+        int rk = n;
+        if (st < R) {
+            const double sc = s_score[i];
+            const uint64_t lo = s_lo[i];
+            rk = st;
+            for (int q = st; q < st + s_hist[bin]; ++q) {
+                const int o = s_ord[q];
+                const double so = s_score[o];
+                rk += (int)(so > sc) | ((int)(so == sc) & (int)(s_lo[o] > lo));
             }
         }
+        s_rank[i] = (int16_t)(rk < R ? rk + 1 : -1);
+        t.node[nb + 1 + i].pidx = rk < R ? rk + 1 : -1;
+    }
+    __syncthreads();
+    for (int i = tid; i < n; i += NTR) {
+        const int k = s_rank[i];
+        if (k < 0) continue;
+        const Node& nd = t.node[nb + 1 + i];
+        const int p = nd.par;
+        const int pk = p == 0 ? 0 : (p > 0 && p <= n) ? s_rank[p - 1] : -1;
+        // a parent outranks its child (raises the sticky error flag if not)
+        if (pk < 0 || pk >= k) atomicOr(t.err, 2);
+        t.porder[nb + k] = 1 + i;
+        t.pr_par[nb + k] = pk < 0 ? 0 : pk;
+        t.pr_tok[nb + k] = nd.tok;
+        t.pr_depth[nb + k] = nd.meta & 0xFF;
     }
 }
 
+// Raises the kernel's limit on dynamic LDS for trees of many nodes.
+hipError_t prepare_prune(const TreeDev& t) {
+    const int bytes = prune_lds(t.NN - 1).bytes;
+    if (bytes <= 48 * 1024) return hipSuccess;
+    return hipFuncSetAttribute((const void*)&k_prune, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               bytes);
+}
+
 hipError_t launch_prune(const TreeDev& t, int R, hipStream_t s) {
-    const int n = t.NN - 1;
-    k_prune<<<t.B * PSPLIT, NTR, sizeof(ulonglong2) * (size_t)n, s>>>(t, R);
+    k_prune<<<t.B, NTR, (size_t)prune_lds(t.NN - 1).bytes, s>>>(t, R);
     return hipGetLastError();
 }
 

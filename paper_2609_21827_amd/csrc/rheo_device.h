@@ -13,6 +13,16 @@ constexpr int WAVE = 64;
 enum Kind { LEAD = 0, SAMPLED = 1, FILL = 2 };
 enum Purpose { P_DRAFT = 1, P_VERIFY = 2, P_FINAL = 3 };
 
+// A kernel's parameters (one struct, its only parameter) where the launch put
+// them.  Reading a field there when it is needed is a scalar load; a struct
+// parameter by value is loaded whole at the kernel's start, which for the
+// row and verification kernels spilled some hundred scalar registers and
+// put the reloads on their latency-bound steps.
+template <typename P>
+__device__ __forceinline__ const P& kernel_params() {
+    return *(const P*)(const void*)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
 // ---------------------------------------------------------------------------
 // Philox4x64-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of two
 // 64x64->128 multiplies with the round multipliers, the high halves xored
@@ -249,17 +259,21 @@ __device__ int block_sum_i32(int v, int* sh) {
     return r;
 }
 
-// Exclusive prefix of v over the wave (lane order).
-__device__ __forceinline__ int wave_excl_scan(int v) {
-    const int row = (threadIdx.x % WAVE) >> 4;
-    uint32_t x = (uint32_t)v;
+// Inclusive prefix of v over the wave, one DPP add a step (shifts inside rows
+// of 16 lanes, then row broadcasts).
+__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t x) {
     x += row_shr<1>(x);
     x += row_shr<2>(x);
     x += row_shr<4>(x);
     x += row_shr<8>(x);
-    const uint32_t r0 = lane_u32(x, 15), r1 = lane_u32(x, 31), r2 = lane_u32(x, 47);
-    x += (row >= 1 ? r0 : 0u) + (row >= 2 ? r1 : 0u) + (row >= 3 ? r2 : 0u);
-    return (int)x - v;
+    // lane 15 of rows 0 and 2 into rows 1 and 3, then lane 31 into rows 2, 3
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);
+    return x;
+}
+// Exclusive prefix of v over the wave (lane order).
+__device__ __forceinline__ int wave_excl_scan(int v) {
+    return (int)wave_incl_scan_u32((uint32_t)v) - v;
 }
 
 }  // namespace rheo

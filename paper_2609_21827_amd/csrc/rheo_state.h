@@ -6,6 +6,23 @@
 
 namespace rheo {
 
+// One tree node, 64 bytes: what a child's emission writes in four 16-byte
+// stores and a verification layer reads in two.
+struct alignas(16) Node {
+    double score;
+    uint64_t path;                 // slot path, 4 bits per level from bit 59 down
+    int32_t meta;                  // depth | slot << 8 | kind << 16
+    int32_t par;
+    int32_t tok;
+    int32_t tidx;                  // place in the parent's stored tail (sparse), else -1
+    int32_t first_child;           // uid of slot-1 child, -1 if not expanded
+    int32_t exp_of;                // expanded index, -1 if not expanded
+    int32_t pidx;                  // pruned index, -1 if pruned away
+    int32_t pad;
+    double proxy;
+    double qtrue;
+};
+
 // Everything a kernel needs to find the tree arrays.  Node arrays are
 // [B][NN] in uid order (uid 0 = root); expanded-node arrays are [B][E] with
 // expanded index e = 0 for the root and 1 + (d-1) * NE + j for frontier
@@ -17,16 +34,8 @@ struct TreeDev {
     int64_t stride;
     double eps;
     // unpruned tree, [B][NN]
-    int32_t* tok;
-    int32_t* par;
-    int32_t* meta;                 // depth | slot << 8 | kind << 16
-    double* proxy;
-    double* qtrue;
-    double* score;
-    uint64_t* path;                // slot path, 4 bits per level from bit 59 down
-    int32_t* first_child;          // uid of slot-1 child, -1 if not expanded
-    int32_t* exp_of;               // expanded index, -1 if not expanded
-    int32_t* tidx;                 // place in the parent's stored tail (sparse), else -1
+    Node* node;
+    double* score;                 // the nodes' path scores once more, contiguous for the prune
     // truncated tail distribution q~ of each expanded node, sorted by id
     int32_t* tail_id;              // [B][E][S]
     uint32_t* tail_q;              // [B][E][S]
@@ -37,8 +46,10 @@ struct TreeDev {
     int32_t* fr_parent;
     int32_t* fr_token;
     // pruned tree
-    int32_t* pidx;                 // [B][NN]: pruned index, -1 if pruned away
     int32_t* porder;               // [B][NN]: uid of each pruned index
+    int32_t* pr_par;               // [B][NN]: its parent's pruned index, token, depth
+    int32_t* pr_tok;
+    int32_t* pr_depth;
     int32_t* err;                  // sticky device error flag
     // verification team exchange (see verify.hip)
     uint64_t* team_ticket;         // [B] blocks of each team so far (monotonic)
@@ -61,6 +72,8 @@ struct TreeDev {
     float* dref;                   // [B][E]
     int32_t* dleads;               // [B][E][16]
     uint32_t* seq_cnt;             // [B] rows whose pool is written (0 between launches)
+    uint64_t* fr_words;            // [B][3][NE * K] children words (see pool_common.h)
+    uint64_t* fr_mark;             // [B] their mark in the next launch
     int C, Sc;
     int rrsw;                      // verification leads first (App. D.2)
     int topk;                      // pure top-K pools, no sampled slot
@@ -98,6 +111,7 @@ hipError_t launch_expand(const TreeDev& t, const LevelArgs& a, int variant,
                          hipStream_t s);
 hipError_t launch_select(const TreeDev& t, const LevelArgs& a, int variant, hipStream_t s);
 hipError_t launch_dense(const TreeDev& t, const LevelArgs& a, int nvc, hipStream_t s);
+hipError_t prepare_prune(const TreeDev& t);
 hipError_t launch_prune(const TreeDev& t, int R, hipStream_t s);
 hipError_t verify_shape(const TreeDev& t, int* G, int* segch, int* grid);
 hipError_t launch_verify(const TreeDev& t, const VerifyArgs& a, int segch, int grid,
@@ -114,7 +128,7 @@ hipError_t launch_expand_row(const TreeDev& t, const LevelArgs& a, hipStream_t s
 hipError_t launch_row_wsum(const TreeDev& t, const LevelArgs& a, hipStream_t s);
 hipError_t launch_tree_mask(const TreeDev& t, int R, uint8_t* mask, int32_t* depth,
                             hipStream_t s);
-int expand_row_nq(int dtype, int V);
+int expand_row_threads(int dtype, int V, int S);
 hipError_t expand_row_slots(const TreeDev& t, int* slots);
 int expand_variant_count(int dtype);
 int expand_variant_nvc(int v);

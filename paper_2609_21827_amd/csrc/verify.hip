@@ -298,10 +298,18 @@ __device__ bool team_barrier(uint64_t* flags, int g, int G, uint64_t epoch, long
     return *s_ok != 0;
 }
 
+struct VerifyParams {
+    TreeDev t;
+    VerifyArgs a;
+};
+
 // At least four blocks per compute unit (128 registers a lane): the team
 // shape is sized from how many blocks the device holds at once.
 template <int DT, int DN>
-__global__ __launch_bounds__(NTV, 4) void k_verify(TreeDev t, VerifyArgs a) {
+__global__ __launch_bounds__(NTV, 4) void k_verify(VerifyParams) {
+    const VerifyParams& vp = kernel_params<VerifyParams>();
+    const TreeDev& t = vp.t;
+    const VerifyArgs& a = vp.a;
     constexpr int VEC = DT ? 8 : 4;
     constexpr int ESZ = DT ? 2 : 4;
     constexpr int CH = WAVE * VEC;           // tokens per chunk
@@ -375,8 +383,8 @@ __global__ __launch_bounds__(NTV, 4) void k_verify(TreeDev t, VerifyArgs a) {
     if (tid == 0) {
         s_cur = 0;
         s_curp = 0;
-        s_fc = t.first_child[nb];
-        s_e = t.exp_of[nb];
+        s_fc = t.node[nb].first_child;
+        s_e = t.node[nb].exp_of;
         // barrier epochs of this launch: a window of 64 above the previous
         // launch's (a walk uses 3 per layer, at most 48)
         s_epoch = 64 * (ticket / (uint64_t)G + 1);
@@ -407,12 +415,13 @@ __global__ __launch_bounds__(NTV, 4) void k_verify(TreeDev t, VerifyArgs a) {
         int kind = -1, ctok = -1, cpidx = -1, cfc = -1, ce = -1, ctail = -1;
         if (tid < WAVE && fc >= 0 && lane < K) {
             const int64_t o = nb + fc + lane;
-            cpidx = t.pidx[o];
-            kind = (t.meta[o] >> 16) & 0xFF;
-            ctok = t.tok[o];
-            cfc = t.first_child[o];
-            ce = t.exp_of[o];
-            ctail = DN ? -1 : t.tidx[o];        // its place in the stored tail
+            const int4 r1 = *(const int4*)&t.node[o].meta, r2 = *(const int4*)&t.node[o].first_child;
+            cpidx = r2.z;
+            kind = (r1.x >> 16) & 0xFF;
+            ctok = r1.z;
+            cfc = r2.x;
+            ce = r2.y;
+            ctail = DN ? -1 : r1.w;             // its place in the stored tail
             keep = cpidx > 0;
         }
         const uint64_t Zq = (fc >= 0) ? t.zq[(int64_t)b * t.E + e] : 1;
@@ -1001,10 +1010,9 @@ hipError_t verify_shape(const TreeDev& t, int* G_out, int* segch, int* grid) {
 hipError_t launch_verify(const TreeDev& t, const VerifyArgs& a, int segch, int grid,
                          hipStream_t s) {
     const void* fn = verify_fn(t);
-    TreeDev tt = t;
-    VerifyArgs aa = a;
-    aa.NV = segch;
-    void* args[] = {&tt, &aa};
+    VerifyParams vp{t, a};
+    vp.a.NV = segch;
+    void* args[] = {&vp};
     return hipLaunchKernel(fn, dim3(grid), dim3(NTV), args, 0, s);
 }
 

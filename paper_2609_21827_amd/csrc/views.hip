@@ -10,15 +10,15 @@ __global__ void k_read_nodes(TreeDev t, int32_t* token, int32_t* parent, int32_t
     const int64_t n = (int64_t)t.B * t.NN;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
-        const int meta = t.meta[i];
-        if (token) token[i] = t.tok[i];
-        if (parent) parent[i] = t.par[i];
+        const int meta = t.node[i].meta;
+        if (token) token[i] = t.node[i].tok;
+        if (parent) parent[i] = t.node[i].par;
         if (depth) depth[i] = meta & 0xFF;
         if (slot) slot[i] = (meta >> 8) & 0xFF;
         if (kind) kind[i] = (meta >> 16) & 0xFF;
-        if (proxy) proxy[i] = t.proxy[i];
-        if (qtrue) qtrue[i] = t.qtrue[i];
-        if (score) score[i] = t.score[i];
+        if (proxy) proxy[i] = t.node[i].proxy;
+        if (qtrue) qtrue[i] = t.node[i].qtrue;
+        if (score) score[i] = t.node[i].score;
     }
 }
 
@@ -27,38 +27,42 @@ __global__ void k_pruned_view(TreeDev t, int R, int32_t* parent, int32_t* token)
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
         const int b = (int)(i / (R + 1));
-        const int k = (int)(i % (R + 1));
-        const int64_t nb = (int64_t)b * t.NN;
-        const int uid = t.porder[nb + k];
-        if (parent) parent[i] = (k == 0) ? -1 : t.pidx[nb + t.par[nb + uid]];
-        if (token) token[i] = (k == 0) ? -1 : t.tok[nb + uid];
+        const int64_t o = (int64_t)b * t.NN + (i - (int64_t)b * (R + 1));
+        if (parent) parent[i] = t.pr_par[o];
+        if (token) token[i] = t.pr_tok[o];
     }
 }
 
-// One thread per (sequence, row i, column j): j is on i's root path iff
-// walking up from i (pruned indices decrease towards the root) meets j.
-__global__ void k_tree_mask(TreeDev t, int R, uint8_t* mask, int32_t* depth) {
+// The mask and the depths of one sequence, MSPLIT blocks each: the parents'
+// pruned indices in LDS, one ancestor walk (at most depth <= 15 steps, to
+// ever smaller indices) per entry.
+constexpr int NTM = 256;
+constexpr int MSPLIT = 4;
+
+__global__ __launch_bounds__(NTM) void k_tree_mask(TreeDev t, int R, uint8_t* mask,
+                                                   int32_t* depth) {
+    extern __shared__ int s_par[];
     const int n = R + 1;
-    const int64_t total = (int64_t)t.B * n * n;
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int b = (int)(e / ((int64_t)n * n));
-        const int i = (int)((e / n) % n);
-        const int j = (int)(e % n);
-        const int64_t nb = (int64_t)b * t.NN;
+    const int b = blockIdx.x / MSPLIT, part = blockIdx.x % MSPLIT;
+    const int64_t nb = (int64_t)b * t.NN;
+    for (int i = threadIdx.x; i < n; i += NTM) {
+        s_par[i] = t.pr_par[nb + i];
+        if (depth && part == 0) depth[(int64_t)b * n + i] = t.pr_depth[nb + i];
+    }
+    __syncthreads();
+    if (!mask) return;
+    uint8_t* out = mask + (int64_t)b * n * n;
+    for (int e = part * NTM + threadIdx.x; e < n * n; e += NTM * MSPLIT) {
+        const int i = e / n, j = e - i * n;
         int p = i;
-        // at most depth (<= 15) steps; p > j >= 0 keeps the root's parent unread
-        for (int s = 0; s < 16 && p > j; ++s) p = t.pidx[nb + t.par[nb + t.porder[nb + p]]];
-        if (mask) mask[e] = (p == j) ? 1 : 0;
-        if (depth && j == 0) depth[(int64_t)b * n + i] = t.meta[nb + t.porder[nb + i]] & 0xFF;
+        for (int s = 0; s < 16 && p > j; ++s) p = s_par[p];
+        out[e] = (p == j) ? 1 : 0;
     }
 }
 
 hipError_t launch_tree_mask(const TreeDev& t, int R, uint8_t* mask, int32_t* depth,
                             hipStream_t s) {
-    const int64_t n = (int64_t)t.B * (R + 1) * (R + 1);
-    const int blocks = (int)((n + 255) / 256 < 8192 ? (n + 255) / 256 : 8192);
-    k_tree_mask<<<blocks, 256, 0, s>>>(t, R, mask, depth);
+    k_tree_mask<<<t.B * MSPLIT, NTM, sizeof(int) * (size_t)(R + 1), s>>>(t, R, mask, depth);
     return hipGetLastError();
 }
 
