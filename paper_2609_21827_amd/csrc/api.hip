@@ -180,7 +180,7 @@ int configure(const rheo_config* cfg_in, rheo_tree* t) {
     // sparse levels run one block per row (the row streamed once, no chunk
     // lists) when the row fits it and the level has at least row_min rows;
     // RHEO_EXPAND_ROW=0 or 1 forces the chunked or the per-row kernel
-    t->row_mode = (!dense && expand_row_threads(c.dtype, c.vocab, S) > 0) ? -1 : 0;
+    t->row_mode = (!dense && expand_row_threads(c.dtype, c.vocab, S, d.cfull != 0) > 0) ? -1 : 0;
     if (const char* er = getenv("RHEO_EXPAND_ROW")) {
         if (er[0] == '0') t->row_mode = 0;
         else if (er[0] == '1' && t->row_mode != 0) t->row_mode = 1;
@@ -436,11 +436,6 @@ int rheo_expand_level(rheo_tree* t, const void* logits, float T, uint64_t key, v
     a.rng_key = key;
     a.fr_key = key;                       // the key of the call that chose the parents
     hipError_t e = hipSuccess;
-    if (t->dev.cfull) {
-        // the construction totals over the whole rows, read by the pools
-        e = launch_row_wsum(t->dev, a, (hipStream_t)stream);
-        if (e != hipSuccess) return hip_fail(e, "row total launch");
-    }
     if (t->dev.dense) {
         e = launch_select(t->dev, a, t->variant, (hipStream_t)stream);
         if (e == hipSuccess)
@@ -448,7 +443,9 @@ int rheo_expand_level(rheo_tree* t, const void* logits, float T, uint64_t key, v
     } else if (t->row_mode == 1 || (t->row_mode < 0 && t->dev.B * a.P >= t->row_min)) {
         e = launch_expand_row(t->dev, a, (hipStream_t)stream);
     } else {
-        e = launch_expand(t->dev, a, t->variant, (hipStream_t)stream);
+        // (the row kernel sums the rows' construction weights itself)
+        if (t->dev.cfull) e = launch_row_wsum(t->dev, a, (hipStream_t)stream);
+        if (e == hipSuccess) e = launch_expand(t->dev, a, t->variant, (hipStream_t)stream);
     }
     if (e != hipSuccess) return hip_fail(e, "expand launch");
     t->draft[t->level] = logits;

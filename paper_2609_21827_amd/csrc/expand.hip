@@ -30,6 +30,7 @@
 
 #include "rheo_device.h"
 #include "rheo_state.h"
+#include "code_hist.h"
 #include "pool_common.h"
 
 namespace rheo {
@@ -222,7 +223,7 @@ __device__ __forceinline__ void pool_form(const TreeDev& t, const LevelArgs& a, 
         pre += (w < wid) ? zw : 0ull;
         anyt |= ps.tie[w];
     }
-    if (t.cfull) S1 = t.s1row[row];          // construction over the whole vocabulary
+    if (t.cfull) S1 = ps.s1full;             // construction over the whole vocabulary
     const int64_t tail_base = ((int64_t)b * t.E + e_idx) * S;
     const bool ident = anyt == 0;
     if (ident) {
@@ -456,6 +457,7 @@ __global__ __launch_bounds__(NTP) void k_pool(TreeDev t, LevelArgs a) {
     __syncthreads();
 
     // the pool, formed by the whole block
+    if (t.cfull && tid == 0) ps.s1full = t.s1row[row];   // (read past pool_form's first barrier)
     if (S <= NTP) pool_form<NTP, 1>(t, a, row, s_pdyn, L, s_pu, pr, s_u, ps);
     else pool_form<NTP, SMAX / NTP>(t, a, row, s_pdyn, L, s_pu, pr, s_u, ps);
 
@@ -1075,9 +1077,10 @@ constexpr int ROW_BATCHES = 8;  // most batches of a row: 64 vectors per thread
 struct RowLds {
     PoolLds p;                 // p.k2: also the ranked candidates, over the codes
     int codes, keys, hist, start;
+    int tab, small;            // counts of the row's values (bf16, whole-vocabulary totals)
 };
 __host__ __device__ inline int row_cap(bool ls) { return ls ? 2048 : 960; }
-__host__ __device__ inline RowLds row_lds(int S, bool ls, int nb, int ntb) {
+__host__ __device__ inline RowLds row_lds(int S, bool ls, int nb, int ntb, bool count) {
     RowLds L;
     const int cap = row_cap(ls), nbins = ls ? 2 * NBINS : NBINS;
     const int S2 = S > 256 ? S : 256;
@@ -1103,6 +1106,10 @@ __host__ __device__ inline RowLds row_lds(int S, bool ls, int nb, int ntb) {
     o += pad16(2 * S);
     L.p.xs = o;
     o += pad16(2 * S);
+    L.tab = o;
+    if (count) o += pad16(2 * HIST_BYTES);
+    L.small = o;
+    if (count) o += 4 * HIST_SMALL;
     L.p.bytes = o;
     return L;
 }
@@ -1150,8 +1157,14 @@ struct RowArgs {
     LevelArgs a;
 };
 
-// LS: supports above kLargeSupport (four offers per lane, larger lists).
-template <int DT, bool LS, int NTB>
+// LS: supports above kLargeSupport (four offers per lane, larger lists).  CF:
+// the construction weights are summed over the whole vocabulary (relative to
+// the row maximum): for bf16 from counts of the row's values, taken as it
+// streams (V = 128256, 256 rows: 32 us a level where a pass of its own for the
+// totals took 91 us before the 23 us of the row kernel); for fp32, whose
+// values hardly repeat, and for rows the counts do not cover, in a second
+// pass over the row.
+template <int DT, bool LS, int NTB, bool CF>
 __global__ __launch_bounds__(NTB, 4) void k_expand_row(RowArgs) {
     const RowArgs& args = kernel_params<RowArgs>();
     const TreeDev& t = args.t;
@@ -1167,6 +1180,8 @@ __global__ __launch_bounds__(NTB, 4) void k_expand_row(RowArgs) {
     __shared__ int s_thr[2 * NW * 16];
     __shared__ int s_wcode[NW];
     __shared__ int s_cnt;
+    __shared__ int s_nsmall;
+    __shared__ uint64_t s_wsum[NW], s_wcount[NW];
     __shared__ PoolShared<NTB> ps;
     __shared__ int s_redi[NW];
     __shared__ int s_pu;
@@ -1182,13 +1197,16 @@ __global__ __launch_bounds__(NTB, 4) void k_expand_row(RowArgs) {
     const int NVR = (V + VEC - 1) / VEC;          // vectors of the row, <= 64 * NTB
     const int NVF = V / VEC;                       // whole vectors
     const int NB = (NVR + NTB * EBATCH - 1) / (NTB * EBATCH);
-    const RowLds L = row_lds(S, LS, NB, NTB);
+    constexpr bool COUNT = CF && DT == 1;
+    const RowLds L = row_lds(S, LS, NB, NTB, COUNT);
     uint4* s_code = (uint4*)(s_pdyn + L.codes);
     uint64_t* s_keys = (uint64_t*)(s_pdyn + L.keys);
     uint64_t* s_ord = (uint64_t*)(s_pdyn + L.p.k2);
     uint64_t* s_top = (uint64_t*)(s_pdyn + L.p.top);
     int* s_hist = (int*)(s_pdyn + L.hist);
     int* s_start = (int*)(s_pdyn + L.start);
+    uint8_t* s_tab = s_pdyn + L.tab;
+    uint32_t* s_small = (uint32_t*)(s_pdyn + L.small);
     const char* base = (const char*)a.logits + (int64_t)row * t.stride * (DT ? 2 : 4);
 
     // the parent's frontier entry is loaded while the row streams (after its
@@ -1200,6 +1218,10 @@ __global__ __launch_bounds__(NTB, 4) void k_expand_row(RowArgs) {
     if (tid == 0) s_cnt = 0;
     for (int i = tid; i < S; i += NTB) s_top[i] = 0ull;   // id -1 until ranked
     for (int i = tid; i < NBIN; i += NTB) s_hist[i] = 0;
+    if (COUNT) {
+        for (int i = tid; i < 2 * HIST_WORDS; i += NTB) ((uint32_t*)s_tab)[i] = 0;
+        if (tid == 0) s_nsmall = 0;
+    }
 
     // ---- the row, streamed ---------------------------------------------------
     // Vector q of this thread: lane `lane` of the 64-vector slot (wid + q) mod
@@ -1235,10 +1257,14 @@ __global__ __launch_bounds__(NTB, 4) void k_expand_row(RowArgs) {
             if (LS) p2 = __builtin_elementwise_max(p2, __builtin_elementwise_min(p1, cq));
             p1 = __builtin_elementwise_max(p1, cq);
         }
+        // two tables, by the lane's parity: fewer lanes meet on one word
+        if (COUNT)
+            hist_add(s_tab, (uint32_t)(lane & 1) * HIST_BYTES, r, &s_nsmall, s_small, 0u);
         s_code[bt * NTB + tid] = make_uint4(cw[0], cw[1], cw[2], cw[3]);
     };
     static_assert(EBATCH == 8, "one 16-byte store of codes per batch");
     if (NB <= 2 && tid == 0) rp = row_parent_load(t, a, b, j);
+    if (COUNT) __syncthreads();                  // (the tables are clear)
     {
         uint4 ra[EBATCH], rb[EBATCH];
         load_batch(ra, 0);
@@ -1275,6 +1301,38 @@ __global__ __launch_bounds__(NTB, 4) void k_expand_row(RowArgs) {
     }
     // the parent record, for the children written at the end
     const ParentRec pr = parent_rec(t, a, b, tid < K, s_pu);
+
+    // the row maximum (fp32: truncated); its code holds the high 16 bits alone
+    const float vmax = __uint_as_float(__float_as_uint(unord32(cmax << 16)) & 0xFFFF0000u);
+    if (COUNT) {
+        // the row's total construction weight from the counts of its values;
+        // s_wcount checks them: every element of every batch in the tables (no
+        // overflow), no value of 2^9 or more, and none at or below -2^9 unless
+        // its weight is 0
+        uint64_t w = 0, n = 0;
+        const uint32_t* tab = (const uint32_t*)s_tab;
+        for (int i = tid; i < HIST_WORDS; i += NTB) {
+            const uint32_t c0 = tab[i], c1v = tab[HIST_WORDS + i];
+            const uint32_t pos = (c0 & 0xFFFFu) + (c1v & 0xFFFFu), neg = (c0 >> 16) + (c1v >> 16);
+            n += pos + neg;
+            if (i >= 1 && i < HIST_OUT) {
+                const float l = hist_value(i);
+                w += (uint64_t)pos * cweight(l, vmax, a.k1) + (uint64_t)neg * cweight(-l, vmax, a.k1);
+            } else if (i >= HIST_OUT) {
+                if (pos != 0 || (neg != 0 && cweight(-512.0f, vmax, a.k1) != 0u)) n += 1ull << 40;
+            }
+        }
+        const int ns = s_nsmall;
+        if (ns > HIST_SMALL) n += 1ull << 40;
+        for (int i = tid; i < min(ns, HIST_SMALL); i += NTB)
+            w += cweight(__uint_as_float(s_small[i] << 16), vmax, a.k1);
+        w = wave_sum_u64(w);
+        n = wave_sum_u64(n);
+        if (lane == 0) {
+            s_wsum[wid] = w;
+            s_wcount[wid] = n;
+        }
+    }
 
     // ---- candidates: elements at or above the threshold --------------------
     float tau;
@@ -1384,7 +1442,6 @@ __global__ __launch_bounds__(NTB, 4) void k_expand_row(RowArgs) {
     // Bins linear in the value over [tau, the row maximum] (a monotone map:
     // one rounded subtraction, one rounded product), by the high bits of the
     // order code when tau is -inf or the maximum +inf.
-    const float vmax = unord32(cmax << 16);
     const bool lin = tau > -INFINITY && vmax < INFINITY;
     const float scale = (float)NBIN / (vmax - tau);
     uint64_t key[KPT];
@@ -1453,6 +1510,41 @@ __global__ __launch_bounds__(NTB, 4) void k_expand_row(RowArgs) {
     }
     __syncthreads();
 
+    if (CF) {
+        // (the barriers since the counts were summed order s_wsum)
+        uint64_t n = 0, w = 0;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) {
+            n += COUNT ? s_wcount[q] : 0ull;
+            w += COUNT ? s_wsum[q] : 0ull;
+        }
+        if (!COUNT || n != (uint64_t)(NB * NTB) * (EBATCH * VEC)) {
+            const float M = key_value(s_top[0]);
+            w = 0;
+            for (int bt = 0; bt < NB; ++bt) {
+                uint4 r[EBATCH];
+                load_batch(r, bt);
+#pragma unroll
+                for (int e = 0; e < EBATCH; ++e) {
+                    // (padding reads as -inf or a NaN word: no weight)
+                    const int e0 = vidx(bt * EBATCH + e) * VEC;
+#pragma unroll
+                    for (int k = 0; k < VEC; ++k) {
+                        const uint32_t x = cweight_below(elem<DT>(r[e], k), M, a.k1);
+                        w += (e0 + k < V) ? x : 0u;
+                    }
+                }
+            }
+            w = wave_sum_u64(w);
+            __syncthreads();                     // (s_wsum is read)
+            if (lane == 0) s_wsum[wid] = w;
+            __syncthreads();
+            w = 0;
+#pragma unroll
+            for (int q = 0; q < NW; ++q) w += s_wsum[q];
+        }
+        if (tid == 0) ps.s1full = w;             // (read past pool_form's first barrier)
+    }
     constexpr int SC = LS ? SMAX : kLargeSupport;    // the largest support of the class
     pool_form<NTB, (SC + NTB - 1) / NTB>(t, a, row, s_pdyn, L.p, s_pu, pr, s_u, ps);
     select_frontier(t, a, b, j, pr, s_top, s_ord, ps);
@@ -1559,34 +1651,39 @@ hipError_t launch_row_wsum(const TreeDev& t, const LevelArgs& a, hipStream_t s) 
 
 constexpr size_t kRowLdsMax = 156 * 1024;   // dynamic LDS of a block (160 KB less the static)
 
-static size_t row_shm(int dtype, int V, int S, int ntb) {
+static size_t row_shm(int dtype, int V, int S, int ntb, bool cfull) {
     const int nvr = (V + (dtype ? 8 : 4) - 1) / (dtype ? 8 : 4);
     const int nb = (nvr + ntb * EBATCH - 1) / (ntb * EBATCH);
-    return (size_t)row_lds(S, S > kLargeSupport, nb, ntb).p.bytes;
+    return (size_t)row_lds(S, S > kLargeSupport, nb, ntb, cfull && dtype == 1).p.bytes;
 }
 
 // Threads of a k_expand_row block for a row of V elements: 512 (64 vectors
 // each: 262,144 bf16 or 131,072 fp32 elements), or 1024 for the fp32 rows
 // beyond; 0 if the row is too long for either or its LDS does not fit.
-int expand_row_threads(int dtype, int V, int S) {
+int expand_row_threads(int dtype, int V, int S, bool cfull) {
     const int nvr = (V + (dtype ? 8 : 4) - 1) / (dtype ? 8 : 4);
     for (int ntb : {NTE, 2 * NTE})
         if (nvr <= ntb * EBATCH * ROW_BATCHES)
-            return row_shm(dtype, V, S, ntb) <= kRowLdsMax ? ntb : 0;
+            return row_shm(dtype, V, S, ntb, cfull) <= kRowLdsMax ? ntb : 0;
     return 0;
 }
 
-template <int DT>
+template <int DT, bool CF>
 static const void* row_fn(int S, int ntb) {
-    if (S > kLargeSupport)
-        return ntb == NTE ? (const void*)&k_expand_row<DT, true, NTE>
-                          : (const void*)&k_expand_row<DT, true, 2 * NTE>;
-    if (ntb == NTE / 2) return (const void*)&k_expand_row<DT, false, NTE / 2>;
-    return ntb == NTE ? (const void*)&k_expand_row<DT, false, NTE>
-                      : (const void*)&k_expand_row<DT, false, 2 * NTE>;
+    // (no bf16 row needs 1024 threads)
+    if (ntb == 2 * NTE) {
+        if constexpr (DT == 0)
+            return S > kLargeSupport ? (const void*)&k_expand_row<DT, true, 2 * NTE, CF>
+                                     : (const void*)&k_expand_row<DT, false, 2 * NTE, CF>;
+        return nullptr;
+    }
+    if (S > kLargeSupport) return (const void*)&k_expand_row<DT, true, NTE, CF>;
+    return ntb == NTE ? (const void*)&k_expand_row<DT, false, NTE, CF>
+                      : (const void*)&k_expand_row<DT, false, NTE / 2, CF>;
 }
 static const void* row_fn(const TreeDev& t, int ntb) {
-    return t.dtype ? row_fn<1>(t.S, ntb) : row_fn<0>(t.S, ntb);
+    if (t.cfull) return t.dtype ? row_fn<1, true>(t.S, ntb) : row_fn<0, true>(t.S, ntb);
+    return t.dtype ? row_fn<1, false>(t.S, ntb) : row_fn<0, false>(t.S, ntb);
 }
 
 // A level of more rows than the device holds 512-thread blocks at once
@@ -1608,7 +1705,7 @@ hipError_t expand_row_slots(const TreeDev& t, int* slots) {
     int dev = 0, cus = 0, per = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    const int wide = t.dense ? 0 : expand_row_threads(t.dtype, t.V, t.S);
+    const int wide = t.dense ? 0 : expand_row_threads(t.dtype, t.V, t.S, t.cfull != 0);
     for (int ntb : {NTE / 2, wide}) {
         if (e != hipSuccess || wide == 0) break;
         if (ntb == NTE / 2 && (t.S > kLargeSupport || wide != NTE)) continue;
@@ -1616,7 +1713,7 @@ hipError_t expand_row_slots(const TreeDev& t, int* slots) {
                                 (int)kRowLdsMax);
         if (e == hipSuccess && ntb == NTE) {
             e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, row_fn(t, ntb), ntb,
-                                                             row_shm(t.dtype, t.V, t.S, ntb));
+                                                             row_shm(t.dtype, t.V, t.S, ntb, t.cfull != 0));
             if (e == hipSuccess) *slots = per * cus;
         }
     }
@@ -1625,11 +1722,11 @@ hipError_t expand_row_slots(const TreeDev& t, int* slots) {
 
 hipError_t launch_expand_row(const TreeDev& t, const LevelArgs& a, hipStream_t s) {
     const int rows = t.B * a.P;
-    const int ntb = row_narrow(t, rows) ? NTE / 2 : expand_row_threads(t.dtype, t.V, t.S);
+    const int ntb = row_narrow(t, rows) ? NTE / 2 : expand_row_threads(t.dtype, t.V, t.S, t.cfull != 0);
     if (ntb == 0) return hipErrorInvalidValue;
     RowArgs ra{t, a};
     void* args[] = {&ra};
-    return hipLaunchKernel(row_fn(t, ntb), dim3(rows), dim3(ntb), args, row_shm(t.dtype, t.V, t.S, ntb), s);
+    return hipLaunchKernel(row_fn(t, ntb), dim3(rows), dim3(ntb), args, row_shm(t.dtype, t.V, t.S, ntb, t.cfull != 0), s);
 }
 
 }  // namespace rheo

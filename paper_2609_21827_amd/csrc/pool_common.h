@@ -78,6 +78,7 @@ template <int NT>
 struct PoolShared {
     uint64_t w1[NT / WAVE], q[NT / WAVE];   // the waves' weight totals
     int tie[NT / WAVE];
+    uint64_t s1full;                         // the row's total construction weight
     int yi;                                  // Y's place in the support
     int last;                                // the sequence's last row
     uint64_t own_score[16], own_path[16];    // the row's own children

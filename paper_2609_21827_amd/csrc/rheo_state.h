@@ -128,7 +128,7 @@ hipError_t launch_expand_row(const TreeDev& t, const LevelArgs& a, hipStream_t s
 hipError_t launch_row_wsum(const TreeDev& t, const LevelArgs& a, hipStream_t s);
 hipError_t launch_tree_mask(const TreeDev& t, int R, uint8_t* mask, int32_t* depth,
                             hipStream_t s);
-int expand_row_threads(int dtype, int V, int S);
+int expand_row_threads(int dtype, int V, int S, bool cfull);
 hipError_t expand_row_slots(const TreeDev& t, int* slots);
 int expand_variant_count(int dtype);
 int expand_variant_nvc(int v);
