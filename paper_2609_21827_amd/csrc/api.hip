@@ -180,7 +180,8 @@ int configure(const rheo_config* cfg_in, rheo_tree* t) {
     // sparse levels run one block per row (the row streamed once, no chunk
     // lists) when the row fits it and the level has at least row_min rows;
     // RHEO_EXPAND_ROW=0 or 1 forces the chunked or the per-row kernel
-    t->row_mode = (!dense && expand_row_threads(c.dtype, c.vocab, S, d.cfull != 0) > 0) ? -1 : 0;
+    t->row_mode = (dense ? c.dtype == RHEO_BF16
+                         : expand_row_threads(c.dtype, c.vocab, S, d.cfull != 0) > 0) ? -1 : 0;
     if (const char* er = getenv("RHEO_EXPAND_ROW")) {
         if (er[0] == '0') t->row_mode = 0;
         else if (er[0] == '1' && t->row_mode != 0) t->row_mode = 1;
@@ -302,6 +303,7 @@ int init_state(rheo_tree* t) {
     if (e != hipSuccess) return hip_fail(e, "no co-resident verification team shape for this tree");
     e = expand_row_slots(d, &d.row_slots);
     if (e == hipSuccess) e = prepare_prune(d);
+    if (e == hipSuccess) e = prepare_dense(d);
     if (e != hipSuccess) return hip_fail(e, "kernel set-up");
     return RHEO_OK;
 }
@@ -436,7 +438,9 @@ int rheo_expand_level(rheo_tree* t, const void* logits, float T, uint64_t key, v
     a.rng_key = key;
     a.fr_key = key;                       // the key of the call that chose the parents
     hipError_t e = hipSuccess;
-    if (t->dev.dense) {
+    if (t->dev.dense && t->row_mode != 0) {
+        e = launch_dense_row(t->dev, a, (hipStream_t)stream);
+    } else if (t->dev.dense) {
         e = launch_select(t->dev, a, t->variant, (hipStream_t)stream);
         if (e == hipSuccess)
             e = launch_dense(t->dev, a, expand_variant_nvc(t->variant), (hipStream_t)stream);

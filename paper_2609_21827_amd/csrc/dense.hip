@@ -1,7 +1,9 @@
 // Level expansion over the full vocabulary (dense mode: the support is all
 // of V; Sec. 3.2 before its sparse approximation).
 //
-// Three kernels per level:
+// bf16: one kernel per level, k_dense_row (described at the kernel), which
+// reads each row once.  fp32, whose values hardly repeat, and on request
+// bf16: three kernels per level:
 //  * k_select (expand.hip) with list length kk = min(V, m + K): the exact
 //    top-kk of every chunk by (logit desc, id asc).
 //  * k_dweights, one 256-thread block per (chunk, row): merges the row's
@@ -22,6 +24,7 @@
 #include "rheo_device.h"
 #include "rheo_state.h"
 #include "pool_common.h"
+#include "row_select.h"
 
 namespace rheo {
 
@@ -198,6 +201,45 @@ __global__ __launch_bounds__(NTD) void k_dweights(TreeDev t, LevelArgs a) {
     }
 }
 
+// A token outside the top kk by logit ties the kk-th construction weight with a
+// smaller id.  The top kk by (w1, id) is then: every token with w1 above that
+// weight (all among the top kk by logit), and the lowest ids with exactly that
+// weight, found by a scan of the row in id order (each thread a contiguous
+// range).  s_tl: the top kk by logit; s_rk: their keys w1 << 32 | ~id.
+template <int DT, int NT>
+__device__ __noinline__ void ranks_by_weight(const char* base, int V, float M, float k1, int kk,
+                                             const uint64_t* s_tl, const uint64_t* s_rk,
+                                             uint64_t* s_x, uint32_t* s_xw, uint64_t* s_red) {
+    const int tid = threadIdx.x;
+    uint32_t wmin = 0xFFFFFFFFu;
+    for (int q = 0; q < kk; ++q) wmin = min(wmin, (uint32_t)(s_rk[q] >> 32));
+    int ngt = 0;
+    for (int q = 0; q < kk; ++q) ngt += (int)((uint32_t)(s_rk[q] >> 32) > wmin);
+    const int need = kk - ngt;
+    const int per = (V + NT - 1) / NT;
+    const int lo = min(V, tid * per), hi = min(V, lo + per);
+    int mine = 0;
+    for (int v = lo; v < hi; ++v) mine += (int)(cweight(dlogit<DT>(base, v), M, k1) == wmin);
+    uint64_t tot;
+    int before = (int)block_excl_scan_u64<NT>((uint64_t)mine, s_red, &tot);
+    // the tokens above wmin keep their (w1, id) order first
+    if (tid < kk && (uint32_t)(s_rk[tid] >> 32) > wmin) {
+        const uint64_t k = s_rk[tid];
+        int rk = 0;
+        for (int q = 0; q < kk; ++q) rk += (int)(s_rk[q] > k);
+        s_x[rk] = s_tl[tid];
+        s_xw[rk] = (uint32_t)(k >> 32);
+    }
+    for (int v = lo; v < hi && before < need; ++v) {
+        const float l = dlogit<DT>(base, v);
+        if (cweight(l, M, k1) == wmin) {
+            s_x[ngt + before] = logit_key(l, (uint32_t)v);
+            s_xw[ngt + before] = wmin;
+            ++before;
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // k_dpool: ranks, tail, Y, pool and frontier of one row
 // ---------------------------------------------------------------------------
@@ -215,7 +257,7 @@ __global__ __launch_bounds__(NTD) void k_dpool(TreeDev t, LevelArgs a) {
     __shared__ uint64_t s_cq[CHT];               // tail weights of one sub-chunk
     __shared__ uint64_t s_red[NTD / WAVE];
     __shared__ PoolShared<NTD> ps;
-    __shared__ int s_pu, s_cs, s_y, s_flag, s_cnt;
+    __shared__ int s_pu, s_cs, s_y, s_flag;
     __shared__ uint64_t s_u, s_t2, s_qy;
 
     const int tid = threadIdx.x, lane = tid % WAVE;
@@ -278,45 +320,12 @@ __global__ __launch_bounds__(NTD) void k_dpool(TreeDev t, LevelArgs a) {
             s_xw[rk] = (uint32_t)(k >> 32);
         }
     } else {
-        // A token outside the top-kk by logit ties the kk-th construction
-        // weight with a smaller id.  The top-kk by (w1, id) is then: every
-        // token with w1 above that weight (all among the top-kk by logit),
-        // and the lowest ids with exactly that weight, found by a scan of
-        // the row in id order (each thread a contiguous range).
         if (tid < kk) {
             const uint32_t w = cweight(key_value(s_tl[tid]), M, a.k1);
             s_rk[tid] = ((uint64_t)w << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)key_id(s_tl[tid]));
         }
         __syncthreads();
-        uint32_t wmin = 0xFFFFFFFFu;
-        for (int q = 0; q < kk; ++q) wmin = min(wmin, (uint32_t)(s_rk[q] >> 32));
-        int ngt = 0;
-        for (int q = 0; q < kk; ++q) ngt += (int)((uint32_t)(s_rk[q] >> 32) > wmin);
-        const int need = kk - ngt;
-        const int per = (V + NTD - 1) / NTD;
-        const int lo = min(V, tid * per), hi = min(V, lo + per);
-        int mine = 0;
-        for (int v = lo; v < hi; ++v) mine += (int)(cweight(dlogit<DT>(base, v), M, a.k1) == wmin);
-        uint64_t tot;
-        int before = (int)block_excl_scan_u64<NTD>((uint64_t)mine, s_red, &tot);
-        if (tid == 0) s_cnt = 0;
-        __syncthreads();
-        // the tokens above wmin keep their (w1, id) order first
-        if (tid < kk && (uint32_t)(s_rk[tid] >> 32) > wmin) {
-            const uint64_t k = s_rk[tid];
-            int rk = 0;
-            for (int q = 0; q < kk; ++q) rk += (int)(s_rk[q] > k);
-            s_x[rk] = s_tl[tid];
-            s_xw[rk] = (uint32_t)(k >> 32);
-        }
-        for (int v = lo; v < hi && before < need; ++v) {
-            const float l = dlogit<DT>(base, v);
-            if (cweight(l, M, a.k1) == wmin) {
-                s_x[ngt + before] = logit_key(l, (uint32_t)v);
-                s_xw[ngt + before] = wmin;
-                ++before;
-            }
-        }
+        ranks_by_weight<DT, NTD>(base, V, M, a.k1, kk, s_tl, s_rk, s_x, s_xw, s_red);
     }
     __syncthreads();
 
@@ -470,6 +479,383 @@ __global__ __launch_bounds__(NTD) void k_dpool(TreeDev t, LevelArgs a) {
     }
     // the next frontier: the last row of the sequence to finish selects it
     select_frontier(t, a, b, j, pr, s_sub, s_sub + 256, ps);
+}
+
+// ---------------------------------------------------------------------------
+// k_dense_row: the whole level for one bf16 row per 512-thread block, the row
+// read once.
+//
+// While the row streams its values are counted (code_hist.h), one table per
+// batch of 32768 elements, and its top m + K found (row_top).  The weights of
+// the counted values, each evaluated once, times the counts give the total
+// construction weight and every batch's tail weight; the tail weight of each
+// value then replaces the counts in the first two tables.  Y ~ q~_T lies in
+// the batch whose interval holds t = floor(U64 Zq / 2^64), which alone is read
+// again: its weights come from the tables.
+//
+// Where the counts do not cover the row (a value of 2^9 or more, a weight
+// below -2^9, an overflow, more values below 2^-11 than are listed) the sums
+// and Y's batch take every element's own weight.  Where a value outside the
+// top m + K shares the last one's construction weight, the ranks come from a
+// scan of the row in id order.
+//
+// Evaluating both weights of every element in a pass of its own bound the
+// level (30 vector instructions an element): at 512 rows of 128256, 34 us to
+// select, 60 for the weights and 15 for the pools, against 61 here.
+// ---------------------------------------------------------------------------
+constexpr int NTX = 512;
+
+__global__ __launch_bounds__(NTX, 4) void k_dense_row(RowArgs) {
+    constexpr int NW = NTX / WAVE;
+    constexpr int SEGV = NTX * EBATCH;           // vectors of a batch
+    const RowArgs& args = kernel_params<RowArgs>();
+    const TreeDev& t = args.t;
+    const LevelArgs& a = args.a;
+    extern __shared__ __align__(16) uint8_t s_pdyn[];
+    __shared__ RowShared<NTX> rs;
+    __shared__ PoolShared<NTX> ps;
+    __shared__ uint64_t s_x[KKMAX];              // x_1..x_kk (logit keys) by (w1 desc, id asc)
+    __shared__ uint32_t s_xw[KKMAX];             // their construction weights
+    __shared__ uint64_t s_rk[KKMAX];             // ranking keys (w1 << 32 | ~id)
+    __shared__ uint64_t s_seg[ROW_BATCHES];      // the batches' tail weights
+    __shared__ uint64_t s_w1, s_n, s_qy;
+    __shared__ uint64_t s_slot[WAVE];            // tail weights of the 64-vector slots of a batch
+    __shared__ uint64_t s_red[NW];
+    __shared__ int s_flag, s_y;
+
+    ieee_mode_off();                             // NaN words drop out of the maxima
+    const int tid = threadIdx.x, lane = tid % WAVE, wid = tid / WAVE;
+    const int row = blockIdx.x;
+    const int b = row / a.P, j = row % a.P;
+    const int V = t.V, K = t.K, m = t.m, kk = t.Sc, NE = t.NE;
+    const int level = a.level;
+    const int64_t nb = (int64_t)b * t.NN;
+    const int NB = row_batches<1, NTX>(V);
+    const RowLds L = row_lds(kk, false, NB, NTX, COUNT_BATCH);
+    uint64_t* s_top = (uint64_t*)(s_pdyn + L.p.top);
+    uint32_t* tab = (uint32_t*)(s_pdyn + L.tab);
+    const uint32_t* s_small = (const uint32_t*)(s_pdyn + L.small);
+    const RowReader<1, NTX> rd = row_reader<1, NTX>(t, a, row);
+    if (tid < ROW_BATCHES) s_seg[tid] = 0;
+    if (tid == 0) {
+        s_w1 = 0;
+        s_n = 0;
+        s_flag = 0;
+        s_y = -1;
+    }
+    const RowTop rt = row_top<1, false, NTX, COUNT_BATCH>(t, a, row, kk, s_pdyn, L, rd, rs);
+
+    // ---- the sums, relative to M and to the guess x_{m+1} = s_top[m] --------
+    const float M = key_value(s_top[0]);
+    const float guess = key_value(s_top[m]);
+    const uint64_t kb = s_top[kk - 1];
+    const float vb = key_value(kb);
+    const uint32_t wmin = cweight(vb, M, a.k1);  // the least weight of the top kk
+    {
+        uint64_t w1 = 0, n = 0, zq[ROW_BATCHES];
+        bool tie = false;
+#pragma unroll
+        for (int s = 0; s < ROW_BATCHES; ++s) zq[s] = 0;
+        for (int i = tid; i < HIST_WORDS; i += NTX) {
+            uint32_t c[ROW_BATCHES], any = 0;
+#pragma unroll
+            for (int s = 0; s < ROW_BATCHES; ++s) {
+                c[s] = s < NB ? tab[s * HIST_WORDS + i] : 0u;
+                any |= c[s];
+                n += (c[s] & 0xFFFFu) + (c[s] >> 16);
+            }
+            uint32_t qp = 0, qn = 0;
+            if (i >= 1 && i < HIST_OUT) {
+                if (any & 0xFFFFu) {
+                    const float l = hist_value(i);
+                    const uint32_t w = cweight(l, M, a.k1);
+                    qp = cweight(l, guess, a.kT);
+                    tie |= l < vb && w == wmin;
+#pragma unroll
+                    for (int s = 0; s < ROW_BATCHES; ++s) {
+                        w1 += (uint64_t)(c[s] & 0xFFFFu) * w;
+                        zq[s] += (uint64_t)(c[s] & 0xFFFFu) * qp;
+                    }
+                }
+                if (any >> 16) {
+                    const float l = -hist_value(i);
+                    const uint32_t w = cweight(l, M, a.k1);
+                    qn = cweight(l, guess, a.kT);
+                    tie |= l < vb && w == wmin;
+#pragma unroll
+                    for (int s = 0; s < ROW_BATCHES; ++s) {
+                        w1 += (uint64_t)(c[s] >> 16) * w;
+                        zq[s] += (uint64_t)(c[s] >> 16) * qn;
+                    }
+                }
+            } else if (i >= HIST_OUT) {
+                // -2^9 and below: only if of no weight
+                if ((any & 0xFFFFu) || ((any >> 16) && (cweight(-512.0f, M, a.k1) != 0u ||
+                                                        cweight(-512.0f, guess, a.kT) != 0u)))
+                    n += 1ull << 40;
+                tie |= any != 0 && wmin == 0u;
+            }
+            // the tail weight of each value, where its counts were
+            tab[i] = qp;
+            tab[HIST_WORDS + i] = qn;
+        }
+        const int ns = rs.nsmall;
+        if (tid == 0 && ns > HIST_SMALL) n += 1ull << 40;
+        for (int i = tid; i < min(ns, HIST_SMALL); i += NTX) {
+            const float l = __uint_as_float(s_small[i] << 16);
+            const uint32_t w = cweight(l, M, a.k1);
+            w1 += w;
+            tie |= l < vb && w == wmin;
+            atomicAdd((unsigned long long*)&s_seg[s_small[i] >> 16],
+                      (unsigned long long)cweight(l, guess, a.kT));
+        }
+        // two different logits of the list that share its last weight
+        if (tid < kk) {
+            const uint64_t k = s_top[tid];
+            tie |= (k >> 32) != (kb >> 32) && cweight(key_value(k), M, a.k1) == wmin;
+        }
+        w1 = wave_sum_u64(w1);
+        n = wave_sum_u64(n);
+        if (lane == 0) {
+            atomicAdd((unsigned long long*)&s_w1, (unsigned long long)w1);
+            atomicAdd((unsigned long long*)&s_n, (unsigned long long)n);
+        }
+#pragma unroll
+        for (int s = 0; s < ROW_BATCHES; ++s) {
+            if (s < NB) {
+                const uint64_t z = wave_sum_u64(zq[s]);
+                if (lane == 0) atomicAdd((unsigned long long*)&s_seg[s], (unsigned long long)z);
+            }
+        }
+        if (__ballot(tie) != 0ull && lane == 0) s_flag = 1;
+    }
+    // x_1..x_kk by (w1 desc, id asc): ranks among the top kk by logit
+    if (tid < kk) {
+        const uint32_t w = cweight(key_value(s_top[tid]), M, a.k1);
+        s_rk[tid] = ((uint64_t)w << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)key_id(s_top[tid]));
+    }
+    __syncthreads();
+    bool counted = s_n == (uint64_t)(NB * NTX) * (EBATCH * 8);
+    if (!s_flag && counted) {                    // (uncounted values may tie unseen)
+        if (tid < kk) {
+            const uint64_t k = s_rk[tid];
+            int rk = 0;
+            for (int q = 0; q < kk; ++q) rk += (int)(s_rk[q] > k);
+            s_x[rk] = s_top[tid];
+            s_xw[rk] = (uint32_t)(k >> 32);
+        }
+    } else {
+        ranks_by_weight<1, NTX>(rd.base, V, M, a.k1, kk, s_top, s_rk, s_x, s_xw, s_red);
+    }
+    __syncthreads();
+    const float ref_t = key_value(s_x[m]);
+    if (tid == 0 && !(ref_t > -INFINITY)) atomicOr(t.err, 512);   // x_{m+1} is -inf
+    uint64_t S1 = s_w1;
+    if (!counted || ref_t != guess) {
+        // every element's own weights
+        counted = false;
+        S1 = 0;
+        for (int s = 0; s < NB; ++s) {
+            uint64_t w1 = 0, zq = 0;
+            uint4 next = load_row_vec<1>(rd.base, rd.vidx(s * EBATCH), V);
+#pragma unroll 1
+            for (int q = s * EBATCH; q < (s + 1) * EBATCH; ++q) {
+                const uint4 x = next;
+                const int e0 = rd.vidx(q) * 8;
+                if (q + 1 < (s + 1) * EBATCH) next = load_row_vec<1>(rd.base, rd.vidx(q + 1), V);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const float l = elem<1>(x, k);
+                    w1 += (e0 + k < V) ? cweight_below(l, M, a.k1) : 0u;
+                    zq += (e0 + k < V) ? cweight(l, ref_t, a.kT) : 0u;
+                }
+            }
+            S1 += block_sum_u64<NTX>(w1, s_red);
+            zq = block_sum_u64<NTX>(zq, s_red);
+            if (tid == 0) s_seg[s] = zq;
+        }
+        __syncthreads();
+    }
+
+    // ---- Y ~ q~_T: the leads leave the tail; the batch that holds
+    //      t = floor(U64 Zq / 2^64), then the 64-vector slot, then the token
+    uint64_t Zq = 0;
+    for (int s = 0; s < NB; ++s) Zq += s_seg[s];
+    for (int i = 0; i < m; ++i) Zq -= cweight(key_value(s_x[i]), ref_t, a.kT);
+    int cs = -1;
+    uint64_t t2 = 0;
+    {
+        const uint64_t tt = __umul64hi(rs.u, Zq);
+        uint64_t acc = 0;
+        for (int s = 0; s < NB; ++s) {
+            uint64_t z = s_seg[s];
+            for (int i = 0; i < m; ++i)
+                if (key_id(s_x[i]) / (SEGV * 8) == s) z -= cweight(key_value(s_x[i]), ref_t, a.kT);
+            if (cs < 0 && tt < acc + z) {
+                cs = s;
+                t2 = tt - acc;
+            }
+            acc += z;
+        }
+    }
+    if (cs >= 0) {
+        // slot (q, wave): vectors NTX q + 64 wave + lane of the batch
+        const int v0 = cs * SEGV + tid;
+        uint4 r[EBATCH];
+#pragma unroll
+        for (int e = 0; e < EBATCH; ++e) r[e] = load_row_vec<1>(rd.base, v0 + e * NTX, V);
+        auto weight = [&](uint32_t bits) -> uint32_t {
+            const uint32_t mag = bits & 0x7FFFu;
+            if (!counted || mag <= HIST_BASE) return cweight(__uint_as_float(bits << 16), ref_t, a.kT);
+            return tab[min(mag - HIST_BASE, (uint32_t)HIST_OUT) + (bits >> 15) * HIST_WORDS];
+        };
+        uint64_t sq[EBATCH];
+#pragma unroll
+        for (int e = 0; e < EBATCH; ++e) {
+            const uint32_t* w = &r[e].x;
+            sq[e] = 0;
+            if (counted) {
+                bool small = false;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const uint32_t mag0 = w[c] & 0x7FFFu, mag1 = (w[c] >> 16) & 0x7FFFu;
+                    small |= mag0 <= HIST_BASE || mag1 <= HIST_BASE;
+                    // (word 0 of the tables is 0: values below 2^-11 follow)
+                    const uint32_t i0 = min(__builtin_elementwise_sub_sat(mag0, HIST_BASE),
+                                            (uint32_t)HIST_OUT),
+                                   i1 = min(__builtin_elementwise_sub_sat(mag1, HIST_BASE),
+                                            (uint32_t)HIST_OUT);
+                    sq[e] += (uint64_t)(tab[i0 + ((w[c] >> 15) & 1u) * HIST_WORDS] +
+                                        tab[i1 + (w[c] >> 31) * HIST_WORDS]);
+                }
+                if (__ballot(small) != 0ull) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        for (int k = 0; k < 2; ++k) {
+                            const uint32_t bits = (w[c] >> (16 * k)) & 0xFFFFu;
+                            if ((bits & 0x7FFFu) <= HIST_BASE)
+                                sq[e] += cweight(__uint_as_float(bits << 16), ref_t, a.kT);
+                        }
+                }
+            } else {
+                const int e0 = (v0 + e * NTX) * 8;
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    sq[e] += (e0 + k < V) ? cweight(elem<1>(r[e], k), ref_t, a.kT) : 0u;
+            }
+            for (int i = 0; i < m; ++i)
+                if (key_id(s_x[i]) / 8 == v0 + e * NTX)
+                    sq[e] -= cweight(key_value(s_x[i]), ref_t, a.kT);
+            const uint64_t z = wave_sum_u64(sq[e]);
+            if (lane == 0) s_slot[e * NW + wid] = z;
+            __builtin_amdgcn_sched_barrier(0);   // (one vector's lookups in registers at a time)
+        }
+        __syncthreads();
+        const uint64_t z = s_slot[lane];
+        const uint64_t pre = wave_incl_scan_u64(z) - z;
+        const uint64_t hit = __ballot(pre <= t2 && t2 - pre < z);
+        const int slot = hit ? (int)__builtin_ctzll(hit) : -1;
+        if (slot >= 0 && slot % NW == wid) {
+            const uint64_t t3 = t2 - lane_u64(pre, slot);
+            uint64_t mine = 0;
+            uint4 x = make_uint4(0, 0, 0, 0);
+#pragma unroll
+            for (int e = 0; e < EBATCH; ++e)
+                if (e == slot / NW) {
+                    mine = sq[e];
+                    x = r[e];
+                }
+            uint64_t acc = wave_incl_scan_u64(mine) - mine;
+            if (acc <= t3 && t3 - acc < mine) {
+                const int e0 = (v0 + slot / NW * NTX) * 8;
+                const uint32_t* w = &x.x;
+                bool found = false;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    uint64_t q = e0 + k < V ? weight((w[k / 2] >> (16 * (k & 1))) & 0xFFFFu) : 0u;
+                    for (int i = 0; i < m; ++i)
+                        if (key_id(s_x[i]) == e0 + k) q = 0;
+                    if (!found && t3 < acc + q) {
+                        found = true;
+                        s_y = e0 + k;
+                        s_qy = q;
+                    }
+                    acc += q;
+                }
+            }
+        }
+    }
+    __syncthreads();
+
+    // ---- wave 0: the expanded node's record and its K children (App. C.1) ----
+    if (wid == 0) {
+        int ytok = s_y;
+        uint32_t qy = (uint32_t)s_qy;
+        if (ytok < 0) {                          // unreachable fallback
+            if (tid == 0) atomicOr(t.err, 1);
+            ytok = key_id(s_x[m]);
+            qy = 1;
+        }
+        const int pu = rs.pu;
+        const int cb = (level == 0) ? 1 : 1 + K + (level - 1) * NE * K;
+        const int e_idx = (level == 0) ? 0 : 1 + (level - 1) * NE + j;
+        if (tid == 0) {
+            t.zq[(int64_t)b * t.E + e_idx] = Zq;
+            t.dref[(int64_t)b * t.E + e_idx] = ref_t;
+            t.node[nb + pu].first_child = cb + j * K;
+            t.node[nb + pu].exp_of = e_idx;
+            if (level == 0) emit_root(t, nb);
+        }
+        if (tid < m) t.dleads[((int64_t)b * t.E + e_idx) * 16 + tid] = key_id(s_x[tid]);
+        // Y's place among x_{m+1}.. (kk: beyond)
+        const uint64_t at = __ballot(tid >= m && tid < kk && key_id(s_x[min(tid, kk - 1)]) == ytok);
+        const int yr = at ? (int)__builtin_ctzll(at) : kk;
+        int rk = min(tid, kk - 1), kind = LEAD;  // pure top-K pools: every slot a lead
+        if (!t.topk && tid >= m) {
+            kind = tid == m ? SAMPLED : FILL;
+            rk = min(tid - 1 + (tid - 1 >= yr ? 1 : 0), kk - 1);
+        }
+        if (kind == SAMPLED) rk = 0;
+        // one division for all lanes, Y's own probability in lane 32
+        uint32_t num = s_xw[max(rk, 0)];
+        uint64_t den = S1;
+        if (kind == SAMPLED && m >= 1) {
+            uint64_t lead = 0;
+            for (int q = 0; q < m; ++q) lead += s_xw[q];
+            const uint64_t z = S1 - lead;
+            const uint64_t wm = s_xw[m - 1];
+            num = (uint32_t)(wm < z ? wm : z);
+        }
+        if (lane == 32) {
+            num = qy;
+            den = Zq;
+        }
+        double proxy = __ddiv_rn((double)num, (double)den);
+        const uint64_t py = lane_u64((uint64_t)__double_as_longlong(proxy), 32);
+        if (kind == SAMPLED && m == 0) proxy = fmin(1.0, __dadd_rn(proxy, t.eps));
+        const double qtrue = kind == SAMPLED ? __longlong_as_double((long long)py) : proxy;
+        const int tok = kind == SAMPLED ? ytok : key_id(s_x[max(rk, 0)]);
+        if (tid < K) emit_child(t, a, b, j, pu, rt.pr, tid, kind, tok, proxy, qtrue, -1, ps);
+    }
+    select_frontier(t, a, b, j, rt.pr, s_top, (uint64_t*)(s_pdyn + L.p.k2), ps);
+}
+
+static size_t dense_row_shm(const TreeDev& t) {
+    return (size_t)row_lds(t.Sc, false, row_batches<1, NTX>(t.V), NTX, COUNT_BATCH).p.bytes;
+}
+
+// Raises the kernel's limit on dynamic LDS.
+hipError_t prepare_dense(const TreeDev& t) {
+    if (!t.dense || !t.dtype) return hipSuccess;
+    return hipFuncSetAttribute((const void*)&k_dense_row,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)dense_row_shm(t));
+}
+
+hipError_t launch_dense_row(const TreeDev& t, const LevelArgs& a, hipStream_t s) {
+    RowArgs ra{t, a};
+    void* args[] = {&ra};
+    return hipLaunchKernel((const void*)&k_dense_row, dim3(t.B * a.P), dim3(NTX), args,
+                           dense_row_shm(t), s);
 }
 
 template <int DT>

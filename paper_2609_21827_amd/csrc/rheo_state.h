@@ -111,6 +111,8 @@ hipError_t launch_expand(const TreeDev& t, const LevelArgs& a, int variant,
                          hipStream_t s);
 hipError_t launch_select(const TreeDev& t, const LevelArgs& a, int variant, hipStream_t s);
 hipError_t launch_dense(const TreeDev& t, const LevelArgs& a, int nvc, hipStream_t s);
+hipError_t launch_dense_row(const TreeDev& t, const LevelArgs& a, hipStream_t s);
+hipError_t prepare_dense(const TreeDev& t);
 hipError_t prepare_prune(const TreeDev& t);
 hipError_t launch_prune(const TreeDev& t, int R, hipStream_t s);
 hipError_t verify_shape(const TreeDev& t, int* G, int* segch, int* grid);

@@ -223,3 +223,19 @@ def test_prune_budgets(dev, R, same):
                 want[i, j] = 1
                 j = par[b][j]
         assert np.array_equal(mask[b], want)
+
+
+# dense mode's row kernel: the counts' edges as above, ties of the last listed
+# construction weight, the draw's batch and slot, the longest row
+@pytest.mark.parametrize("kind", ["plain", "edges", "small", "large", "const", "sorted", "sorted_up",
+                                  "ties", "signed_zeros", "zero_cross"])
+@pytest.mark.parametrize("V,m,K,T,method", [(9001, 1, 5, 1.0, "rheo"), (32769, 0, 12, 0.7, "rrsw"),
+                                            (70000, 3, 4, 1.5, "topk")])
+def test_dense_rows(dev, kind, V, m, K, T, method):
+    _check(V, "bf16", 0, kind, 14, m=m, K=K, depth=2, T=T, method=method)
+
+
+@pytest.mark.parametrize("dtype,V", [("bf16", 32760), ("bf16", 32768), ("bf16", 131073),
+                                     ("bf16", 262143), ("bf16", 300), ("f32", 5003)])
+def test_dense_sizes(dev, dtype, V):
+    _check(V, dtype, 0, "plain", 15, depth=2)
