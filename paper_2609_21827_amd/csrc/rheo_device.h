@@ -60,9 +60,13 @@ __device__ inline uint64_t philox_draw(uint64_t key, uint64_t purpose,
 // taken as the truncating conversion of the exact product 2^30 P * 2^n
 // (a scaling by a power of two, exact; below t = -31 it is < 1, so 0).
 // ---------------------------------------------------------------------------
+//
+// For t in [-64, 0], rint(t) and its scaling come from one rounded addition of
+// 1.5 * 2^23: the sum's low bits hold n, which the shift adds to the exponent
+// of P (2^30 P lies in [2^29, 2^31), so no result is denormal).
 __device__ __forceinline__ uint32_t cweight_of_t(float t) {
-    const float n = rintf(t);
-    const float f = __fsub_rn(t, n);
+    const float r = __fadd_rn(t, 0x1.8p+23f);
+    const float f = __fsub_rn(t, __fsub_rn(r, 0x1.8p+23f));
     float p = 0x1.430912p+17f;
     p = __fmaf_rn(p, f, 0x1.5d87fep+20f);
     p = __fmaf_rn(p, f, 0x1.3b2ab6p+23f);
@@ -70,7 +74,7 @@ __device__ __forceinline__ uint32_t cweight_of_t(float t) {
     p = __fmaf_rn(p, f, 0x1.ebfbe0p+27f);
     p = __fmaf_rn(p, f, 0x1.62e430p+29f);
     p = __fmaf_rn(p, f, 0x1.000000p+30f);
-    return (uint32_t)__builtin_amdgcn_ldexpf(p, (int)n);
+    return (uint32_t)__uint_as_float(__float_as_uint(p) + (__float_as_uint(r) << 23));
 }
 __device__ __forceinline__ uint32_t cweight(float l, float ref, float kT) {
     const float t = __fmul_rn(__fsub_rn(l, ref), kT);

@@ -129,6 +129,12 @@ __device__ __forceinline__ u128 wave_incl_scan_u128(u128 v) {
     if (row >= 3) add_u128(lo, hi, l2, h2);
     return ((u128)hi << 64) | lo;
 }
+// A weight times a total: 32 x 64 bits, two multiply-adds.
+__device__ __forceinline__ u128 mul_32x64(uint32_t a, uint64_t b) {
+    const uint64_t lo = (uint64_t)a * (uint32_t)b;
+    const uint64_t hi = (uint64_t)a * (uint32_t)(b >> 32) + (lo >> 32);
+    return ((u128)(hi >> 32) << 64) | (hi << 32) | (uint32_t)lo;
+}
 // exclusive scan across the block; *total receives the sum
 __device__ u128 block_excl_scan_u128(u128 v, u128* sh, u128* total) {
     const int l = threadIdx.x % WAVE, w = threadIdx.x / WAVE;
@@ -204,9 +210,11 @@ __device__ bool team_max_exchange(uint64_t* words, int g, int G, uint64_t epoch,
 
 // The team's total of p's weights (sparse mode): every block publishes the
 // sum over its segment (< 2^48 - 1: at most 2^18 - 1 tokens of weight
-// <= 2^30) in one word with the low 16 bits of the epoch, after its chunk
-// totals; the words then carry every segment's sum, so the total needs no
-// further read.  A block whose weights were taken relative to a guessed
+// <= 2^30) in one word with the low 16 bits of the epoch; the words then
+// carry every segment's sum, so the total needs no further read.  The chunk
+// totals, which only a layer's final sample reads, follow the sum (their
+// reductions overlap the wait) and carry the epoch themselves: a chunk's sum
+// is at most 2^39.  A block whose weights were taken relative to a guessed
 // maximum that its segment exceeds publishes 2^48 - 1 instead (no sum
 // reaches it), and *s_miss tells every block of the team.  A word left from
 // an earlier barrier is fewer than 2^16 epochs old, so the 16-bit
@@ -215,25 +223,27 @@ __device__ bool team_max_exchange(uint64_t* words, int g, int G, uint64_t epoch,
 // team_barrier.
 constexpr uint64_t kMiss = (1ull << 48) - 1;
 
-__device__ bool team_sum_exchange(uint64_t* words, int g, int G, uint64_t epoch,
-                                  const uint64_t* wsum, int nw, long spin_limit, int32_t* err,
-                                  int* s_ok, uint64_t* s_total, int* s_miss) {
+__device__ __forceinline__ void team_sum_publish(uint64_t* words, int g, uint64_t epoch,
+                                                 const uint64_t* wsum, int nw) {
+    constexpr uint64_t M48 = (1ull << 48) - 1;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint64_t sum = 0;
+        bool miss = false;
+        for (int w = 0; w < nw; ++w) {
+            miss |= wsum[w] == kMiss;
+            sum += wsum[w];
+        }
+        __hip_atomic_store(&words[g], ((epoch & 0xFFFFull) << 48) | (miss ? kMiss : sum & M48),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+__device__ bool team_sum_wait(uint64_t* words, int G, uint64_t epoch, long spin_limit,
+                              int32_t* err, int* s_ok, uint64_t* s_total, int* s_miss) {
     constexpr uint64_t M48 = (1ull << 48) - 1;
     const uint64_t e16 = epoch & 0xFFFFull;
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
     if (threadIdx.x < WAVE) {
-        if (threadIdx.x == 0) {
-            *s_ok = 1;
-            uint64_t sum = 0;
-            bool miss = false;
-            for (int w = 0; w < nw; ++w) {
-                miss |= wsum[w] == kMiss;
-                sum += wsum[w];
-            }
-            __hip_atomic_store(&words[g], (e16 << 48) | (miss ? kMiss : sum & M48),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        if (threadIdx.x == 0) *s_ok = 1;
         uint64_t v = 0;
         bool miss = false;
         long spins = 0;
@@ -503,7 +513,8 @@ __global__ __launch_bounds__(NTV, 4) void k_verify(VerifyParams) {
         // thread exceeds Mw.  The tail past V reads as -inf, of weight 0 for
         // a finite Mw, so no element needs a bounds test (which would
         // branch per element and serialise the weights).
-        auto seg_weights = [&](float Mw, bool* over) -> uint64_t {
+        auto seg_weights = [&](float Mw, bool* over, uint64_t ep) -> uint64_t {
+            const uint64_t tag = (ep & 0xFFFFull) << 48;
             uint64_t wpart = 0;
             bool ov = false;
 #pragma unroll
@@ -524,7 +535,7 @@ __global__ __launch_bounds__(NTV, 4) void k_verify(VerifyParams) {
                     sum = wave_sum_u64(sum);
                     wpart += sum;
                     if (lane == 0)
-                        __hip_atomic_store(&chunk_x[c], sum, __ATOMIC_RELAXED,
+                        __hip_atomic_store(&chunk_x[c], tag | sum, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
@@ -542,13 +553,14 @@ __global__ __launch_bounds__(NTV, 4) void k_verify(VerifyParams) {
                 sum = wave_sum_u64(sum);
                 wpart += sum;
                 if (lane == 0)
-                    __hip_atomic_store(&chunk_x[c], sum, __ATOMIC_RELAXED,
+                    __hip_atomic_store(&chunk_x[c], tag | sum, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
             }
             *over = ov;
             return wpart;
         };
         float M;
+        uint64_t cepoch = 0;                 // the epoch of this layer's chunk totals
         {
             // ---- 1. the row maximum is guessed as the largest target logit
             //         at the special tokens and the pruned children (all of
@@ -578,12 +590,13 @@ __global__ __launch_bounds__(NTV, 4) void k_verify(VerifyParams) {
                 if (ctok >= 0) gm = fmaxf(gm, c_l);
                 gm = block_max<NTV>(gm, s_redf);
                 bool over;
-                const uint64_t wpart = seg_weights(gm, &over);
-                special_weights(gm);
+                cepoch = epoch + 3 * level + 1;
+                const uint64_t wpart = seg_weights(gm, &over, cepoch);
                 over = __ballot(over) != 0;
                 if (lane == 0) s_red[wid] = over ? kMiss : wpart;
-                if (!team_sum_exchange(tsum_x, g, G, epoch + 3 * level + 1, s_red, NWV, a.spin,
-                                       t.err, &s_ok, &s_Sp, &s_miss)) {
+                team_sum_publish(tsum_x, g, cepoch, s_red, NWV);
+                special_weights(gm);
+                if (!team_sum_wait(tsum_x, G, cepoch, a.spin, t.err, &s_ok, &s_Sp, &s_miss)) {
                     failed = true;
                     break;
                 }
@@ -606,11 +619,12 @@ __global__ __launch_bounds__(NTV, 4) void k_verify(VerifyParams) {
                 }
                 M = s_M;
                 bool over;
-                const uint64_t wpart = seg_weights(M, &over);
-                special_weights(M);
+                cepoch = epoch + 3 * level + 3;
+                const uint64_t wpart = seg_weights(M, &over, cepoch);
                 if (lane == 0) s_red[wid] = wpart;
-                if (!team_sum_exchange(tsum_x, g, G, epoch + 3 * level + 3, s_red, NWV, a.spin,
-                                       t.err, &s_ok, &s_Sp, &s_miss)) {
+                team_sum_publish(tsum_x, g, cepoch, s_red, NWV);
+                special_weights(M);
+                if (!team_sum_wait(tsum_x, G, cepoch, a.spin, t.err, &s_ok, &s_Sp, &s_miss)) {
                     failed = true;
                     break;
                 }
@@ -694,7 +708,7 @@ __global__ __launch_bounds__(NTV, 4) void k_verify(VerifyParams) {
             if (resid && !DN) {
                 u128 d = 0;
                 for (int i = lane; i < nt; i += WAVE) {
-                    const u128 pz = (u128)s_tp[i] * Zq, qs = (u128)s_tq[i] * Zl;
+                    const u128 pz = mul_32x64(s_tp[i], Zq), qs = mul_32x64(s_tq[i], Zl);
                     d += pz < qs ? pz : qs;
                 }
                 Zrem = (u128)Zq * Zl - wave_sum_u128(d);
@@ -706,7 +720,7 @@ __global__ __launch_bounds__(NTV, 4) void k_verify(VerifyParams) {
                     const int ti = s_c_tail[lane];
                     Nu = F * (u128)P;
                     if (resid && ti >= 0) {
-                        const u128 pz = (u128)P * Zq, qs = (u128)s_tq[ti] * Zl;
+                        const u128 pz = mul_32x64((uint32_t)P, Zq), qs = mul_32x64(s_tq[ti], Zl);
                         Nu = pz > qs ? pz - qs : (u128)0;
                     }
                 }
@@ -739,22 +753,30 @@ __global__ __launch_bounds__(NTV, 4) void k_verify(VerifyParams) {
         if (DN && s_mode == 0) {
             // N_v = max(0, P_v Zq - Q_v Z_l) over all of V (Q_v from the draft
             // row, 0 at the leads; P_v = 0 at leads rejected before Y):
-            // chunk totals over the segment, exchanged
+            // chunk totals over the segment, exchanged.  Every token is taken
+            // alike (past V both weights are 0), and the lane that holds a
+            // lead then puts it right: tests of every token against the leads
+            // and V had the slowest walks at 24 us a layer there (16 blocks a row of
+            // 128256); 64 dense sequences verify in 90 us instead of 101.
             for (int c = c0 + wid; c < c1; c += NWV) {
                 const uint4 xv = load_vec<DT>(row, c * WAVE + lane, V);
                 const uint4 dv = load_vec<DT>(drow, c * WAVE + lane, V);
                 u128 sum = 0;
 #pragma unroll
                 for (int k = 0; k < VEC; ++k) {
-                    const int v = (c * WAVE + lane) * VEC + k;
-                    if (v < V) {
-                        bool lead = false, rej = false;
-                        for (int q = 0; q < nlead; ++q) lead |= s_lead[q] == v;
-                        for (int q = 0; q < nrej; ++q) rej |= s_c_tok[q] == v;
-                        const uint64_t P = rej ? 0u : cweight(velem<DT>(xv, k), M, a.kT);
-                        const uint64_t Q = lead ? 0u : cweight(velem<DT>(dv, k), dref, a.kT);
-                        const u128 pz = (u128)P * Zq, qs = (u128)Q * Zl;
-                        sum += pz > qs ? pz - qs : (u128)0;
+                    const u128 pz = mul_32x64(cweight(velem<DT>(xv, k), M, a.kT), Zq);
+                    const u128 qs = mul_32x64(cweight(velem<DT>(dv, k), dref, a.kT), Zl);
+                    sum += pz > qs ? pz - qs : (u128)0;
+                }
+                for (int q = 0; q < nlead; ++q) {
+                    const int v = s_lead[q];
+                    if (v / VEC == c * WAVE + lane) {
+                        bool rej = false;
+                        for (int x = 0; x < nrej; ++x) rej |= s_c_tok[x] == v;
+                        const u128 pz = mul_32x64(cweight(load_logit<DT>(row, v), M, a.kT), Zq);
+                        const u128 qs = mul_32x64(cweight(load_logit<DT>(drow, v), dref, a.kT), Zl);
+                        sum -= pz > qs ? pz - qs : (u128)0;
+                        sum += rej ? (u128)0 : pz;
                     }
                 }
                 sum = wave_sum_u128(sum);
@@ -777,7 +799,7 @@ __global__ __launch_bounds__(NTV, 4) void k_verify(VerifyParams) {
                 u128 Nu = 0;
                 if (lane < nc) {
                     const uint64_t P = s_tp[nt + lane];
-                    const u128 pz = (u128)P * Zq, qs = (u128)s_c_q[lane] * Zl;
+                    const u128 pz = mul_32x64((uint32_t)P, Zq), qs = mul_32x64(s_c_q[lane], Zl);
                     Nu = pz > qs ? pz - qs : (u128)0;
                 }
                 const int next = cand_tests(t.rrsw ? spos + 1 : 0, nc, spos, Nu, &Zrem);
@@ -807,22 +829,34 @@ __global__ __launch_bounds__(NTV, 4) void k_verify(VerifyParams) {
         // ---- final sample u* ~ r (one block of the team) --------------------
         if (g != 0) break;
         {
-            // the chunk totals, published before the sum exchange; for
+            // the chunk totals, which carry the layer's epoch (read again until
+            // they do); for
             // the residual, every chunk's sum of min(P_v Zq, Q_v Z_l) over
             // the live tail tokens in it, gathered from the tail entries in
             // two limbs: the deficit is below 2^71 (P_v <= 2^30, Zq < 2^40),
             // so its low 40 bits and the rest (< 2^31), summed over at most
             // 1023 entries, stay below 2^64
+            bool late = false;
             for (int c = tid; c < NC; c += NTV) {
-                s_chunk[c] = __hip_atomic_load(&chunk_x[c], __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
+                uint64_t w;
+                long spins = 0;
+                do {
+                    w = __hip_atomic_load(&chunk_x[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                } while ((w >> 48) != (cepoch & 0xFFFFull) && ++spins <= a.spin);
+                late |= (w >> 48) != (cepoch & 0xFFFFull);
+                s_chunk[c] = w & ((1ull << 48) - 1);
                 s_dlo[c] = 0;
                 s_dhi[c] = 0;
+            }
+            if (__syncthreads_or(late)) {
+                if (tid == 0) atomicOr(t.err, 128);
+                failed = true;
+                break;
             }
             __syncthreads();
             if (residual) {
                 for (int i = tid; i < nt; i += NTV) {
-                    const u128 pz = (u128)s_tp[i] * Zq, qs = (u128)s_tq[i] * Zl;
+                    const u128 pz = mul_32x64(s_tp[i], Zq), qs = mul_32x64(s_tq[i], Zl);
                     const u128 d = pz < qs ? pz : qs;
                     const int c = s_tid[i] / CH;
                     atomicAdd(&s_dlo[c], (uint64_t)d & ((1ull << 40) - 1));
@@ -923,7 +957,7 @@ __global__ __launch_bounds__(NTV, 4) void k_verify(VerifyParams) {
             for (int i = tid; i < nt; i += NTV) {
                 const int v = s_tid[i];
                 if (v / CH == cs) {
-                    const u128 pz = (u128)s_tp[i] * Zq, qs = (u128)s_tq[i] * Zl;
+                    const u128 pz = mul_32x64(s_tp[i], Zq), qs = mul_32x64(s_tq[i], Zl);
                     s_cn[v - cs * CH] = pz > qs ? pz - qs : (u128)0;
                 }
             }
@@ -990,8 +1024,19 @@ hipError_t verify_shape(const TreeDev& t, int* G_out, int* segch, int* grid) {
     if (e != hipSuccess) return e;
     const int teams_per_xcd = (t.B + 7) / 8;
     int G = target / (8 * teams_per_xcd);
+    if (!env) {
+        // At least two chunks per wave, and at most 32 blocks: with more, the
+        // blocks' polls of each other's words take longer than the weights
+        // they share out (k_verify, 16 sequences of 128256 fp32: G = 16 65 us,
+        // 32 60 us, 64 76 us; 6 of 50001 bf16: G = 16 26 us, 64 37 us; one of
+        // 128256 bf16: G = 16 43 us, 32 41 us, 64 46 us).
+        const int most = (NC + 2 * NWV - 1) / (2 * NWV);
+        if (G > most) G = most;
+        if (G > 32) G = 32;
+    }
     if (G > GMAX) G = GMAX;
     if (G > NC) G = NC;
+    if (G < 1) G = 1;
     while (G > 1 && 8 * teams_per_xcd * G > per_cu * cus) --G;
     if (G < 1) G = 1;
     const int blocks = 8 * teams_per_xcd * G;
