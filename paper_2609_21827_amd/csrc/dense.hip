@@ -519,7 +519,7 @@ __global__ __launch_bounds__(NTX, 4) void k_dense_row(RowArgs) {
     __shared__ uint64_t s_rk[KKMAX];             // ranking keys (w1 << 32 | ~id)
     __shared__ uint64_t s_seg[ROW_BATCHES];      // the batches' tail weights
     __shared__ uint64_t s_w1, s_n, s_qy;
-    __shared__ uint64_t s_slot[WAVE];            // tail weights of the 64-vector slots of a batch
+    __shared__ uint64_t s_slot[NW];              // the waves' tail weights of a batch
     __shared__ uint64_t s_red[NW];
     __shared__ int s_flag, s_y;
 
@@ -551,47 +551,47 @@ __global__ __launch_bounds__(NTX, 4) void k_dense_row(RowArgs) {
     const uint64_t kb = s_top[kk - 1];
     const float vb = key_value(kb);
     const uint32_t wmin = cweight(vb, M, a.k1);  // the least weight of the top kk
-    {
-        uint64_t w1 = 0, n = 0, zq[ROW_BATCHES];
+    // (NS: the tables read, 4 or 8)
+    auto totals = [&](auto NS_) {
+        constexpr int NS = decltype(NS_)::value;
+        uint64_t w1 = 0, n = 0, zq[NS];
         bool tie = false;
 #pragma unroll
-        for (int s = 0; s < ROW_BATCHES; ++s) zq[s] = 0;
+        for (int s = 0; s < NS; ++s) zq[s] = 0;
         for (int i = tid; i < HIST_WORDS; i += NTX) {
-            uint32_t c[ROW_BATCHES], any = 0;
+            uint32_t c[NS], any = 0, pos = 0, neg = 0;
 #pragma unroll
-            for (int s = 0; s < ROW_BATCHES; ++s) {
+            for (int s = 0; s < NS; ++s) {
                 c[s] = s < NB ? tab[s * HIST_WORDS + i] : 0u;
                 any |= c[s];
-                n += (c[s] & 0xFFFFu) + (c[s] >> 16);
+                pos += c[s] & 0xFFFFu;
+                neg += c[s] >> 16;
             }
+            n += pos + neg;
             uint32_t qp = 0, qn = 0;
             if (i >= 1 && i < HIST_OUT) {
-                if (any & 0xFFFFu) {
+                if (pos) {
                     const float l = hist_value(i);
                     const uint32_t w = cweight(l, M, a.k1);
                     qp = cweight(l, guess, a.kT);
                     tie |= l < vb && w == wmin;
+                    w1 += (uint64_t)pos * w;
 #pragma unroll
-                    for (int s = 0; s < ROW_BATCHES; ++s) {
-                        w1 += (uint64_t)(c[s] & 0xFFFFu) * w;
-                        zq[s] += (uint64_t)(c[s] & 0xFFFFu) * qp;
-                    }
+                    for (int s = 0; s < NS; ++s) zq[s] += (uint64_t)(c[s] & 0xFFFFu) * qp;
                 }
-                if (any >> 16) {
+                if (neg) {
                     const float l = -hist_value(i);
                     const uint32_t w = cweight(l, M, a.k1);
                     qn = cweight(l, guess, a.kT);
                     tie |= l < vb && w == wmin;
+                    w1 += (uint64_t)neg * w;
 #pragma unroll
-                    for (int s = 0; s < ROW_BATCHES; ++s) {
-                        w1 += (uint64_t)(c[s] >> 16) * w;
-                        zq[s] += (uint64_t)(c[s] >> 16) * qn;
-                    }
+                    for (int s = 0; s < NS; ++s) zq[s] += (uint64_t)(c[s] >> 16) * qn;
                 }
             } else if (i >= HIST_OUT) {
                 // -2^9 and below: only if of no weight
-                if ((any & 0xFFFFu) || ((any >> 16) && (cweight(-512.0f, M, a.k1) != 0u ||
-                                                        cweight(-512.0f, guess, a.kT) != 0u)))
+                if (pos || (neg && (cweight(-512.0f, M, a.k1) != 0u ||
+                                    cweight(-512.0f, guess, a.kT) != 0u)))
                     n += 1ull << 40;
                 tie |= any != 0 && wmin == 0u;
             }
@@ -621,14 +621,15 @@ __global__ __launch_bounds__(NTX, 4) void k_dense_row(RowArgs) {
             atomicAdd((unsigned long long*)&s_n, (unsigned long long)n);
         }
 #pragma unroll
-        for (int s = 0; s < ROW_BATCHES; ++s) {
-            if (s < NB) {
-                const uint64_t z = wave_sum_u64(zq[s]);
-                if (lane == 0) atomicAdd((unsigned long long*)&s_seg[s], (unsigned long long)z);
-            }
+        for (int s = 0; s < NS; ++s) {
+            const uint64_t z = wave_sum_u64(zq[s]);
+            if (lane == 0 && s < NB)
+                atomicAdd((unsigned long long*)&s_seg[s], (unsigned long long)z);
         }
         if (__ballot(tie) != 0ull && lane == 0) s_flag = 1;
-    }
+    };
+    if (NB <= 4) totals(std::integral_constant<int, 4>());
+    else totals(std::integral_constant<int, ROW_BATCHES>());
     // x_1..x_kk by (w1 desc, id asc): ranks among the top kk by logit
     if (tid < kk) {
         const uint32_t w = cweight(key_value(s_top[tid]), M, a.k1);
@@ -699,36 +700,35 @@ __global__ __launch_bounds__(NTX, 4) void k_dense_row(RowArgs) {
         }
     }
     if (cs >= 0) {
-        // slot (q, wave): vectors NTX q + 64 wave + lane of the batch
-        const int v0 = cs * SEGV + tid;
+        // wave w reads the 64-vector slots 8 w .. 8 w + 7 of the batch
+        const int v0 = cs * SEGV + wid * (EBATCH * WAVE) + lane;
         uint4 r[EBATCH];
 #pragma unroll
-        for (int e = 0; e < EBATCH; ++e) r[e] = load_row_vec<1>(rd.base, v0 + e * NTX, V);
-        auto weight = [&](uint32_t bits) -> uint32_t {
-            const uint32_t mag = bits & 0x7FFFu;
-            if (!counted || mag <= HIST_BASE) return cweight(__uint_as_float(bits << 16), ref_t, a.kT);
-            return tab[min(mag - HIST_BASE, (uint32_t)HIST_OUT) + (bits >> 15) * HIST_WORDS];
-        };
-        uint64_t sq[EBATCH];
+        for (int e = 0; e < EBATCH; ++e) r[e] = load_row_vec<1>(rd.base, v0 + e * WAVE, V);
+        uint64_t sq[EBATCH], all = 0;
+        const hist_u16x2 hbase = {(unsigned short)HIST_BASE, (unsigned short)HIST_BASE};
+        const hist_u16x2 hout = {(unsigned short)HIST_OUT, (unsigned short)HIST_OUT};
+        const hist_u16x2 four = {4, 4};
+        const hist_u16x2 half = {(unsigned short)HIST_BYTES, (unsigned short)HIST_BYTES};
 #pragma unroll
         for (int e = 0; e < EBATCH; ++e) {
             const uint32_t* w = &r[e].x;
             sq[e] = 0;
             if (counted) {
-                bool small = false;
+                // the value's weight from the tables (word 0 is 0: values below
+                // 2^-11 follow; past the row NaN words, of no weight)
+                hist_u16x2 least = {0xFFFF, 0xFFFF};
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    const uint32_t mag0 = w[c] & 0x7FFFu, mag1 = (w[c] >> 16) & 0x7FFFu;
-                    small |= mag0 <= HIST_BASE || mag1 <= HIST_BASE;
-                    // (word 0 of the tables is 0: values below 2^-11 follow)
-                    const uint32_t i0 = min(__builtin_elementwise_sub_sat(mag0, HIST_BASE),
-                                            (uint32_t)HIST_OUT),
-                                   i1 = min(__builtin_elementwise_sub_sat(mag1, HIST_BASE),
-                                            (uint32_t)HIST_OUT);
-                    sq[e] += (uint64_t)(tab[i0 + ((w[c] >> 15) & 1u) * HIST_WORDS] +
-                                        tab[i1 + (w[c] >> 31) * HIST_WORDS]);
+                    const hist_u16x2 mag = __builtin_bit_cast(hist_u16x2, w[c] & 0x7FFF7FFFu);
+                    hist_u16x2 i = __builtin_elementwise_sub_sat(mag, hbase);
+                    least = __builtin_elementwise_min(least, i);
+                    i = __builtin_elementwise_min(i, hout) * four +
+                        (__builtin_bit_cast(hist_u16x2, w[c]) >> (unsigned short)15) * half;
+                    sq[e] += (uint64_t)(*(const uint32_t*)((const uint8_t*)tab + i.x) +
+                                        *(const uint32_t*)((const uint8_t*)tab + i.y));
                 }
-                if (__ballot(small) != 0ull) {
+                if (__ballot(least.x == 0 || least.y == 0) != 0ull) {
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
                         for (int k = 0; k < 2; ++k) {
@@ -738,49 +738,62 @@ __global__ __launch_bounds__(NTX, 4) void k_dense_row(RowArgs) {
                         }
                 }
             } else {
-                const int e0 = (v0 + e * NTX) * 8;
+                const int e0 = (v0 + e * WAVE) * 8;
 #pragma unroll
                 for (int k = 0; k < 8; ++k)
                     sq[e] += (e0 + k < V) ? cweight(elem<1>(r[e], k), ref_t, a.kT) : 0u;
             }
             for (int i = 0; i < m; ++i)
-                if (key_id(s_x[i]) / 8 == v0 + e * NTX)
+                if (key_id(s_x[i]) / 8 == v0 + e * WAVE)
                     sq[e] -= cweight(key_value(s_x[i]), ref_t, a.kT);
-            const uint64_t z = wave_sum_u64(sq[e]);
-            if (lane == 0) s_slot[e * NW + wid] = z;
+            all += sq[e];
             __builtin_amdgcn_sched_barrier(0);   // (one vector's lookups in registers at a time)
         }
+        all = wave_sum_u64(all);
+        if (lane == 0) s_slot[wid] = all;
         __syncthreads();
-        const uint64_t z = s_slot[lane];
-        const uint64_t pre = wave_incl_scan_u64(z) - z;
-        const uint64_t hit = __ballot(pre <= t2 && t2 - pre < z);
-        const int slot = hit ? (int)__builtin_ctzll(hit) : -1;
-        if (slot >= 0 && slot % NW == wid) {
-            const uint64_t t3 = t2 - lane_u64(pre, slot);
-            uint64_t mine = 0;
-            uint4 x = make_uint4(0, 0, 0, 0);
+        // the wave that holds t2 goes through its slots, then the lanes of one
+        uint64_t acc = 0;
+        int own = -1;
+        for (int w = 0; w < NW; ++w) {
+            const uint64_t z = s_slot[w];
+            if (own < 0 && t2 - acc < z) own = w;
+            if (own < 0) acc += z;
+        }
+        if (own == wid) {
+            uint64_t t3 = t2 - acc;              // remainder within the slots to come
+            uint64_t p = 0, mine = 0;
+            int slot = -1;
 #pragma unroll
-            for (int e = 0; e < EBATCH; ++e)
-                if (e == slot / NW) {
-                    mine = sq[e];
-                    x = r[e];
+            for (int e = 0; e < EBATCH; ++e) {
+                if (slot < 0) {
+                    const uint64_t inc = wave_incl_scan_u64(sq[e]);
+                    const uint64_t z = lane_u64(inc, WAVE - 1);
+                    if (t3 >= z) {
+                        t3 -= z;
+                    } else {
+                        slot = e;
+                        p = inc - sq[e];
+                        mine = sq[e];
+                    }
                 }
-            uint64_t acc = wave_incl_scan_u64(mine) - mine;
-            if (acc <= t3 && t3 - acc < mine) {
-                const int e0 = (v0 + slot / NW * NTX) * 8;
-                const uint32_t* w = &x.x;
+            }
+            if (slot >= 0 && p <= t3 && t3 - p < mine) {
+                // one lane: its vector again, element by element
+                const int vi = v0 + slot * WAVE;
+                const uint4 x = load_row_vec<1>(rd.base, vi, V);
                 bool found = false;
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
-                    uint64_t q = e0 + k < V ? weight((w[k / 2] >> (16 * (k & 1))) & 0xFFFFu) : 0u;
+                    uint64_t q = vi * 8 + k < V ? cweight(elem<1>(x, k), ref_t, a.kT) : 0u;
                     for (int i = 0; i < m; ++i)
-                        if (key_id(s_x[i]) == e0 + k) q = 0;
-                    if (!found && t3 < acc + q) {
+                        if (key_id(s_x[i]) == vi * 8 + k) q = 0;
+                    if (!found && t3 < p + q) {
                         found = true;
-                        s_y = e0 + k;
+                        s_y = vi * 8 + k;
                         s_qy = q;
                     }
-                    acc += q;
+                    p += q;
                 }
             }
         }
@@ -853,6 +866,7 @@ hipError_t prepare_dense(const TreeDev& t) {
 
 hipError_t launch_dense_row(const TreeDev& t, const LevelArgs& a, hipStream_t s) {
     RowArgs ra{t, a};
+    ra.a.cached = level_cached(t, t.B * a.P);
     void* args[] = {&ra};
     return hipLaunchKernel((const void*)&k_dense_row, dim3(t.B * a.P), dim3(NTX), args,
                            dense_row_shm(t), s);

@@ -925,6 +925,7 @@ hipError_t launch_expand_row(const TreeDev& t, const LevelArgs& a, hipStream_t s
     const int ntb = row_narrow(t, rows) ? NTE / 2 : expand_row_threads(t.dtype, t.V, t.S, t.cfull != 0);
     if (ntb == 0) return hipErrorInvalidValue;
     RowArgs ra{t, a};
+    ra.a.cached = level_cached(t, t.B * a.P);
     void* args[] = {&ra};
     return hipLaunchKernel(row_fn(t, ntb), dim3(rows), dim3(ntb), args, row_shm(t.dtype, t.V, t.S, ntb, t.cfull != 0), s);
 }

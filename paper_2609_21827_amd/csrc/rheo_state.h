@@ -91,6 +91,7 @@ struct LevelArgs {
     float kT;                      // sampling kT
     uint64_t rng_key;
     uint64_t fr_key;               // rng_key of the launch that chose this level's parents
+    int cached;                    // row kernels: ordinary loads (set by their launch)
 };
 
 struct VerifyArgs {

@@ -490,6 +490,14 @@ struct RowShared {
     uint64_t u;
 };
 
+// Whether a level's rows are read with ordinary loads: those of a few rows stay
+// in the L2s (4 MB on each of 8 XCDs) for the second read of the candidates
+// (8 rows of 128256 bf16: 16.6 us a level with streaming loads, 15.5 with
+// these); those of many evict each other (512 rows: 33.6 against 34.7 us).
+inline bool level_cached(const TreeDev& t, int rows) {
+    return (int64_t)rows * t.stride * (t.dtype ? 2 : 4) <= (16 << 20);
+}
+
 // A row as a block of NTB threads reads it: vector q of a thread is lane
 // `lane` of the 64-vector slot (wave + q) mod waves of block stride q; a batch
 // is EBATCH strides.  Rotating the slot spreads every wave's reads over all
@@ -499,15 +507,22 @@ template <int DT, int NTB>
 struct RowReader {
     const char* base;
     int V, NVF, wsu, lane;
+    bool cached;               // the level's rows stay in the L2s (see level_cached)
     __device__ __forceinline__ int vidx(int q) const {
         return (((wsu + q) & (NTB / WAVE - 1)) * WAVE + lane) + NTB * q;
     }
     __device__ __forceinline__ void load_batch(uint4 (&r)[EBATCH], int bt) const {
         // plain loads where every lane of the block reads whole vectors
         if (NTB * (bt * EBATCH + EBATCH) <= NVF) {
+            if (cached) {
 #pragma unroll
-            for (int e = 0; e < EBATCH; ++e)
-                r[e] = load_stream16(base + (int64_t)vidx(bt * EBATCH + e) * 16);
+                for (int e = 0; e < EBATCH; ++e)
+                    r[e] = *(const uint4*)(base + (int64_t)vidx(bt * EBATCH + e) * 16);
+            } else {
+#pragma unroll
+                for (int e = 0; e < EBATCH; ++e)
+                    r[e] = load_stream16(base + (int64_t)vidx(bt * EBATCH + e) * 16);
+            }
         } else {
 #pragma unroll
             for (int e = 0; e < EBATCH; ++e) {
@@ -527,6 +542,7 @@ __device__ __forceinline__ RowReader<DT, NTB> row_reader(const TreeDev& t, const
     rd.NVF = t.V / (DT ? 8 : 4);
     rd.wsu = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
     rd.lane = threadIdx.x % WAVE;
+    rd.cached = a.cached != 0;
     return rd;
 }
 template <int DT, int NTB>
