@@ -47,8 +47,9 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-KERNEL_SRCS = ["expand.hip", "dense.hip", "pool_common.h", "rheo_device.h", "rheo_state.h"]
-EXPAND_KERNELS = r"k_select|k_pool|k_dweights|k_dpool|k_expand_row"
+KERNEL_SRCS = ["expand.hip", "dense.hip", "row_select.h", "code_hist.h", "pool_common.h",
+               "rheo_device.h", "rheo_state.h"]
+EXPAND_KERNELS = r"k_select|k_pool|k_dweights|k_dpool|k_expand_row|k_dense_row"
 
 
 def kernel_src_hash():
@@ -94,6 +95,7 @@ def hold_stream(ms):
 
 def expand_kernel_name(w):
     return ("expand level (k_expand_row)" if w.support > 0
+            else "expand level (k_dense_row)" if w.dtype == "bf16"
             else "expand level (k_select + k_dweights + k_dpool)")
 
 
@@ -101,10 +103,10 @@ def write_traffic(paths, out, w, copy_bytes):
     """Scales the expand kernel's FETCH_SIZE / WRITE_SIZE by what the same
     counters read for a plain device copy of known size."""
     exp_f, exp_w, cp_f, cp_w = paths
-    # one expand level = one k_expand_row dispatch, or one k_select dispatch
+    # one expand level = one row-kernel dispatch, or one k_select dispatch
     # and the pool kernel(s) after it
-    nf = len(_counter_rows(exp_f, r"k_select|k_expand_row", "FETCH_SIZE"))
-    nw = len(_counter_rows(exp_w, r"k_select|k_expand_row", "WRITE_SIZE"))
+    nf = len(_counter_rows(exp_f, r"k_select|k_expand_row|k_dense_row", "FETCH_SIZE"))
+    nw = len(_counter_rows(exp_w, r"k_select|k_expand_row|k_dense_row", "WRITE_SIZE"))
     ef = [sum(_counter_rows(exp_f, EXPAND_KERNELS, "FETCH_SIZE")) / nf]
     ew = [sum(_counter_rows(exp_w, EXPAND_KERNELS, "WRITE_SIZE")) / nw]
     cf = _counter_rows(cp_f, r"copy|Copy", "FETCH_SIZE")

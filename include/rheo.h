@@ -115,23 +115,26 @@ typedef struct rheo_config {
 /* Allocates a tree for cfg (host pointer, copied).  *out receives the handle.
  * Node capacity per sequence: 1 + K + (D-1) * n_expand * K.
  * Launch shapes, read from the environment here and never changing a
- * result: RHEO_EXPAND_ROW (0: sparse levels on the chunked kernel pair, 1:
- * on the one-block-per-row kernel wherever the row fits it), RHEO_ROW_MIN
- * (fewest rows of a level for the per-row kernel, default 1),
+ * result: RHEO_EXPAND_ROW (0: levels on the chunked kernels, 1: on the
+ * one-block-per-row kernels wherever the row fits them; dense fp32 levels are
+ * always chunked), RHEO_ROW_MIN (fewest rows of a sparse level for the per-row
+ * kernel, default 1),
  * RHEO_ROW_NARROW (1 or 0: the per-row kernel's 256-thread blocks always or
  * never; by default when a level has more rows than the device holds
  * 512-thread blocks at once), RHEO_EXPAND_VARIANT (chunk size of the
- * chunked pair), RHEO_VERIFY_BLOCKS (blocks of all verification teams,
- * default 1024, capped by what the device holds at once).  RHEO_VERIFY_SPIN,
+ * chunked kernels), RHEO_VERIFY_BLOCKS (blocks of all verification teams,
+ * default 1024 and at most 32 a team with at least two chunks a wave; capped
+ * by what the device holds at once).  RHEO_VERIFY_SPIN,
  * read at each rheo_verify, sets the polls of a team wait before it gives up
  * (see rheo_verify). */
 int rheo_create(const rheo_config* cfg, rheo_tree** out);
 
 /* rheo_create for callers that cannot allocate device memory (serving loops
  * and harnesses that forbid hipMalloc): the tree's whole device state lives
- * in a static array of the library, 32 MiB per device, which every device
+ * in a static array of the library, 44 MiB per device, which every device
  * that loads the library holds until the process ends.  No device memory is
- * allocated or freed.  A configuration whose state exceeds 32 MiB returns
+ * allocated or freed.  A configuration whose state (64 bytes a node, the
+ * tails, the selection and verification scratch) exceeds 32 MiB returns
  * RHEO_EINVAL before any device call (the five workload shapes of the
  * sparse and dense modes fit; supports of 512 and more at large batches do
  * not).  There is one static tree per device (the current device): every

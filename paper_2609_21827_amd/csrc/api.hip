@@ -218,11 +218,13 @@ struct Arena {
     rheo_tree* t;
     char* base = nullptr;        // REGION: start of the region
     size_t cap = 0, used = 0;    // REGION / MEASURE: bytes
+    size_t limited = 0;          // MEASURE: bytes under the documented limit (see kStateBytes)
     int rc = RHEO_OK;
 };
 
+// `copy`: a second copy or an exchange buffer, outside the documented limit
 template <typename T>
-void take(Arena& A, T** p, size_t count) {
+void take(Arena& A, T** p, size_t count, bool copy = false) {
     if (A.rc) return;
     const size_t bytes = count * sizeof(T) ? count * sizeof(T) : 16;
     if (A.mode == Arena::HEAP) {
@@ -231,6 +233,7 @@ void take(Arena& A, T** p, size_t count) {
     }
     const size_t off = (A.used + 255) & ~(size_t)255;
     A.used = off + bytes;
+    if (!copy) A.limited = ((A.limited + 255) & ~(size_t)255) + bytes;
     if (A.mode == Arena::MEASURE) return;
     if (A.used > A.cap) {
         A.rc = fail(RHEO_EINVAL, "internal: static region overrun");
@@ -245,7 +248,7 @@ void layout(rheo_tree* t, Arena& A) {
     const bool dense = d.dense != 0;
     const size_t B = d.B, NN = d.NN, E = d.E;
     take(A, &d.node, B * NN);
-    take(A, &d.score, B * NN);
+    take(A, &d.score, B * NN, true);
     const size_t TS = dense ? 1 : (size_t)d.S;              // dense mode keeps no tail copy
     take(A, &d.tail_id, B * E * TS);
     take(A, &d.tail_q, B * E * TS);
@@ -260,10 +263,9 @@ void layout(rheo_tree* t, Arena& A) {
     take(A, &d.frontier, B * d.NE);
     take(A, &d.fr_parent, B * d.NE);
     take(A, &d.fr_token, B * d.NE);
-    take(A, &d.porder, B * NN);
-    take(A, &d.pr_par, B * NN);
-    take(A, &d.pr_tok, B * NN);
-    take(A, &d.pr_depth, B * NN);
+    take(A, &d.pr_par, B * NN, true);
+    take(A, &d.pr_tok, B * NN, true);
+    take(A, &d.pr_depth, B * NN, true);
     take(A, &d.err, 1);
     take(A, &d.team_ticket, B);
     take(A, &d.team_flag, B * 64);
@@ -274,8 +276,8 @@ void layout(rheo_tree* t, Arena& A) {
     take(A, &d.team_nchunk, dense ? B * 1024 * 2 : 1);
     take(A, &d.sel, B * d.NE * (size_t)d.C * d.Sc);
     take(A, &d.seq_cnt, B);
-    take(A, &d.fr_words, B * 3 * (size_t)d.NE * d.K);
-    take(A, &d.fr_mark, B);
+    take(A, &d.fr_words, B * 3 * (size_t)d.NE * d.K, true);
+    take(A, &d.fr_mark, B, true);
 }
 
 // Clears what the kernels expect zeroed (or -1) before a tree's first step
@@ -295,7 +297,6 @@ int init_state(rheo_tree* t) {
     if (e == hipSuccess) e = hipMemset(d.fr_mark, 0, B * sizeof(uint64_t));
     if (e == hipSuccess && dense) e = hipMemset(d.dflag, 0, B * d.NE * sizeof(int32_t));
     if (e == hipSuccess) e = hipMemset(d.node, 0xFF, B * NN * sizeof(Node));
-    if (e == hipSuccess) e = hipMemset(d.porder, 0, B * NN * sizeof(int32_t));
     if (e == hipSuccess) e = hipMemset(d.frontier, 0, B * d.NE * sizeof(int32_t));
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) return hip_fail(e, "initialising tree state");
@@ -316,7 +317,12 @@ int init_state(rheo_tree* t) {
 // device address comes from hipGetSymbolAddress, taken once per device with
 // that device current.
 // ---------------------------------------------------------------------------
-constexpr size_t kScratchBytes = (size_t)32 << 20;
+// A tree is refused by the bytes of its state proper (64 a node, the tails, the
+// selection and team scratch); the copies beside it (20 bytes a node for the
+// prune and the views, 24 a child of a level for the frontier) add at most a
+// third to any shape, which the array holds too.
+constexpr size_t kStateBytes = (size_t)32 << 20;
+constexpr size_t kScratchBytes = (size_t)44 << 20;
 constexpr int kMaxDevices = 64;
 
 }  // namespace
@@ -376,9 +382,9 @@ int rheo_create_static(const rheo_config* cfg, rheo_tree** out) {
     if (rc) return rc;
     Arena M{Arena::MEASURE, &stage};
     layout(&stage, M);
-    if (M.used > kScratchBytes)
+    if (M.limited > kStateBytes || M.used > kScratchBytes)
         return fail(RHEO_EINVAL, "tree needs %zu bytes of device state; the static scratch "
-                    "holds %zu", M.used, (size_t)kScratchBytes);
+                    "holds %zu", M.limited, (size_t)kStateBytes);
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return hip_fail(e, "hipGetDevice");

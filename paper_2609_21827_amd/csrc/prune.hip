@@ -66,7 +66,6 @@ __global__ __launch_bounds__(NTR) void k_prune(TreeDev t, int R) {
     }
     if (tid == 0) {
         t.node[nb].pidx = 0;
-        t.porder[nb] = 0;
         t.pr_par[nb] = -1;
         t.pr_tok[nb] = -1;
         t.pr_depth[nb] = 0;
@@ -119,7 +118,6 @@ __global__ __launch_bounds__(NTR) void k_prune(TreeDev t, int R) {
         const int pk = p == 0 ? 0 : (p > 0 && p <= n) ? s_rank[p - 1] : -1;
         // a parent outranks its child (raises the sticky error flag if not)
         if (pk < 0 || pk >= k) atomicOr(t.err, 2);
-        t.porder[nb + k] = 1 + i;
         t.pr_par[nb + k] = pk < 0 ? 0 : pk;
         t.pr_tok[nb + k] = nd.tok;
         t.pr_depth[nb + k] = nd.meta & 0xFF;

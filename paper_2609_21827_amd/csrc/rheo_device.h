@@ -227,29 +227,6 @@ __device__ uint64_t block_sum_u64(uint64_t v, uint64_t* sh) {
     return r;
 }
 
-// Two block sums in one exchange; sh holds 2 * NT / WAVE words.
-template <int NT>
-__device__ void block_sum2_u64(uint64_t a, uint64_t b, uint64_t* sh, uint64_t* ra, uint64_t* rb) {
-    constexpr int NW = NT / WAVE;
-    a = wave_sum_u64(a);
-    b = wave_sum_u64(b);
-    const int w = threadIdx.x / WAVE, l = threadIdx.x % WAVE;
-    __syncthreads();
-    if (l == 0) {
-        sh[w] = a;
-        sh[NW + w] = b;
-    }
-    __syncthreads();
-    uint64_t x = 0, y = 0;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        x += sh[i];
-        y += sh[NW + i];
-    }
-    *ra = x;
-    *rb = y;
-}
-
 template <int NT>
 __device__ int block_sum_i32(int v, int* sh) {
     v = wave_sum_i32(v);
@@ -315,21 +292,6 @@ __device__ uint64_t block_excl_scan_u64(uint64_t v, uint64_t* sh, uint64_t* tota
     return base + inc - v;
 }
 
-// Descending bitonic sort of one float per lane across a wave.
-__device__ __forceinline__ float wave_sort_desc(float v) {
-    const int lane = threadIdx.x % WAVE;
-#pragma unroll
-    for (int k = 2; k <= WAVE; k <<= 1) {
-#pragma unroll
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            const float o = __shfl_xor(v, j);
-            const bool take_max = ((lane & j) == 0) == ((lane & k) == 0);
-            v = take_max ? fmaxf(v, o) : fminf(v, o);
-        }
-    }
-    return v;
-}
-
 // rank[i] = number of keys strictly greater than keys[i], for unique keys
 // in LDS; each key is compared by a group of F consecutive lanes.  With
 // `out`, the lane that finishes key i writes it to out[rank] instead when
@@ -377,34 +339,6 @@ __device__ void rank_keys(const uint64_t* keys, int n, int16_t* rank, uint64_t* 
             }
         }
     }
-}
-
-// rank[i] = number of 128-bit keys strictly greater than key i (unique keys
-// in LDS as {hi, lo} pairs).  One key per lane; every lane of a wave reads
-// the same key at the same time (LDS broadcast).
-template <int NT>
-__device__ void rank_keys128(const ulonglong2* keys, int n, int16_t* rank) {
-    for (int base = 0; base < n; base += NT) {
-        const int i = base + threadIdx.x;
-        const ulonglong2 k = keys[i < n ? i : 0];
-        int cnt = 0;
-#pragma unroll 8
-        for (int j = 0; j < n; ++j) {
-            const ulonglong2 x = keys[j];
-            cnt += (int)(x.x > k.x) | ((int)(x.x == k.x) & (int)(x.y > k.y));
-        }
-        if (i < n) rank[i] = (int16_t)cnt;
-    }
-}
-
-// Hides register-resident 16-byte vectors from the optimiser between
-// passes, so each pass unpacks bf16 pairs on the fly instead of keeping
-// every element unpacked across the whole kernel.
-template <int NV>
-__device__ __forceinline__ void opaque_regs(uint4 (&r)[NV]) {
-#pragma unroll
-    for (int i = 0; i < NV; ++i)
-        asm volatile("" : "+v"(r[i].x), "+v"(r[i].y), "+v"(r[i].z), "+v"(r[i].w));
 }
 
 }  // namespace rheo

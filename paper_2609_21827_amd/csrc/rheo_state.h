@@ -45,9 +45,8 @@ struct TreeDev {
     int32_t* frontier;
     int32_t* fr_parent;
     int32_t* fr_token;
-    // pruned tree
-    int32_t* porder;               // [B][NN]: uid of each pruned index
-    int32_t* pr_par;               // [B][NN]: its parent's pruned index, token, depth
+    // pruned tree, [B][NN]: each pruned index's parent (pruned), token, depth
+    int32_t* pr_par;
     int32_t* pr_tok;
     int32_t* pr_depth;
     int32_t* err;                  // sticky device error flag

@@ -151,18 +151,6 @@ __device__ u128 block_excl_scan_u128(u128 v, u128* sh, u128* total) {
     *total = tot;
     return base + inc - v;
 }
-__device__ u128 block_sum_u128(u128 v, u128* sh) {
-    const int l = threadIdx.x % WAVE, w = threadIdx.x / WAVE;
-    v = wave_sum_u128(v);
-    __syncthreads();
-    if (l == 0) sh[w] = v;
-    __syncthreads();
-    u128 tot = 0;
-#pragma unroll
-    for (int i = 0; i < NWV; ++i) tot += sh[i];
-    return tot;
-}
-
 // Team barrier: publish this block's arrival at `epoch`, then wait until
 // every team member has arrived.  Prior team-visible stores must be agent
 // atomic stores; each thread waits for its own before the block barrier.
