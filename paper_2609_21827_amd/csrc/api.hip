@@ -104,6 +104,18 @@ int check_T(float T) {
     return RHEO_OK;
 }
 
+// Dense bf16 levels run one block per row (k_dense_row) but for two kinds that
+// the chunked kernels run faster: a few long rows, which share a row over many
+// blocks (whole steps, by rows against chunked: 7 rows of 130670 211 and 192
+// us, 32 of 128133 383 and 341, 48 of 250708 510 and 498; 9 of 34571 116 and
+// 134), and many short rows, whose own elements are fewer than the values the
+// counts have to be weighted for (520 rows of 12902 442 and 380 us, 1200 of
+// 18349 372 and 348, 55 of 11720 186 and 188).
+bool dense_by_rows(const TreeDev& d, int P) {
+    const int rows = d.B * P;
+    return d.V <= 65536 ? rows < 256 || d.V >= 24576 : rows >= 64;
+}
+
 // Every call of one step takes the step's temperature and key: the stored
 // tail weights (and, in dense mode, the q~ verification recomputes from the
 // draft rows) and the draws of the sampled slots depend on both.
@@ -444,7 +456,7 @@ int rheo_expand_level(rheo_tree* t, const void* logits, float T, uint64_t key, v
     a.rng_key = key;
     a.fr_key = key;                       // the key of the call that chose the parents
     hipError_t e = hipSuccess;
-    if (t->dev.dense && t->row_mode != 0) {
+    if (t->dev.dense && (t->row_mode == 1 || (t->row_mode < 0 && dense_by_rows(t->dev, a.P)))) {
         e = launch_dense_row(t->dev, a, (hipStream_t)stream);
     } else if (t->dev.dense) {
         e = launch_select(t->dev, a, t->variant, (hipStream_t)stream);

@@ -243,9 +243,11 @@ __device__ void exact_select_fallback(const char* base, int V, int vfirst, uint3
     constexpr int NW = NT / WAVE;
     static_assert(NQ % 4 == 0 && NQ <= 64, "re-read in groups of four vectors");
     const int tid = threadIdx.x, lane = tid % WAVE, wid = tid / WAVE;
-    // an opaque trip count keeps each pass a loop (re-reading per pass)
-    // rather than one straight-line block holding every element
-    int nq = NQ;
+    // the vectors of the range inside the row, in groups of four; the opaque trip
+    // count keeps each pass a loop (re-reading per pass) rather than one
+    // straight-line block holding every element
+    int nq = __builtin_amdgcn_readfirstlane(
+        min(NQ, (((V + VEC - 1) / VEC - vfirst + NT - 1) / NT + 3) & ~3));
     asm volatile("" : "+s"(nq));
     auto group = [&](int q0, uint4 (&w)[4]) {
         // an opaque index keeps every pass's loads (and what is computed
