@@ -303,6 +303,9 @@ int init_state(rheo_tree* t) {
     if (e == hipSuccess) e = hipMemset(d.team_flag, 0, B * 64 * sizeof(uint64_t));
     if (e == hipSuccess) e = hipMemset(d.team_max, 0, B * 64 * sizeof(uint64_t));
     if (e == hipSuccess) e = hipMemset(d.team_sum, 0, B * 64 * sizeof(uint64_t));
+    // (every tree starts at the same epochs, so totals that an earlier tree left
+    // in this memory would pass for this one's; tag 0 is no epoch's)
+    if (e == hipSuccess) e = hipMemset(d.team_chunk, 0, B * 1024 * sizeof(uint64_t));
     if (e == hipSuccess) e = hipMemset(d.seq_cnt, 0, B * sizeof(uint32_t));
     // the first launch's mark is a clear top bit: no word carries it
     if (e == hipSuccess) e = hipMemset(d.fr_words, 0xFF, B * 3 * d.NE * d.K * sizeof(uint64_t));

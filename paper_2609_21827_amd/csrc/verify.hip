@@ -205,8 +205,9 @@ __device__ bool team_max_exchange(uint64_t* words, int g, int G, uint64_t epoch,
 // is at most 2^39.  A block whose weights were taken relative to a guessed
 // maximum that its segment exceeds publishes 2^48 - 1 instead (no sum
 // reaches it), and *s_miss tells every block of the team.  A word left from
-// an earlier barrier is fewer than 2^16 epochs old, so the 16-bit
-// comparison cannot mistake it for the current one.  wsum holds the block's
+// an earlier barrier is fewer than 2^16 epochs old (a new tree's words are
+// cleared: 0 is no epoch's tag), so the 16-bit comparison cannot mistake it
+// for the current one.  wsum holds the block's
 // per-wave sums, kMiss for a wave that saw the guess exceeded.  Bounded like
 // team_barrier.
 constexpr uint64_t kMiss = (1ull << 48) - 1;

@@ -54,3 +54,25 @@ def test_static_tree_matches_allocated_tree(dev):
                 assert np.array_equal(n1[k], n2[k]), (w.name, k)
             for x, y in zip(p1, p2):
                 assert np.array_equal(x, y), w.name
+
+
+@pytest.mark.parametrize("static", [True, False])
+def test_recreated_tree_starts_clean(dev, static):
+    """The first step of a tree whose memory an earlier tree of the same shape
+    used: every tree numbers its exchanges alike, so a word left there would
+    pass for its own (a chunk total not yet overwritten gave the final sample
+    of another target row)."""
+    from paper_2609_21827_amd.driver import make_tree, replay_step, run_step
+    w = W["headline"].with_(name="again", B=16, depth=2, R=12)
+    rec, ref = [{}, {}], []
+    tree = make_tree(w, device=dev)
+    for s in (0, 1):
+        ref.append(run_step(tree, w, s, device=dev, record=rec[s]))
+    torch.cuda.synchronize()
+    tree.close()
+    for i in range(8):
+        tree = make_tree(w, device=dev, static=static)
+        out = [x.cpu() for x in replay_step(tree, rec[i % 2], w.R)]
+        assert tree.device_error() == 0
+        tree.close()
+        assert all(torch.equal(o, r) for o, r in zip(out, ref[i % 2])), i
