@@ -12,6 +12,7 @@
 
 #include "rheo.h"
 #include "rheo_state.h"
+#include "team_words.h"
 
 using namespace rheo;
 
@@ -234,9 +235,11 @@ struct Arena {
     int rc = RHEO_OK;
 };
 
-// `copy`: a second copy or an exchange buffer, outside the documented limit
+// `counted`: elements under the documented limit (a second copy or an exchange
+// buffer is outside it)
+constexpr size_t kAll = ~(size_t)0;
 template <typename T>
-void take(Arena& A, T** p, size_t count, bool copy = false) {
+void take(Arena& A, T** p, size_t count, size_t counted = kAll) {
     if (A.rc) return;
     const size_t bytes = count * sizeof(T) ? count * sizeof(T) : 16;
     if (A.mode == Arena::HEAP) {
@@ -245,7 +248,8 @@ void take(Arena& A, T** p, size_t count, bool copy = false) {
     }
     const size_t off = (A.used + 255) & ~(size_t)255;
     A.used = off + bytes;
-    if (!copy) A.limited = ((A.limited + 255) & ~(size_t)255) + bytes;
+    if (counted)
+        A.limited = ((A.limited + 255) & ~(size_t)255) + (counted == kAll ? bytes : counted * sizeof(T));
     if (A.mode == Arena::MEASURE) return;
     if (A.used > A.cap) {
         A.rc = fail(RHEO_EINVAL, "internal: static region overrun");
@@ -260,7 +264,7 @@ void layout(rheo_tree* t, Arena& A) {
     const bool dense = d.dense != 0;
     const size_t B = d.B, NN = d.NN, E = d.E;
     take(A, &d.node, B * NN);
-    take(A, &d.score, B * NN, true);
+    take(A, &d.score, B * NN, 0);
     const size_t TS = dense ? 1 : (size_t)d.S;              // dense mode keeps no tail copy
     take(A, &d.tail_id, B * E * TS);
     take(A, &d.tail_q, B * E * TS);
@@ -275,21 +279,21 @@ void layout(rheo_tree* t, Arena& A) {
     take(A, &d.frontier, B * d.NE);
     take(A, &d.fr_parent, B * d.NE);
     take(A, &d.fr_token, B * d.NE);
-    take(A, &d.pr_par, B * NN, true);
-    take(A, &d.pr_tok, B * NN, true);
-    take(A, &d.pr_depth, B * NN, true);
+    take(A, &d.pr_par, B * NN, 0);
+    take(A, &d.pr_tok, B * NN, 0);
+    take(A, &d.pr_depth, B * NN, 0);
     take(A, &d.err, 1);
     take(A, &d.team_ticket, B);
     take(A, &d.team_flag, B * 64);
     take(A, &d.team_max, B * 64);
-    take(A, &d.team_sum, B * 64);
+    take(A, &d.team_sum, B * kTeamSets * 64, B * 64);
     take(A, &d.team_chunk, B * 1024);
     take(A, &d.team_sp, B * (1024 + 16));
     take(A, &d.team_nchunk, dense ? B * 1024 * 2 : 1);
     take(A, &d.sel, B * d.NE * (size_t)d.C * d.Sc);
     take(A, &d.seq_cnt, B);
-    take(A, &d.fr_words, B * 3 * (size_t)d.NE * d.K, true);
-    take(A, &d.fr_mark, B, true);
+    take(A, &d.fr_words, B * 3 * (size_t)d.NE * d.K, 0);
+    take(A, &d.fr_mark, B, 0);
 }
 
 // Clears what the kernels expect zeroed (or -1) before a tree's first step
@@ -302,7 +306,7 @@ int init_state(rheo_tree* t) {
     if (e == hipSuccess) e = hipMemset(d.team_ticket, 0, B * sizeof(uint64_t));
     if (e == hipSuccess) e = hipMemset(d.team_flag, 0, B * 64 * sizeof(uint64_t));
     if (e == hipSuccess) e = hipMemset(d.team_max, 0, B * 64 * sizeof(uint64_t));
-    if (e == hipSuccess) e = hipMemset(d.team_sum, 0, B * 64 * sizeof(uint64_t));
+    if (e == hipSuccess) e = hipMemset(d.team_sum, 0, B * kTeamSets * 64 * sizeof(uint64_t));
     // (every tree starts at the same epochs, so totals that an earlier tree left
     // in this memory would pass for this one's; tag 0 is no epoch's)
     if (e == hipSuccess) e = hipMemset(d.team_chunk, 0, B * 1024 * sizeof(uint64_t));

@@ -50,6 +50,7 @@
 
 #include "rheo_device.h"
 #include "rheo_state.h"
+#include "team_words.h"
 
 namespace rheo {
 
@@ -204,10 +205,13 @@ __device__ bool team_max_exchange(uint64_t* words, int g, int G, uint64_t epoch,
 // reductions overlap the wait) and carry the epoch themselves: a chunk's sum
 // is at most 2^39.  A block whose weights were taken relative to a guessed
 // maximum that its segment exceeds publishes 2^48 - 1 instead (no sum
-// reaches it), and *s_miss tells every block of the team.  A word left from
-// an earlier barrier is fewer than 2^16 epochs old (a new tree's words are
-// cleared: 0 is no epoch's tag), so the 16-bit comparison cannot mistake it
-// for the current one.  wsum holds the block's
+// reaches it), and *s_miss tells every block of the team.  Consecutive layers
+// use two sets of words (team_words.h).  A word left from an earlier
+// exchange is fewer than 2^16 epochs old (a new tree's words are cleared: 0 is
+// no epoch's tag), so the 16-bit comparison cannot mistake it for the current
+// one.  A layer's second exchange (after a guess that was exceeded) uses the
+// same set: the maximum exchange between the two orders them, as it orders
+// the maxima of different layers.  wsum holds the block's
 // per-wave sums, kMiss for a wave that saw the guess exceeded.  Bounded like
 // team_barrier.
 constexpr uint64_t kMiss = (1ull << 48) - 1;
@@ -223,14 +227,14 @@ __device__ __forceinline__ void team_sum_publish(uint64_t* words, int g, uint64_
             miss |= wsum[w] == kMiss;
             sum += wsum[w];
         }
-        __hip_atomic_store(&words[g], ((epoch & 0xFFFFull) << 48) | (miss ? kMiss : sum & M48),
+        __hip_atomic_store(&words[g], (team_tag(epoch) << 48) | (miss ? kMiss : sum & M48),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 __device__ bool team_sum_wait(uint64_t* words, int G, uint64_t epoch, long spin_limit,
                               int32_t* err, int* s_ok, uint64_t* s_total, int* s_miss) {
     constexpr uint64_t M48 = (1ull << 48) - 1;
-    const uint64_t e16 = epoch & 0xFFFFull;
+    const uint64_t e16 = team_tag(epoch);
     if (threadIdx.x < WAVE) {
         if (threadIdx.x == 0) *s_ok = 1;
         uint64_t v = 0;
@@ -367,7 +371,6 @@ __global__ __launch_bounds__(NTV, 4) void k_verify(VerifyParams) {
                                         __HIP_MEMORY_SCOPE_AGENT);
     uint64_t* tmax_x = t.team_max + (int64_t)b * GMAX;
     uint64_t* chunk_x = t.team_chunk + (int64_t)b * NCMAX;
-    uint64_t* tsum_x = t.team_sum + (int64_t)b * GMAX;
     uint64_t* nchunk_x = t.team_nchunk + (int64_t)b * NCMAX * 2;   // dense residual totals
     auto nchunk_at = [&](int c) -> u128 {
         const uint64_t lo = __hip_atomic_load(&nchunk_x[2 * c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -386,7 +389,7 @@ __global__ __launch_bounds__(NTV, 4) void k_verify(VerifyParams) {
         s_e = t.node[nb].exp_of;
         // barrier epochs of this launch: a window of 64 above the previous
         // launch's (a walk uses 3 per layer, at most 48)
-        s_epoch = 64 * (ticket / (uint64_t)G + 1);
+        s_epoch = team_first_epoch(ticket / (uint64_t)G);
     }
     __syncthreads();
     const uint64_t epoch = s_epoch;
@@ -503,7 +506,7 @@ __global__ __launch_bounds__(NTV, 4) void k_verify(VerifyParams) {
         // a finite Mw, so no element needs a bounds test (which would
         // branch per element and serialise the weights).
         auto seg_weights = [&](float Mw, bool* over, uint64_t ep) -> uint64_t {
-            const uint64_t tag = (ep & 0xFFFFull) << 48;
+            const uint64_t tag = team_tag(ep) << 48;
             uint64_t wpart = 0;
             bool ov = false;
 #pragma unroll
@@ -550,6 +553,7 @@ __global__ __launch_bounds__(NTV, 4) void k_verify(VerifyParams) {
         };
         float M;
         uint64_t cepoch = 0;                 // the epoch of this layer's chunk totals
+        uint64_t* const tsum_x = t.team_sum + ((int64_t)b * kTeamSets + team_set(epoch, level)) * GMAX;
         {
             // ---- 1. the row maximum is guessed as the largest target logit
             //         at the special tokens and the pruned children (all of
@@ -831,8 +835,8 @@ __global__ __launch_bounds__(NTV, 4) void k_verify(VerifyParams) {
                 long spins = 0;
                 do {
                     w = __hip_atomic_load(&chunk_x[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                } while ((w >> 48) != (cepoch & 0xFFFFull) && ++spins <= a.spin);
-                late |= (w >> 48) != (cepoch & 0xFFFFull);
+                } while ((w >> 48) != team_tag(cepoch) && ++spins <= a.spin);
+                late |= (w >> 48) != team_tag(cepoch);
                 s_chunk[c] = w & ((1ull << 48) - 1);
                 s_dlo[c] = 0;
                 s_dhi[c] = 0;

@@ -110,3 +110,22 @@ def test_static_tree_size_limit_on_host():
     h = ctypes.c_void_p()
     assert lib.rheo_create_static(ctypes.byref(cfg), ctypes.byref(h)) == binding.RHEO_EINVAL
     assert "static scratch" in lib.rheo_last_error().decode()
+
+
+@needs_lib
+@pytest.mark.parametrize("kw,nbytes", [
+    (dict(batch=128, vocab=128256, row_stride=128256, pool=10, depth=8, support=1024), 103114240),
+    (dict(batch=3000, vocab=1000, support=0, depth=1), 93121248),
+    (dict(batch=1500, vocab=5001, row_stride=5008, dtype=0, support=64), 34568304),
+    (dict(batch=300, vocab=262143, row_stride=262144, support=256, pool=12, leads=0, depth=6,
+          n_expand=5, construct_full=1), 50824880),
+])
+def test_static_tree_limit_counts(kw, nbytes):
+    """The bytes the limit counts for a shape: what is refused stays refused and
+    what is accepted stays accepted when the device state is laid out anew."""
+    from paper_2609_21827_amd import binding
+    lib = binding.load_library()
+    h = ctypes.c_void_p()
+    cfg = _cfg(**kw)
+    assert lib.rheo_create_static(ctypes.byref(cfg), ctypes.byref(h)) == binding.RHEO_EINVAL
+    assert f"needs {nbytes} bytes" in lib.rheo_last_error().decode()
