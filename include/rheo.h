@@ -200,7 +200,8 @@ int rheo_frontier_view(const rheo_tree* tree, const int32_t** parent_index,
 int rheo_prune(rheo_tree* tree, int32_t budget, void* stream);
 
 /* The pruned tree in rank order, index 0 = root:
- *   parent  [B][R+1] int32 (pruned index of the parent, -1 for the root)
+ *   parent  [B][R+1] int32 (pruned index of the parent, -1 for the root and
+ *           where device error bit 1 reports a kept node's parent as pruned)
  *   token   [B][R+1] int32 (-1 for the root)
  * Row i of the target buffer given to rheo_verify must hold the target
  * model's logits at pruned node i. */

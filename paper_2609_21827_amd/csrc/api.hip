@@ -317,6 +317,9 @@ int init_state(rheo_tree* t) {
     if (e == hipSuccess && dense) e = hipMemset(d.dflag, 0, B * d.NE * sizeof(int32_t));
     if (e == hipSuccess) e = hipMemset(d.node, 0xFF, B * NN * sizeof(Node));
     if (e == hipSuccess) e = hipMemset(d.frontier, 0, B * d.NE * sizeof(int32_t));
+    if (e == hipSuccess) e = hipMemset(d.pr_par, 0xFF, B * NN * sizeof(int32_t));
+    if (e == hipSuccess) e = hipMemset(d.pr_tok, 0xFF, B * NN * sizeof(int32_t));
+    if (e == hipSuccess) e = hipMemset(d.pr_depth, 0, B * NN * sizeof(int32_t));
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) return hip_fail(e, "initialising tree state");
     e = verify_shape(d, &t->vG, &t->v_segch, &t->v_grid);

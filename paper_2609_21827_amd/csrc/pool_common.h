@@ -109,8 +109,8 @@ __device__ __forceinline__ ParentRec parent_rec(const TreeDev& t, const LevelArg
 
 // Children words: the fields of a level's new children that the frontier
 // selection reads in another block, [B][3][NE * K]: score, slot path, token,
-// each with the launch's mark in its top bit (a score is at most 1, a path
-// below 2^60).  The mark flips with every launch that uses the words (the
+// each with the launch's mark in its top bit (a path is below 2^60, and a
+// score's sign says nothing: it is clear, or a NaN's).  The mark flips with every launch that uses the words (the
 // sequence's last row flips it once all rows have arrived), so a word that
 // carries it is this launch's.  Agent-scope stores and loads.
 constexpr uint64_t kMark = 1ull << 63;
@@ -133,7 +133,8 @@ __device__ __forceinline__ void emit_child(const TreeDev& t, const LevelArgs& a,
     if (level > 0 && level + 1 < t.D) {
         const int n = t.NE * K;
         uint64_t* w = child_words(t, b) + j * K + s;
-        __hip_atomic_store(&w[0], score | pr.mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&w[0], (score & ~kMark) | pr.mark, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&w[n], path | pr.mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&w[2 * n], (uint64_t)(uint32_t)tok | pr.mark, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
@@ -245,8 +246,8 @@ __device__ __forceinline__ void select_frontier(const TreeDev& t, const LevelArg
     }
     __syncthreads();
     // F adjacent lanes a child (a power of two, at most 8), each over every
-    // F-th key.  Scores first, as the non-negative doubles they are (one
-    // full-rate compare); the rest of the key only where two are equal, which
+    // F-th key.  Scores first, as the doubles they are (non-negative, not NaN:
+    // prio_key; one full-rate compare); the rest of the key only where two are equal, which
     // is rare.
     int F = 1;
     while (F < 8 && 2 * F * n <= NT) F *= 2;

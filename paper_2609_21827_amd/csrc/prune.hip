@@ -22,8 +22,8 @@ namespace rheo {
 constexpr int NTR = 512;
 constexpr int PBINS = 512;                   // one bin per thread
 
-// The bin of a score in [0, 1]: its exponent and three mantissa bits, from 511
-// (score 1) down to 2^-63 and below (0).
+// The bin of a score in [0, 1] or infinite (score_order): its exponent and three mantissa bits, from 511
+// (1 and above) down to 2^-63 and below (0).
 __device__ __forceinline__ int score_bin(double s) {
     const int k = (int)((uint64_t)__double_as_longlong(s) >> 49);
     return min(max(k - ((0x3FF << 3) - (PBINS - 1)), 0), PBINS - 1);
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(NTR) void k_prune(TreeDev t, int R) {
     s_hist[tid] = 0;
     __syncthreads();
     for (int i = tid; i < n; i += NTR) {
-        const double sc = t.score[nb + 1 + i];
+        const double sc = score_order(t.score[nb + 1 + i]);
         const int bin = score_bin(sc);
         s_score[i] = sc;
         s_bs[i] = bin | (atomicAdd(&s_hist[bin], 1) << 16);
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(NTR) void k_prune(TreeDev t, int R) {
         const int pk = p == 0 ? 0 : (p > 0 && p <= n) ? s_rank[p - 1] : -1;
         // a parent outranks its child (raises the sticky error flag if not)
         if (pk < 0 || pk >= k) atomicOr(t.err, 2);
-        t.pr_par[nb + k] = pk < 0 ? 0 : pk;
+        t.pr_par[nb + k] = pk;
         t.pr_tok[nb + k] = nd.tok;
         t.pr_depth[nb + k] = nd.meta & 0xFF;
     }

@@ -105,12 +105,21 @@ __device__ __forceinline__ uint64_t logit_key(float v, uint32_t id) {
 __device__ __forceinline__ float key_value(uint64_t k) { return unord32((uint32_t)(k >> 32)); }
 __device__ __forceinline__ int key_id(uint64_t k) { return (int)(0xFFFFFFFFu - (uint32_t)k); }
 
+// A path score as it is ordered: below a row without a finite logit, where the
+// proxies are 0/0 and the error flag is set, the scores are NaN; they rank
+// above every number (as the bits of a NaN do) and tie with each other, so the
+// order is total and every rank is taken whatever the rows hold.
+__device__ __forceinline__ double score_order(double score) {
+    return score == score ? score : __longlong_as_double(0x7FF0000000000000ll);
+}
+
 // Priority of a tree node (App. C.1): score descending, depth ascending,
 // slot path ascending -- as a 128-bit key where larger = better.  Scores
-// are non-negative, so their IEEE bits are already order-preserving.
+// are non-negative, so their IEEE bits are already order-preserving, and never
+// NaN here, so the upper half may be compared as a double.
 __device__ __forceinline__ void prio_key(double score, int depth, uint64_t path,
                                          uint64_t& hi, uint64_t& lo) {
-    hi = (uint64_t)__double_as_longlong(score);
+    hi = (uint64_t)__double_as_longlong(score_order(score));
     lo = ((uint64_t)(15 - depth) << 60) | (0x0FFFFFFFFFFFFFFFull - path);
 }
 

@@ -35,7 +35,8 @@ __global__ void k_pruned_view(TreeDev t, int R, int32_t* parent, int32_t* token)
 
 // The mask and the depths of one sequence, MSPLIT blocks each: the parents'
 // pruned indices in LDS, one ancestor walk (at most depth <= 15 steps, to
-// ever smaller indices) per entry.
+// ever smaller indices; where the error flag says that a parent was pruned,
+// to -1 or not at all) per entry.
 constexpr int NTM = 256;
 constexpr int MSPLIT = 4;
 
@@ -46,7 +47,7 @@ __global__ __launch_bounds__(NTM) void k_tree_mask(TreeDev t, int R, uint8_t* ma
     const int b = blockIdx.x / MSPLIT, part = blockIdx.x % MSPLIT;
     const int64_t nb = (int64_t)b * t.NN;
     for (int i = threadIdx.x; i < n; i += NTM) {
-        s_par[i] = t.pr_par[nb + i];
+        s_par[i] = min(max(t.pr_par[nb + i], -1), R);
         if (depth && part == 0) depth[(int64_t)b * n + i] = t.pr_depth[nb + i];
     }
     __syncthreads();

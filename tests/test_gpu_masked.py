@@ -119,3 +119,85 @@ def test_undefined_rows_set_error_bit(dev):
         if b != 5:
             assert all(torch.equal(o[b], r[b]) for o, r in zip(out, ref)), b
     tree.close()
+
+
+@pytest.mark.parametrize("over,env", [
+    (dict(V=1003, dtype="bf16", support=128), None),
+    (dict(V=1003, dtype="bf16", support=128), {"RHEO_EXPAND_ROW": "0"}),
+    (dict(V=4099, dtype="f32", support=300, m=0), None),
+    (dict(V=4099, dtype="bf16", support=64, construct_full=True), None),
+    (dict(V=1003, dtype="bf16", support=0), {"RHEO_EXPAND_ROW": "1"}),
+    (dict(V=1003, dtype="bf16", support=0, m=2), {"RHEO_EXPAND_ROW": "0"}),
+    (dict(V=1001, dtype="f32", support=0), None),
+])
+def test_fully_masked_draft_rows(dev, over, env):
+    """Draft rows without a finite logit, at the root, at one node of level 1
+    and at every node of level 2: reported by error bit 9, the tree whole all
+    the same (scores that are NaN rank above the others and tie: every
+    frontier entry and pruned index is taken), the other sequences unaffected."""
+    import os
+    from paper_2609_21827_amd.driver import make_tree, run_step
+    w = W["tiny"].with_(name="undef_rows", recipe="zipf", K=5, n_expand=5, depth=4, R=30, B=8,
+                        sigma=1.5, sigma_t=0.8, **over)
+    K, NE, B, D = w.K, w.n_expand, w.B, w.depth
+    os.environ.update(env or {})
+    try:
+        tree = make_tree(w, device=dev, row_stride=(w.V + 7) // 8 * 8)
+    finally:
+        for k in env or {}:
+            del os.environ[k]
+    rec = {}
+
+    def step(drafts):
+        tree.begin_step()
+        front = []
+        for rows in drafts:
+            tree.expand_level(rows, rec["T"], rec["rng_key"])
+            front.append([x.cpu().numpy() for x in tree.frontier_view()])
+        nodes = {k: v.cpu().numpy() for k, v in tree.read_nodes().items()}
+        tree.prune(w.R)
+        views = [x.cpu().numpy() for x in (*tree.pruned_view(), *tree.tree_mask())]
+        out = [x.cpu().numpy() for x in tree.verify(rec["target"], rec["T"], rec["rng_key"])]
+        return front, nodes, views, out
+
+    run_step(tree, w, 0, device=dev, record=rec)
+    ref = step(rec["draft"])
+    assert tree.device_error() == 0
+    drafts = [d.clone() for d in rec["draft"]]
+    drafts[0][1] = float("-inf")
+    drafts[1][4, 2] = float("-inf")
+    drafts[2][6] = float("-inf")
+    for _ in range(2):                  # both values of the children words' mark
+        front, nodes, views, out = step(drafts)
+    err = tree.device_error()
+    tree.close()
+    assert err & 512 and not err & (16 | 64 | 128 | 256), err
+    for b in (0, 2, 3, 5, 7):
+        for x, y in zip([*nodes.values(), *views, *out], [*ref[1].values(), *ref[2], *ref[3]]):
+            assert np.array_equal(x[b], y[b]), b
+    par, tok, mask, dep = views
+    for b in range(B):
+        n = {k: v[b] for k, v in nodes.items()}
+        score = np.where(np.isnan(n["score"]), np.inf, n["score"])
+        path = [()]
+        for u in range(1, len(score)):
+            path.append(path[n["parent"][u]] + (int(n["slot"][u]),))
+        best = lambda uids: sorted(uids, key=lambda u: (-score[u], n["depth"][u], path[u]))
+        for level in range(D - 1):
+            first = 1 if level == 0 else 1 + K + (level - 1) * NE * K
+            kept = best(range(first, first + (1 if level == 0 else NE) * K))[:NE]
+            assert list(front[level][0][b]) == [(u - first) // K for u in kept], (b, level)
+            assert list(front[level][1][b]) == [n["token"][u] for u in kept], (b, level)
+        kept = [0] + best(range(1, len(score)))[:w.R]
+        place = {u: i for i, u in enumerate(kept)}
+        want = [-1] + [place.get(int(n["parent"][u]), -1) for u in kept[1:]]
+        assert list(par[b]) == want, b
+        assert list(tok[b]) == [-1] + [n["token"][u] for u in kept[1:]], b
+        assert list(dep[b]) == [n["depth"][u] for u in kept], b
+        for i in range(w.R + 1):
+            for j in range(w.R + 1):
+                p = i
+                for _ in range(16):
+                    p = want[p] if p > j else p
+                assert mask[b][i][j] == (p == j), (b, i, j)
+        assert np.all((out[2][b] >= -1) & (out[2][b] < w.V))
