@@ -172,7 +172,7 @@ int configure(const rheo_config* cfg_in, rheo_tree* t) {
     d.eps = c.eps_m0;
     d.NN = 1 + c.pool + (c.depth - 1) * c.n_expand * c.pool;
     d.E = 1 + (c.depth - 1) * c.n_expand;
-    if (16 * (size_t)(d.NN - 1) > 64 * 1024) {
+    if (d.NN - 1 > kMaxNodes) {
         return fail(RHEO_EINVAL, "tree too large (%d nodes per sequence)", d.NN);
     }
     // expand variant: 16 vectors per thread and chunk (dense mode: 8, whose

@@ -860,8 +860,9 @@ static size_t dense_row_shm(const TreeDev& t) {
 // Raises the kernel's limit on dynamic LDS.
 hipError_t prepare_dense(const TreeDev& t) {
     if (!t.dense || !t.dtype) return hipSuccess;
+    if (dense_row_shm(t) > kRowLdsMax) return hipErrorInvalidValue;
     return hipFuncSetAttribute((const void*)&k_dense_row,
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)dense_row_shm(t));
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRowLdsMax);
 }
 
 hipError_t launch_dense_row(const TreeDev& t, const LevelArgs& a, hipStream_t s) {

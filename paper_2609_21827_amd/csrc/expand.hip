@@ -848,8 +848,6 @@ hipError_t launch_row_wsum(const TreeDev& t, const LevelArgs& a, hipStream_t s) 
     return hipGetLastError();
 }
 
-constexpr size_t kRowLdsMax = 156 * 1024;   // dynamic LDS of a block (160 KB less the static)
-
 static size_t row_shm(int dtype, int V, int S, int ntb, bool cfull) {
     const int nvr = (V + (dtype ? 8 : 4) - 1) / (dtype ? 8 : 4);
     const int nb = (nvr + ntb * EBATCH - 1) / (ntb * EBATCH);

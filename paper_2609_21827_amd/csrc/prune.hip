@@ -124,12 +124,11 @@ __global__ __launch_bounds__(NTR) void k_prune(TreeDev t, int R) {
     }
 }
 
-// Raises the kernel's limit on dynamic LDS for trees of many nodes.
-hipError_t prepare_prune(const TreeDev& t) {
-    const int bytes = prune_lds(t.NN - 1).bytes;
-    if (bytes <= 48 * 1024) return hipSuccess;
+// Raises the kernel's limit on dynamic LDS to what the largest tree takes (the
+// limit is the kernel's, not one tree's).
+hipError_t prepare_prune(const TreeDev&) {
     return hipFuncSetAttribute((const void*)&k_prune, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               bytes);
+                               prune_lds(kMaxNodes).bytes);
 }
 
 hipError_t launch_prune(const TreeDev& t, int R, hipStream_t s) {

@@ -6,6 +6,8 @@
 
 namespace rheo {
 
+constexpr int kMaxNodes = 4096;    // non-root nodes of a sequence
+
 // One tree node, 64 bytes: what a child's emission writes in four 16-byte
 // stores and a verification layer reads in two.
 struct alignas(16) Node {

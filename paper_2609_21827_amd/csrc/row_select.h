@@ -392,6 +392,11 @@ __device__ __forceinline__ int fallback_count(int* cnt) {
     return __hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+// Dynamic LDS of a row kernel's block (160 KB less the static): the limit set
+// for each of them, the same whatever tree sets it, since it belongs to the
+// kernel and every tree launches under it.
+constexpr size_t kRowLdsMax = 156 * 1024;
+
 constexpr int NBINS = 512;    // histogram bins of the ranking (LS: twice as many)
 constexpr int ROW_BATCHES = 8;  // most batches of a row: 64 vectors per thread
 

@@ -76,3 +76,42 @@ def test_recreated_tree_starts_clean(dev, static):
         assert tree.device_error() == 0
         tree.close()
         assert all(torch.equal(o, r) for o, r in zip(out, ref[i % 2])), i
+
+
+@pytest.mark.parametrize("dense", [False, True])
+def test_smaller_tree_leaves_larger_one_its_lds(dev, dense):
+    """A tree whose prune kernel, and in dense mode whose row kernel, takes most of
+    a compute unit's LDS still runs after a smaller tree of the kind is created."""
+    import os
+    from paper_2609_21827_amd.binding import Tree
+    V, K, depth, R = (262143, 4, 2, 12) if dense else (2048, 15, 13, 500)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+
+    def make(V, depth):
+        return Tree(batch=1, vocab=V, pool=K, leads=1, depth=depth, support=0 if dense else 64,
+                    dtype=torch.bfloat16, row_stride=(V + 7) // 8 * 8)
+
+    os.environ["RHEO_EXPAND_ROW"] = "1"
+    try:
+        large = make(V, depth)
+        draft = [torch.randn((n, large.row_stride), generator=g, device="cuda").mul_(3).bfloat16()
+                 for n in [1] + [K] * (depth - 1)]
+        target = torch.randn((R + 1, large.row_stride), generator=g, device="cuda").mul_(3).bfloat16()
+
+        def step():
+            large.begin_step()
+            for rows in draft:
+                large.expand_level(rows, 1.0, 77)
+            large.prune(R)
+            return [x.cpu() for x in (*large.pruned_view(), *large.verify(target, 1.0, 77))]
+
+        ref = step()
+        small = make(1000, 2)
+        out = step()
+        assert large.device_error() == 0
+        small.close()
+        large.close()
+    finally:
+        del os.environ["RHEO_EXPAND_ROW"]
+    assert all(torch.equal(o, r) for o, r in zip(out, ref))
