@@ -33,18 +33,17 @@ __global__ void k_pruned_view(TreeDev t, int R, int32_t* parent, int32_t* token)
     }
 }
 
-// The mask and the depths of one sequence, MSPLIT blocks each: the parents'
+// The mask and the depths of one sequence, by `split` blocks: the parents'
 // pruned indices in LDS, one ancestor walk (at most depth <= 15 steps, to
 // ever smaller indices; where the error flag says that a parent was pruned,
 // to -1 or not at all) per entry.
 constexpr int NTM = 256;
-constexpr int MSPLIT = 4;
 
-__global__ __launch_bounds__(NTM) void k_tree_mask(TreeDev t, int R, uint8_t* mask,
-                                                   int32_t* depth) {
+__global__ __launch_bounds__(NTM) void k_tree_mask(TreeDev t, int R, int split,
+                                                   uint8_t* mask, int32_t* depth) {
     extern __shared__ int s_par[];
     const int n = R + 1;
-    const int b = blockIdx.x / MSPLIT, part = blockIdx.x % MSPLIT;
+    const int b = blockIdx.x / split, part = blockIdx.x % split;
     const int64_t nb = (int64_t)b * t.NN;
     for (int i = threadIdx.x; i < n; i += NTM) {
         s_par[i] = min(max(t.pr_par[nb + i], -1), R);
@@ -53,7 +52,7 @@ __global__ __launch_bounds__(NTM) void k_tree_mask(TreeDev t, int R, uint8_t* ma
     __syncthreads();
     if (!mask) return;
     uint8_t* out = mask + (int64_t)b * n * n;
-    for (int e = part * NTM + threadIdx.x; e < n * n; e += NTM * MSPLIT) {
+    for (int e = part * NTM + threadIdx.x; e < n * n; e += NTM * split) {
         const int i = e / n, j = e - i * n;
         int p = i;
         for (int s = 0; s < 16 && p > j; ++s) p = s_par[p];
@@ -63,7 +62,16 @@ __global__ __launch_bounds__(NTM) void k_tree_mask(TreeDev t, int R, uint8_t* ma
 
 hipError_t launch_tree_mask(const TreeDev& t, int R, uint8_t* mask, int32_t* depth,
                             hipStream_t s) {
-    k_tree_mask<<<t.B * MSPLIT, NTM, sizeof(int) * (size_t)(R + 1), s>>>(t, R, mask, depth);
+    // Blocks of a sequence: four entries a thread, so that one large mask fills
+    // the chip (one sequence, R = 400: 5.1 us with sixteen entries a thread, 145 us
+    // at R = 1000 by four blocks), at least four and at most 8192 in all, beyond
+    // which each would only read the parents again (32 sequences, R = 3000: 242 us).
+    const int64_t n2 = (int64_t)(R + 1) * (R + 1);
+    int64_t split = (n2 + 4 * NTM - 1) / (4 * NTM);
+    if (split > 8192 / t.B) split = 8192 / t.B;
+    if (split < 4) split = 4;
+    k_tree_mask<<<t.B * (int)split, NTM, sizeof(int) * (size_t)(R + 1), s>>>(t, R, (int)split, mask,
+                                                                         depth);
     return hipGetLastError();
 }
 

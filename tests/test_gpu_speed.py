@@ -1,0 +1,97 @@
+"""Calls whose time must not fall off a cliff: sizes and values at which a kernel
+leaves its common path, timed against the same call beside them (or a bound
+several times what it takes).  The margins are wide: each stands between what
+the call takes and what it took while it was broken."""
+
+import os
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2609_21827_amd import binding
+    binding.load_library()
+    return "cuda"
+
+
+def _time(f, n=8):
+    """us of one call among others, the best of five runs."""
+    best = float("inf")
+    f()
+    for _ in range(5):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        torch.cuda.synchronize()
+        torch.cuda._sleep(500000)
+        a.record()
+        for _ in range(n):
+            f()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) / n * 1e3)
+    return best
+
+
+class Levels:
+    """A tree and the draft rows of its levels."""
+
+    def __init__(self, B, V, K, depth, support, dtype="bf16", shape=None, env=None, full=False):
+        from paper_2609_21827_amd.binding import Tree
+        td = torch.bfloat16 if dtype == "bf16" else torch.float32
+        g = torch.Generator(device="cuda")
+        g.manual_seed(5)
+        stride = (V + 7) // 8 * 8
+        base = torch.randn((B, 1, V), generator=g, device="cuda").mul_(2)
+        self.rows = []
+        for n in [1] + [K] * (depth - 1):
+            x = torch.randn((B, n, V), generator=g, device="cuda").mul_(0.7).add_(base)
+            if shape is not None:
+                shape(x)
+            r = torch.zeros((B, n, stride), dtype=td, device="cuda")
+            r[..., :V] = x
+            self.rows.append(r)
+        os.environ.update(env or {})
+        try:
+            self.tree = Tree(batch=B, vocab=V, pool=K, leads=1, depth=depth, support=support,
+                             dtype=td, row_stride=stride, construct_full=full)
+        finally:
+            for k in env or {}:
+                del os.environ[k]
+
+    def step(self):
+        self.tree.begin_step()
+        for r in self.rows:
+            self.tree.expand_level(r, 1.0, 9)
+
+    def time(self):
+        us = _time(self.step)
+        assert self.tree.device_error() == 0
+        self.tree.close()
+        return us
+
+
+# 9 million entries of one sequence: 32 us over the whole chip, 1800 by four blocks
+# of its compute units; a million: 6 and 145 us
+@pytest.mark.parametrize("B,R,bound", [(1, 3000, 200), (1, 1000, 60), (4, 1000, 80)])
+def test_large_masks(dev, B, R, bound):
+    L = Levels(B, 2048, 15, 15, 128)
+    L.step()
+    L.tree.prune(R)
+    out = (torch.empty((B, R + 1, R + 1), dtype=torch.uint8, device=dev),
+           torch.empty((B, R + 1), dtype=torch.int32, device=dev))
+    us = _time(lambda: L.tree.tree_mask(out=out))
+    par = L.tree.pruned_view()[0][0].cpu()
+    L.tree.close()
+    print(f"{us:.1f} us")
+    assert us < bound
+    # the last rows against the parents' walk
+    for i in range(max(0, R - 40), R + 1):
+        path, p = set(), i
+        while p >= 0:
+            path.add(p)
+            p = int(par[p])
+        assert set(torch.nonzero(out[0][0, i]).flatten().tolist()) == path
