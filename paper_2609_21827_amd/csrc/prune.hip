@@ -9,11 +9,20 @@
 // compared: the scores are counted in bins of an eighth of an octave (a
 // monotone map of the score's high bits), one prefix sum gives every bin's
 // first rank, and the exact order inside the bins that begin below rank R
-// comes from comparing a bin's members with each other.  The kernel is a
-// chain of latencies (one read of the scores, one of the candidates'
-// records).  Counting every node against every other, on sixteen blocks a
-// sequence, took 6.6 us at 456 nodes and 64 sequences and 21 us at 710 nodes
-// and 128; this takes 5.2 and 8.2 us.
+// comes from comparing a bin's members with each other, which lie side by
+// side in LDS and are read eight at a time.  The kernel is a chain of
+// latencies (one read of the scores, one of the candidates' records).
+// Counting every node against every other, on sixteen blocks a sequence, took
+// 6.6 us at 392 nodes and 64 sequences and 22.5 us at 710 nodes and 128; this
+// takes 4.3 and 6.9 us.
+//
+// A bin of many members costs their number squared, so the bins follow where
+// scores pile up: scores of 0 (weights of 0 below confident rows) have a bin
+// per depth, which is their next criterion; trees of more nodes than threads,
+// whose deep scores pass below the 62 octaves of the other bins (flat rows:
+// eleven octaves a level at V = 2048), take coarser ones if their least score
+// needs them.  3165 nodes of equal rows, R = 3000: 111 us by counting all, 460
+// with the scores below 2^-63 in one bin, 59 so.
 #include "rheo_device.h"
 #include "rheo_state.h"
 
@@ -21,23 +30,37 @@ namespace rheo {
 
 constexpr int NTR = 512;
 constexpr int PBINS = 512;                   // one bin per thread
+constexpr int ZBINS = 15;                    // of them, for scores of 0: one per depth
+constexpr int kOne = 0x3FF << 3;             // score_bits of 1
 
-// The bin of a score in [0, 1] or infinite (score_order): its exponent and three mantissa bits, from 511
-// (1 and above) down to 2^-63 and below (0).
-__device__ __forceinline__ int score_bin(double s) {
-    const int k = (int)((uint64_t)__double_as_longlong(s) >> 49);
-    return min(max(k - ((0x3FF << 3) - (PBINS - 1)), 0), PBINS - 1);
+// The exponent of a score and three bits of its mantissa.
+__device__ __forceinline__ int score_bits(double s) {
+    return (int)((uint64_t)__double_as_longlong(s) >> 49);
+}
+// The bin of a score in [0, 1] or infinite (score_order), of a node of
+// index i among the non-root nodes: 511 for 1 and above.
+__device__ __forceinline__ int score_bin(double s, int coarse, const TreeDev& t, int i) {
+    if (s == 0.0) {
+        const int above = i < t.K ? 0 : 1 + (i - t.K) / (t.NE * t.K);   // depth - 1
+        return ZBINS - 1 - above;
+    }
+    return min(max(((score_bits(s) - kOne) >> coarse) + PBINS - 1, ZBINS), PBINS - 1);
 }
 
+struct alignas(16) ScoreKey {
+    double score;
+    uint64_t lo;                             // lower half of the priority key
+};
+constexpr int KSTEP = 8;                     // keys compared at a time
+
 struct PruneLds {
-    int lo, ord, bs, rank, bytes;            // scores first
+    int score, bs, rank, bytes;              // the keys, in bin order, first
 };
 __host__ __device__ inline PruneLds prune_lds(int n) {
     PruneLds L;
-    L.lo = 8 * n;
-    L.bs = L.lo + 8 * n;
-    L.ord = L.bs + 4 * n;
-    L.rank = L.ord + 2 * n;
+    L.score = 16 * (n + KSTEP);
+    L.bs = L.score + 8 * n;
+    L.rank = L.bs + 4 * n;
     L.bytes = L.rank + 2 * n;
     return L;
 }
@@ -51,19 +74,33 @@ __global__ __launch_bounds__(NTR) void k_prune(TreeDev t, int R) {
     const int n = t.NN - 1;                  // non-root nodes, uids 1..NN-1
     const int64_t nb = (int64_t)b * t.NN;
     const PruneLds L = prune_lds(n);
-    double* s_score = (double*)s_dyn;
-    uint64_t* s_lo = (uint64_t*)(s_dyn + L.lo);
+    ScoreKey* s_key = (ScoreKey*)s_dyn;
+    double* s_score = (double*)(s_dyn + L.score);
     int* s_bs = (int*)(s_dyn + L.bs);
-    int16_t* s_ord = (int16_t*)(s_dyn + L.ord);
     int16_t* s_rank = (int16_t*)(s_dyn + L.rank);
     s_hist[tid] = 0;
-    __syncthreads();
+    int coarse = 0;
+    int least = kOne;
     for (int i = tid; i < n; i += NTR) {
         const double sc = score_order(t.score[nb + 1 + i]);
-        const int bin = score_bin(sc);
         s_score[i] = sc;
+        if (sc != 0.0) least = min(least, score_bits(sc));
+    }
+    if (n > NTR) {
+        // the widest bins whose range does not end above the least score
+        for (int o = 1; o < WAVE; o <<= 1) least = min(least, __shfl_xor(least, o));
+        if (lane == 0) s_w[wid] = least;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < NTR / WAVE; ++w) least = min(least, s_w[w]);
+        while (((kOne - least) >> coarse) > PBINS - 1 - ZBINS) ++coarse;
+    }
+    __syncthreads();
+    for (int i = tid; i < n; i += NTR) {
+        const int bin = score_bin(s_score[i], coarse, t, i);
         s_bs[i] = bin | (atomicAdd(&s_hist[bin], 1) << 16);
     }
+    if (tid < KSTEP) s_key[n + tid].score = -1.0;
     if (tid == 0) {
         t.node[nb].pidx = 0;
         t.pr_par[nb] = -1;
@@ -80,16 +117,17 @@ __global__ __launch_bounds__(NTR) void k_prune(TreeDev t, int R) {
         s_start[PBINS - 1 - tid] = ex;
     }
     __syncthreads();
-    // candidates: the members of the bins that begin below rank R, with the
-    // lower half of their priority key
+    // every score in bin order, and for the candidates, the members of the bins
+    // that begin below rank R, the lower half of their priority key
     for (int i = tid; i < n; i += NTR) {
         const int bs = s_bs[i], st = s_start[bs & 0xFFFF];
+        ScoreKey& k = s_key[st + (bs >> 16)];
+        k.score = s_score[i];
+        k.lo = 0;                            // (ranks below every candidate of its score)
         if (st < R) {
             const Node& nd = t.node[nb + 1 + i];
-            uint64_t hi, lo;
-            prio_key(s_score[i], nd.meta & 0xFF, nd.path, hi, lo);
-            s_lo[i] = lo;
-            s_ord[st + (bs >> 16)] = (int16_t)i;
+            uint64_t hi;
+            prio_key(k.score, nd.meta & 0xFF, nd.path, hi, k.lo);
         }
     }
     __syncthreads();
@@ -97,13 +135,17 @@ __global__ __launch_bounds__(NTR) void k_prune(TreeDev t, int R) {
         const int bin = s_bs[i] & 0xFFFF, st = s_start[bin];
         int rk = n;
         if (st < R) {
-            const double sc = s_score[i];
-            const uint64_t lo = s_lo[i];
+            const ScoreKey me = s_key[st + (s_bs[i] >> 16)];
             rk = st;
-            for (int q = st; q < st + s_hist[bin]; ++q) {
-                const int o = s_ord[q];
-                const double so = s_score[o];
-                rk += (int)(so > sc) | ((int)(so == sc) & (int)(s_lo[o] > lo));
+            // (keys past the bin rank lower and count for nothing)
+            for (int q = st; q < st + s_hist[bin]; q += KSTEP) {
+                ScoreKey k[KSTEP];
+#pragma unroll
+                for (int u = 0; u < KSTEP; ++u) k[u] = s_key[q + u];
+#pragma unroll
+                for (int u = 0; u < KSTEP; ++u)
+                    rk += (int)(k[u].score > me.score) |
+                          ((int)(k[u].score == me.score) & (int)(k[u].lo > me.lo));
             }
         }
         s_rank[i] = (int16_t)(rk < R ? rk + 1 : -1);

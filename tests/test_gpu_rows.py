@@ -225,6 +225,53 @@ def test_prune_budgets(dev, R, same):
         assert np.array_equal(mask[b], want)
 
 
+@pytest.mark.parametrize("kind", ["plain", "flat", "const", "onehot", "mixed"])
+@pytest.mark.parametrize("K,depth", [(15, 15), (12, 8), (3, 3)])
+def test_prune_piles(dev, kind, K, depth):
+    """Scores that pile up: equal and nearly equal ones below 2^-63, scores of 0
+    (one token a row has all the weight), both beside ordinary ones; trees of
+    more nodes than a block has threads; budgets up to every node."""
+    from paper_2609_21827_amd.binding import Tree
+    rng = np.random.default_rng(9)
+    V, B = 2048, 2
+    tree = Tree(batch=B, vocab=V, pool=K, leads=1, depth=depth, support=64, dtype=torch.float32)
+    rows = []
+    for n in [1] + [K] * (depth - 1):
+        x = rng.standard_normal((B, n, V)).astype(np.float32) * 3
+        if kind == "flat":
+            x *= 1e-3
+        elif kind == "const":
+            x[:] = 0.5
+        elif kind != "plain":
+            hot = np.ones((B, n), bool) if kind == "onehot" else rng.random((B, n)) < 0.5
+            for b, j in zip(*np.nonzero(hot)):
+                x[b, j, rng.integers(V)] += 60
+        rows.append(torch.from_numpy(x).to("cuda"))
+    N = 1 + K + (depth - 1) * K * K
+    views = {}
+    try:
+        for R in sorted({1, min(60, N - 1), N // 2, N - 1}):
+            tree.begin_step()
+            for x in rows:
+                tree.expand_level(x, 1.0, KEY)
+            nodes = {k: v.cpu().numpy() for k, v in tree.read_nodes().items()}
+            tree.prune(R)
+            views[R] = [v.cpu().numpy() for v in tree.pruned_view()]
+        assert tree.device_error() == 0
+    finally:
+        tree.close()
+    for b in range(B):
+        n = {k: v[b] for k, v in nodes.items()}
+        path = [()]
+        for u in range(1, N):
+            path.append(path[n["parent"][u]] + (int(n["slot"][u]),))
+        order = [0] + sorted(range(1, N), key=lambda u: (-n["score"][u], n["depth"][u], path[u]))
+        place = {u: i for i, u in enumerate(order)}
+        for R, (par, tok) in views.items():
+            assert list(par[b]) == [-1] + [place[n["parent"][u]] for u in order[1:R + 1]], (b, R)
+            assert list(tok[b]) == [-1] + [n["token"][u] for u in order[1:R + 1]], (b, R)
+
+
 # dense mode's row kernel: the counts' edges as above, ties of the last listed
 # construction weight, the draw's batch and slot, the longest row
 @pytest.mark.parametrize("kind", ["plain", "edges", "small", "large", "const", "sorted", "sorted_up",

@@ -95,3 +95,27 @@ def test_large_masks(dev, B, R, bound):
             path.add(p)
             p = int(par[p])
         assert set(torch.nonzero(out[0][0, i]).flatten().tolist()) == path
+
+
+# 3165 nodes of nearly equal rows (scores down to 2^-165), and of rows with one
+# token each (scores of 0 but for a few): 460 us a prune with all of these in one
+# bin, 111 by comparing every two
+@pytest.mark.parametrize("kind", ["flat", "onehot"])
+def test_prune_of_piled_scores(dev, kind):
+    def shape(x):
+        if kind == "flat":
+            x.mul_(0.01)
+        else:
+            x[..., 7] += 60
+    L = Levels(4, 2048, 15, 15, 128, shape=shape)
+
+    def both():
+        L.step()
+        L.tree.prune(3000)
+
+    both()
+    us = _time(both) - _time(L.step)
+    assert L.tree.device_error() == 0
+    L.tree.close()
+    print(f"{us:.1f} us")
+    assert us < 200
