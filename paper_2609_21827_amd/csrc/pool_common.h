@@ -243,12 +243,23 @@ __device__ __forceinline__ void select_frontier(const TreeDev& t, const LevelArg
         s_hi[tid] = hi;
         s_lo[tid] = lo;
         s_tok[tid] = tok;
+    } else if (tid < 256) {
+        s_hi[tid] = (uint64_t)__double_as_longlong(-1.0);   // below every score
+        s_lo[tid] = 0;
     }
     __syncthreads();
     // F adjacent lanes a child (a power of two, at most 8), each over every
     // F-th key.  Scores first, as the doubles they are (non-negative, not NaN:
-    // prio_key; one full-rate compare); the rest of the key only where two are equal, which
-    // is rare.
+    // prio_key; one full-rate compare).  The sampled child has its last lead's
+    // score wherever that is below z, so two equal scores are the rule: the
+    // places of the equal ones are summed beside their number, and of two the
+    // other is known; more than two take a second pass over the keys.  Eight
+    // keys are read at a time, up to the 256 that the arrays hold.
+    //
+    // The 144 children of twelve a node, one lane each (256 threads): read one
+    // by one and in two passes they took some 7 us more than by 128-bit
+    // compares in one, now less than that.
+    constexpr int STEP = 8;
     int F = 1;
     while (F < 8 && 2 * F * n <= NT) F *= 2;
     const int c = tid / F;
@@ -257,23 +268,38 @@ __device__ __forceinline__ void select_frontier(const TreeDev& t, const LevelArg
     const double mine = __longlong_as_double((long long)s_hi[cc]);
     const uint64_t mlo = s_lo[cc];
     const int ctok = s_tok[cc];
-    int rk = 0, eq = 0;
-#pragma unroll 8
-    for (int q = tid % F; q < n; q += F) {
-        const double h = __longlong_as_double((long long)s_hi[q]);
-        rk += (int)(h > mine);
-        eq += (int)(h == mine);
+    uint32_t rk = 0, eq = 0;                     // eq: number << 16 | sum of places (< 2^16)
+    for (int q = tid % F; q < n; q += STEP * F) {
+        double h[STEP];
+#pragma unroll
+        for (int u = 0; u < STEP; ++u) h[u] = __longlong_as_double((long long)s_hi[q + u * F]);
+#pragma unroll
+        for (int u = 0; u < STEP; ++u) {
+            rk += (uint32_t)(h[u] > mine);
+            eq += h[u] == mine ? (uint32_t)(0x10000 + q + u * F) : 0u;
+        }
     }
-    uint32_t sums = (uint32_t)rk | ((uint32_t)eq << 16);
-    sums = lanes_sum(sums, F);
-    if (__ballot((sums >> 16) > 1u) != 0ull) {
-        rk = 0;
-        for (int q = tid % F; q < n; q += F)
-            rk += (int)(__longlong_as_double((long long)s_hi[q]) == mine) & (int)(s_lo[q] > mlo);
-        sums += lanes_sum((uint32_t)rk, F);
+    rk = lanes_sum(rk, F);
+    eq = lanes_sum(eq, F);
+    if ((eq >> 16) == 2u) rk += (uint32_t)(s_lo[(int)(eq & 0xFFFFu) - cc] > mlo);
+    if (__ballot((eq >> 16) > 2u) != 0ull) {
+        uint32_t more = 0;
+        for (int q = tid % F; q < n; q += STEP * F) {
+            double h[STEP];
+            uint64_t l[STEP];
+#pragma unroll
+            for (int u = 0; u < STEP; ++u) {
+                h[u] = __longlong_as_double((long long)s_hi[q + u * F]);
+                l[u] = s_lo[q + u * F];
+            }
+#pragma unroll
+            for (int u = 0; u < STEP; ++u)
+                more += (uint32_t)((int)(h[u] == mine) & (int)(l[u] > mlo));
+        }
+        more = lanes_sum(more, F);
+        if ((eq >> 16) > 2u) rk += more;
     }
-    rk = (int)(sums & 0xFFFFu);
-    if (tid % F == 0 && c < n && rk < NE) {
+    if (tid % F == 0 && c < n && rk < (uint32_t)NE) {
         t.frontier[(int64_t)b * NE + rk] = cb + c;
         t.fr_parent[(int64_t)b * NE + rk] = c / K;
         t.fr_token[(int64_t)b * NE + rk] = ctok;

@@ -119,3 +119,11 @@ def test_prune_of_piled_scores(dev, kind):
     L.tree.close()
     print(f"{us:.1f} us")
     assert us < 200
+
+
+# the frontier of 144 children by a 256-thread block: 1.05 times the levels of 100
+# children, 1.27 with the keys read one by one in two passes
+def test_frontier_of_many_children(dev):
+    us = {K: Levels(2, 32000, K, 7, 0, dtype="f32").time() for K in (10, 12)}
+    print(us)
+    assert us[12] < 1.17 * us[10]
