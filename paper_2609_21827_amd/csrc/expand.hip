@@ -612,7 +612,7 @@ __device__ __forceinline__ void select_block(const TreeDev& t, const LevelArgs& 
     if (cnt > CAPC) {
         // degenerate chunk: exact selection from the chunk in memory
         const int eb = v0 * VEC;                 // first element of the chunk
-        __shared__ int s_tie[32][NW];
+        __shared__ int s_scr[256];           // (32 vectors x NW waves, or a digit's counts)
         __syncthreads();
         if (tid == 0) s_cnt = 0;
         exact_select_fallback<DT, NTC, NVC>(
@@ -624,7 +624,7 @@ __device__ __forceinline__ void select_block(const TreeDev& t, const LevelArgs& 
                     else s_keys[pos] = logit_key(v, (uint32_t)id);
                 }
             },
-            s_redi, s_tie);
+            s_redi, s_scr);
         cnt = min(fallback_count(&s_cnt), CAPC);
     }
 

@@ -224,25 +224,46 @@ __device__ __forceinline__ uint32_t offer_threshold(uint32_t c1, uint32_t c2, in
     return offer_threshold<NT>(c1, c2, 0u, 0u, false, nsel, s_cnt);
 }
 
+// Adds 1 to s_hist[d] for every lane with `in`: one add for all the lanes that share
+// the first such lane's digit, so that equal elements do not queue on a word.
+__device__ __forceinline__ void count_digit(int* s_hist, uint32_t d, bool in) {
+    const uint64_t all = __ballot(in);
+    if (all == 0ull) return;
+    const int lead = (int)__builtin_ctzll(all);
+    const uint64_t same = __ballot(in && d == lane_u32(d, lead));
+    const int lane = threadIdx.x % WAVE;
+    if (lane == lead) atomicAdd(&s_hist[d], __popcll(same));
+    else if (in && !((same >> lane) & 1ull)) atomicAdd(&s_hist[d], 1);
+}
+
 // Exact selection for a degenerate range: more candidates than LDS holds
-// (massive ties at the threshold, or large values crowded into few
-// threads).  The range is NQ vectors per thread, vector q of this thread at
+// (massive ties at the threshold, large values crowded into few threads, or a
+// support near the number of the row's vectors, whose maxima then bound
+// nothing).  The range is NQ vectors per thread, vector q of this thread at
 // index vfirst + q * NT + tid; elements at V and beyond do not count;
-// push(v, id) records an element.  Rare, so it re-reads the range, four
-// vectors at a time.  bf16: count the elements whose code lies above the
-// threshold code h; if the nsel-th largest element has code h, take
-// everything above h and the smallest ids among those at h (ranks of the
-// ties in id order from per-wave counts and wave scans); if it lies above h
-// and the elements above h fit (at most cap), take those.  Otherwise, and for
-// fp32, find the nsel-th largest key by bisection.  Ends with a barrier.
+// push(v, id) records an element.  It re-reads the range, four vectors at a
+// time, once per pass.
+//
+// bf16: count the elements whose code lies above the threshold code h; if the
+// nsel-th largest element has code h, x = h; if it lies above h and the
+// elements above h fit (at most cap), take those.  Otherwise, and for fp32, x
+// = the nsel-th largest code (bf16: the 16-bit order code, fp32: the 32-bit
+// one) by its digits from the top, 8 bits a pass, each from a histogram of
+// the elements that share the digits before.  Then everything above x and the
+// smallest ids among those at x (ranks of the ties in id order from per-wave
+// counts and wave scans).  By bisection of the 64-bit key, in 64 passes, a level of
+// 1000 bf16 elements at support 128 took 197 us, of 2500 fp32 elements at
+// support 1024 180; so they take 33 and 53.
+//
+// s_scr holds max(256, NQ * NT / WAVE) ints.  Ends with a barrier.
 template <int DT, int NT, int NQ, typename Push>
 __device__ void exact_select_fallback(const char* base, int V, int vfirst, uint32_t h, int nsel,
-                                      int cap, Push push, int* s_redi,
-                                      int (*s_tie)[NT / WAVE]) {
+                                      int cap, Push push, int* s_redi, int* s_scr) {
     constexpr int VEC = DT ? 8 : 4;
     constexpr int NW = NT / WAVE;
     static_assert(NQ % 4 == 0 && NQ <= 64, "re-read in groups of four vectors");
     const int tid = threadIdx.x, lane = tid % WAVE, wid = tid / WAVE;
+    int (*s_tie)[NW] = (int (*)[NW])s_scr;
     // the vectors of the range inside the row, in groups of four; the opaque trip
     // count keeps each pass a loop (re-reading per pass) rather than one
     // straight-line block holding every element
@@ -257,7 +278,10 @@ __device__ void exact_select_fallback(const char* base, int V, int vfirst, uint3
 #pragma unroll
         for (int q = 0; q < 4; ++q) w[q] = load_row_vec<DT>(base, vf + (q0 + q) * NT + tid, V);
     };
-    bool done = false;
+    auto code = [](float v) { return DT ? ord32(v) >> 16 : ord32(v); };
+    uint32_t x = h;                              // the nsel-th largest code
+    int need = 0;                                // elements to take at it
+    bool found = false;
     if (DT) {
         int ngt = 0;
 #pragma unroll 1
@@ -269,13 +293,25 @@ __device__ void exact_select_fallback(const char* base, int V, int vfirst, uint3
                 const int e0 = (vfirst + (q0 + q) * NT + tid) * VEC;
 #pragma unroll
                 for (int k = 0; k < VEC; ++k)
-                    ngt += (e0 + k < V && (ord32(elem<DT>(w[q], k)) >> 16) > h) ? 1 : 0;
+                    ngt += (e0 + k < V && code(elem<DT>(w[q], k)) > h) ? 1 : 0;
             }
         }
         ngt = block_sum_i32<NT>(ngt, s_redi);
-        if (ngt < nsel) {
-            // ties at h, in id order: vector q, then thread, then element
-            const int need = nsel - ngt;
+        need = nsel - ngt;
+        found = need > 0;
+        if (!found && ngt <= cap) {
+            need = 0;                            // (all above h, none at it)
+            found = true;
+        }
+    }
+    if (!found) {
+        x = 0;
+        need = nsel;
+#pragma unroll 1
+        for (int sh = DT ? 8 : 24; sh >= 0; sh -= 8) {
+            __syncthreads();                     // (the digit before is read)
+            for (int i = tid; i < 256; i += NT) s_scr[i] = 0;
+            __syncthreads();
 #pragma unroll 1
             for (int q0 = 0; q0 < nq; q0 += 4) {
                 uint4 w[4];
@@ -283,89 +319,43 @@ __device__ void exact_select_fallback(const char* base, int V, int vfirst, uint3
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int e0 = (vfirst + (q0 + q) * NT + tid) * VEC;
-                    int nt = 0;
 #pragma unroll
-                    for (int k = 0; k < VEC; ++k)
-                        nt += (e0 + k < V && (ord32(elem<DT>(w[q], k)) >> 16) == h) ? 1 : 0;
-                    const int tot = wave_sum_i32(nt);
-                    if (lane == 0) s_tie[q0 + q][wid] = tot;
+                    for (int k = 0; k < VEC; ++k) {
+                        const uint32_t c = code(elem<DT>(w[q], k));
+                        count_digit(s_scr, (c >> sh) & 255u,
+                                    e0 + k < V && ((c ^ x) >> sh) >> 8 == 0u);
+                    }
                 }
             }
             __syncthreads();
-            int prior = 0;                   // ties in the vectors before q, all threads
-#pragma unroll 1
-            for (int q0 = 0; q0 < nq; q0 += 4) {
-                uint4 w[4];
-                group(q0, w);
+            // every wave finds the largest digit that `need` elements reach; lane l
+            // holds digits 4 l .. 4 l + 3
+            int cnt[4], sum = 0;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int e0 = (vfirst + (q0 + q) * NT + tid) * VEC;
-                    int nt = 0;
-#pragma unroll
-                    for (int k = 0; k < VEC; ++k)
-                        nt += (e0 + k < V && (ord32(elem<DT>(w[q], k)) >> 16) == h) ? 1 : 0;
-                    int rk = prior + wave_excl_scan(nt);
-#pragma unroll
-                    for (int ww = 0; ww < NW; ++ww) {
-                        rk += (ww < wid) ? s_tie[q0 + q][ww] : 0;
-                        prior += s_tie[q0 + q][ww];
-                    }
-#pragma unroll
-                    for (int k = 0; k < VEC; ++k) {
-                        const float v = elem<DT>(w[q], k);
-                        const uint32_t cd = ord32(v) >> 16;
-                        if (e0 + k < V) {
-                            if (cd > h) {
-                                push(v, e0 + k);
-                            } else if (cd == h) {
-                                if (rk < need) push(v, e0 + k);
-                                ++rk;
-                            }
-                        }
-                    }
-                }
+            for (int k = 0; k < 4; ++k) {
+                cnt[k] = s_scr[4 * lane + k];
+                sum += cnt[k];
             }
-            done = true;
-        } else if (ngt <= cap) {
-#pragma unroll 1
-            for (int q0 = 0; q0 < nq; q0 += 4) {
-                uint4 w[4];
-                group(q0, w);
+            const int ex = wave_excl_scan(sum);
+            int above = (int)lane_u32((uint32_t)(ex + sum), WAVE - 1) - ex - sum;
+            int digit = -1, left = 0;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int e0 = (vfirst + (q0 + q) * NT + tid) * VEC;
-#pragma unroll
-                    for (int k = 0; k < VEC; ++k) {
-                        const float v = elem<DT>(w[q], k);
-                        if (e0 + k < V && (ord32(v) >> 16) > h) push(v, e0 + k);
-                    }
+            for (int k = 3; k >= 0; --k) {
+                if (above < need && above + cnt[k] >= need) {
+                    digit = 4 * lane + k;
+                    left = need - above;
                 }
+                above += cnt[k];
             }
-            done = true;
+            const uint64_t own = __ballot(digit >= 0);     // one lane: nsel <= the range
+            const int l = own ? (int)__builtin_ctzll(own) : 0;
+            x |= lane_u32((uint32_t)max(digit, 0), l) << sh;
+            need = (int)lane_u32((uint32_t)left, l);
         }
+        __syncthreads();
     }
-    if (!done) {
-        uint64_t x = 0;
-#pragma unroll 1
-        for (int bit = 63; bit >= 0; --bit) {
-            const uint64_t cand = x | (1ull << bit);
-            int n = 0;
-#pragma unroll 1
-            for (int q0 = 0; q0 < nq; q0 += 4) {
-                uint4 w[4];
-                group(q0, w);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int e0 = (vfirst + (q0 + q) * NT + tid) * VEC;
-#pragma unroll
-                    for (int k = 0; k < VEC; ++k)
-                        n += (e0 + k < V &&
-                              logit_key(elem<DT>(w[q], k), (uint32_t)(e0 + k)) >= cand) ? 1 : 0;
-                }
-            }
-            n = block_sum_i32<NT>(n, s_redi);
-            if (n >= nsel) x = cand;
-        }
+    // ties at x, in id order: vector q, then thread, then element
+    if (need > 0) {
 #pragma unroll 1
         for (int q0 = 0; q0 < nq; q0 += 4) {
             uint4 w[4];
@@ -373,10 +363,48 @@ __device__ void exact_select_fallback(const char* base, int V, int vfirst, uint3
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int e0 = (vfirst + (q0 + q) * NT + tid) * VEC;
+                int nt = 0;
 #pragma unroll
-                for (int k = 0; k < VEC; ++k) {
-                    const float v = elem<DT>(w[q], k);
-                    if (e0 + k < V && logit_key(v, (uint32_t)(e0 + k)) >= x) push(v, e0 + k);
+                for (int k = 0; k < VEC; ++k)
+                    nt += (e0 + k < V && code(elem<DT>(w[q], k)) == x) ? 1 : 0;
+                const int tot = wave_sum_i32(nt);
+                if (lane == 0) s_tie[q0 + q][wid] = tot;
+            }
+        }
+        __syncthreads();
+    }
+    int prior = 0;                               // ties in the vectors before q, all threads
+#pragma unroll 1
+    for (int q0 = 0; q0 < nq; q0 += 4) {
+        uint4 w[4];
+        group(q0, w);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int e0 = (vfirst + (q0 + q) * NT + tid) * VEC;
+            int rk = 0;
+            if (need > 0) {
+                int nt = 0;
+#pragma unroll
+                for (int k = 0; k < VEC; ++k)
+                    nt += (e0 + k < V && code(elem<DT>(w[q], k)) == x) ? 1 : 0;
+                rk = prior + wave_excl_scan(nt);
+#pragma unroll
+                for (int ww = 0; ww < NW; ++ww) {
+                    rk += (ww < wid) ? s_tie[q0 + q][ww] : 0;
+                    prior += s_tie[q0 + q][ww];
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) {
+                const float v = elem<DT>(w[q], k);
+                const uint32_t cd = code(v);
+                if (e0 + k < V) {
+                    if (cd > x) {
+                        push(v, e0 + k);
+                    } else if (cd == x) {
+                        if (rk < need) push(v, e0 + k);
+                        ++rk;
+                    }
                 }
             }
         }
@@ -701,8 +729,23 @@ __device__ __forceinline__ RowTop row_top(const TreeDev& t, const LevelArgs& a, 
     // ---- candidates: elements at or above the threshold --------------------
     float tau;
     int cnt;
-    for (bool again = false;; again = true) {
+    // Where the threshold is no logit's (the wave with the fewest vectors has
+    // not S / waves of them that are finite: supports near the number of the
+    // row's vectors, masked rows) every element of the row is a candidate:
+    // rows of more than fit ask the whole block's offers at once, and where
+    // these bound nothing either go straight to the exact selection.
+    auto unbound = [&]() { return (h << 16) <= ord32(-INFINITY) && V > CC; };
+    bool again = false;
+    if (unbound()) {
+        h = max(h, offer_threshold<NTB>(c1, c2, c3, c4, LS, S, rs.thr));
+        again = true;
+    }
+    for (;; again = true) {
         tau = (h << 16) > ord32(-INFINITY) ? unord32(h << 16) : -INFINITY;
+        if (unbound()) {
+            cnt = CC + 1;
+            break;
+        }
         // this thread's vectors of maximum >= tau: bit 8 bt + e is vector 2 e
         // of batch bt for e < 4, vector 2 e - 7 above (PAIR: vectors 4 e and
         // 4 e + 2 for e < 2, 4 e - 15 and 4 e - 13 for e = 4, 5).  A code >= h is a
@@ -781,7 +824,9 @@ __device__ __forceinline__ RowTop row_top(const TreeDev& t, const LevelArgs& a, 
                 const int ex = wave_excl_scan(n);
                 int cb = 0;
                 if (lane == WAVE - 1) cb = atomicAdd(&rs.cnt, ex + n);
-                int pos = (int)lane_u32((uint32_t)cb, WAVE - 1) + ex;
+                int pos = (int)lane_u32((uint32_t)cb, WAVE - 1);
+                if (pos > CC) take = 0;          // (too many already: the rest need not be read)
+                pos += ex;
 #pragma unroll
                 for (int k = 0; k < VEC; ++k) {
                     const float v = elem<DT>(x[r], k);
@@ -805,7 +850,6 @@ __device__ __forceinline__ RowTop row_top(const TreeDev& t, const LevelArgs& a, 
     }
     if (cnt > CC) {
         // massive ties at the threshold: exact selection from the row
-        int (*s_tie)[NW] = (int (*)[NW])(lds + L.start);
         __syncthreads();
         if (tid == 0) rs.cnt = 0;
         int* const cntp = &rs.cnt;
@@ -815,16 +859,33 @@ __device__ __forceinline__ RowTop row_top(const TreeDev& t, const LevelArgs& a, 
                 const int pos = atomicAdd(cntp, 1);
                 if (pos < CC) s_keys[pos] = logit_key(v, (uint32_t)id);
             },
-            rs.red, s_tie);
+            rs.red, (int*)(lds + L.start));
         cnt = min(fallback_count(&rs.cnt), CC);
     }
 
     // ---- the support: the top S candidates in (logit desc, id asc) order ----
     // Bins linear in the value over [tau, the row maximum] (a monotone map:
-    // one rounded subtraction, one rounded product), by the high bits of the
-    // order code when tau is -inf or the maximum +inf.
-    const bool lin = tau > -INFINITY && vmax < INFINITY;
-    const float scale = (float)NBIN / (vmax - tau);
+    // one rounded subtraction, one rounded product); from the least finite
+    // candidate up when tau is -inf (short rows: by the order code's high bits
+    // instead, an octave a bin, a level of 2000 elements, all of them candidates at
+    // support 512, took 85 us; so it takes 18).
+    float low = tau;
+    if (!(tau > -INFINITY)) {
+        float neg = -INFINITY;                   // the largest negated value
+#pragma unroll
+        for (int r = 0; r < KPT; ++r) {
+            const int i = tid + r * NTB;
+            const float v = key_value(s_keys[i < cnt ? i : 0]);
+            if (i < cnt && v > -INFINITY) neg = fmaxf(neg, -v);
+        }
+        neg = wave_max(neg);
+        if (lane == 0) rs.red[wid] = __float_as_int(neg);
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < NW; ++w) neg = fmaxf(neg, __int_as_float(rs.red[w]));
+        low = fminf(-neg, vmax);
+    }
+    const float scale = (float)NBIN / (vmax - low);
     uint64_t key[KPT];
     int kbin[KPT], kslot[KPT];
 #pragma unroll
@@ -835,8 +896,7 @@ __device__ __forceinline__ RowTop row_top(const TreeDev& t, const LevelArgs& a, 
         kslot[r] = 0;
         if (i < cnt) {
             key[r] = s_keys[i];
-            const float x = lin ? (key_value(key[r]) - tau) * scale
-                                : (float)((uint32_t)(key[r] >> 32) >> 23);
+            const float x = (key_value(key[r]) - low) * scale;   // (NaN: bin 0)
             kbin[r] = (int)fminf(fmaxf(x, 0.0f), (float)(NBIN - 1));
             kslot[r] = atomicAdd(&s_hist[kbin[r]], 1);
         }

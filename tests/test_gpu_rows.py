@@ -286,3 +286,18 @@ def test_dense_rows(dev, kind, V, m, K, T, method):
                                      ("bf16", 262143), ("bf16", 300), ("f32", 5003)])
 def test_dense_sizes(dev, dtype, V):
     _check(V, dtype, 0, "plain", 15, depth=2)
+
+
+# rows of hardly more elements than the support, of more elements than a block
+# holds candidates but of few vectors, and of few finite logits: the threshold
+# bounds nothing and the selection is exact from the row, digit by digit
+@pytest.mark.parametrize("kind", ["plain", "ties", "const", "few", "cluster", "signed_zeros",
+                                  "zero_cross", "small", "large"])
+@pytest.mark.parametrize("dtype,V,support,env", [
+    ("bf16", 1000, 128, None), ("bf16", 2051, 1024, None), ("bf16", 8253, 1024, None),
+    ("bf16", 1000, 128, {"RHEO_ROW_NARROW": "1"}), ("bf16", 3001, 700, {"RHEO_EXPAND_ROW": "0"}),
+    ("f32", 2003, 512, None), ("f32", 2051, 1024, None), ("f32", 1003, 900, None),
+    ("f32", 3001, 700, {"RHEO_EXPAND_ROW": "0"}), ("bf16", 700, 0, {"RHEO_EXPAND_ROW": "1"}),
+])
+def test_short_rows(dev, kind, dtype, V, support, env):
+    _check(V, dtype, support, kind, 17, depth=2, env=env)

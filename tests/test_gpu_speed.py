@@ -127,3 +127,15 @@ def test_frontier_of_many_children(dev):
     us = {K: Levels(2, 32000, K, 7, 0, dtype="f32").time() for K in (10, 12)}
     print(us)
     assert us[12] < 1.17 * us[10]
+
+
+# rows whose threshold bounds nothing, against rows of one candidate list: 1000
+# elements of bf16 at support 128 took 14 times the levels of 900, 2000 of fp32 at
+# support 512 five times those of 4000, both by bisection of the key in 64 passes
+@pytest.mark.parametrize("dtype,V,ref,support", [("bf16", 1000, 900, 128), ("f32", 2000, 4000, 512),
+                                                 ("bf16", 2000, 4000, 256),
+                                                 ("bf16", 4000, 8000, 1024)])
+def test_short_rows(dev, dtype, V, ref, support):
+    us = {v: Levels(5, v, 8, 4, support, dtype=dtype).time() for v in (V, ref)}
+    print(us)
+    assert us[V] < 3 * us[ref]
