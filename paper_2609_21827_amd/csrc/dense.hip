@@ -204,24 +204,20 @@ __global__ __launch_bounds__(NTD) void k_dweights(TreeDev t, LevelArgs a) {
 // A token outside the top kk by logit ties the kk-th construction weight with a
 // smaller id.  The top kk by (w1, id) is then: every token with w1 above that
 // weight (all among the top kk by logit), and the lowest ids with exactly that
-// weight, found by a scan of the row in id order (each thread a contiguous
-// range).  s_tl: the top kk by logit; s_rk: their keys w1 << 32 | ~id.
+// weight, found by a scan of the row in id order, a vector a thread at a time and
+// no further than the last of them.  s_tl: the top kk by logit; s_rk: their keys
+// w1 << 32 | ~id.
 template <int DT, int NT>
 __device__ __noinline__ void ranks_by_weight(const char* base, int V, float M, float k1, int kk,
                                              const uint64_t* s_tl, const uint64_t* s_rk,
                                              uint64_t* s_x, uint32_t* s_xw, uint64_t* s_red) {
+    constexpr int VEC = DT ? 8 : 4;
     const int tid = threadIdx.x;
     uint32_t wmin = 0xFFFFFFFFu;
     for (int q = 0; q < kk; ++q) wmin = min(wmin, (uint32_t)(s_rk[q] >> 32));
     int ngt = 0;
     for (int q = 0; q < kk; ++q) ngt += (int)((uint32_t)(s_rk[q] >> 32) > wmin);
     const int need = kk - ngt;
-    const int per = (V + NT - 1) / NT;
-    const int lo = min(V, tid * per), hi = min(V, lo + per);
-    int mine = 0;
-    for (int v = lo; v < hi; ++v) mine += (int)(cweight(dlogit<DT>(base, v), M, k1) == wmin);
-    uint64_t tot;
-    int before = (int)block_excl_scan_u64<NT>((uint64_t)mine, s_red, &tot);
     // the tokens above wmin keep their (w1, id) order first
     if (tid < kk && (uint32_t)(s_rk[tid] >> 32) > wmin) {
         const uint64_t k = s_rk[tid];
@@ -230,13 +226,28 @@ __device__ __noinline__ void ranks_by_weight(const char* base, int V, float M, f
         s_x[rk] = s_tl[tid];
         s_xw[rk] = (uint32_t)(k >> 32);
     }
-    for (int v = lo; v < hi && before < need; ++v) {
-        const float l = dlogit<DT>(base, v);
-        if (cweight(l, M, k1) == wmin) {
-            s_x[ngt + before] = logit_key(l, (uint32_t)v);
-            s_xw[ngt + before] = wmin;
-            ++before;
+    int before = 0;                              // tokens of weight wmin so far
+    for (int v0 = 0; v0 * VEC < V && before < need; v0 += NT) {
+        const uint4 x = dload_vec<DT>(base, v0 + tid, V);
+        const int e0 = (v0 + tid) * VEC;
+        uint32_t hit = 0;
+#pragma unroll
+        for (int k = 0; k < VEC; ++k)
+            hit |= (uint32_t)(e0 + k < V && cweight(delem<DT>(x, k), M, k1) == wmin) << k;
+        uint64_t tot;
+        int pos = before + (int)block_excl_scan_u64<NT>((uint64_t)__popc(hit), s_red, &tot);
+        if (hit != 0u && pos < need) {
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) {
+                if (((hit >> k) & 1u) == 0u) continue;
+                if (pos < need) {
+                    s_x[ngt + pos] = logit_key(delem<DT>(x, k), (uint32_t)(e0 + k));
+                    s_xw[ngt + pos] = wmin;
+                }
+                ++pos;
+            }
         }
+        before += (int)tot;
     }
 }
 
@@ -494,10 +505,10 @@ __global__ __launch_bounds__(NTD) void k_dpool(TreeDev t, LevelArgs a) {
 // again: its weights come from the tables.
 //
 // Where the counts do not cover the row (a value of 2^9 or more, a weight
-// below -2^9, an overflow, more values below 2^-11 than are listed) the sums
-// and Y's batch take every element's own weight.  Where a value outside the
-// top m + K shares the last one's construction weight, the ranks come from a
-// scan of the row in id order.
+// below -2^9, an overflow, more small values than are listed, few values) the
+// sums and Y's batch take every element's own weight, in one more pass over the
+// row.  Where a value outside the top m + K shares the last one's construction
+// weight, the ranks come from a scan of the row in id order.
 //
 // Evaluating both weights of every element in a pass of its own bound the
 // level (30 vector instructions an element): at 512 rows of 128256, 34 us to
@@ -521,7 +532,7 @@ __global__ __launch_bounds__(NTX, 4) void k_dense_row(RowArgs) {
     __shared__ uint64_t s_w1, s_n, s_qy;
     __shared__ uint64_t s_slot[NW];              // the waves' tail weights of a batch
     __shared__ uint64_t s_red[NW];
-    __shared__ int s_flag, s_y;
+    __shared__ int s_flag, s_y, s_idmax;
 
     ieee_mode_off();                             // NaN words drop out of the maxima
     const int tid = threadIdx.x, lane = tid % WAVE, wid = tid / WAVE;
@@ -542,6 +553,7 @@ __global__ __launch_bounds__(NTX, 4) void k_dense_row(RowArgs) {
         s_n = 0;
         s_flag = 0;
         s_y = -1;
+        s_idmax = -1;
     }
     const RowTop rt = row_top<1, false, NTX, COUNT_BATCH>(t, a, row, kk, s_pdyn, L, rd, rs);
 
@@ -551,6 +563,7 @@ __global__ __launch_bounds__(NTX, 4) void k_dense_row(RowArgs) {
     const uint64_t kb = s_top[kk - 1];
     const float vb = key_value(kb);
     const uint32_t wmin = cweight(vb, M, a.k1);  // the least weight of the top kk
+    const int ns = rs.nsmall;
     // (NS: the tables read, 4 or 8)
     auto totals = [&](auto NS_) {
         constexpr int NS = decltype(NS_)::value;
@@ -588,7 +601,16 @@ __global__ __launch_bounds__(NTX, 4) void k_dense_row(RowArgs) {
 #pragma unroll
                     for (int s = 0; s < NS; ++s) zq[s] += (uint64_t)(c[s] >> 16) * qn;
                 }
-            } else if (i >= HIST_OUT) {
+            } else if (i == 0) {
+                // zeros, and the listed values, which are put right below
+                const uint32_t w = cweight(0.0f, M, a.k1);
+                qp = qn = cweight(0.0f, guess, a.kT);
+                tie |= pos + neg > (uint32_t)ns && 0.0f < vb && w == wmin;
+                w1 += (uint64_t)(pos + neg) * w;
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+                    zq[s] += (uint64_t)((c[s] & 0xFFFFu) + (c[s] >> 16)) * qp;
+            } else {
                 // -2^9 and below: only if of no weight
                 if (pos || (neg && (cweight(-512.0f, M, a.k1) != 0u ||
                                     cweight(-512.0f, guess, a.kT) != 0u)))
@@ -599,15 +621,14 @@ __global__ __launch_bounds__(NTX, 4) void k_dense_row(RowArgs) {
             tab[i] = qp;
             tab[HIST_WORDS + i] = qn;
         }
-        const int ns = rs.nsmall;
-        if (tid == 0 && ns > HIST_SMALL) n += 1ull << 40;
-        for (int i = tid; i < min(ns, HIST_SMALL); i += NTX) {
+        for (int i = tid; i < ns; i += NTX) {
             const float l = __uint_as_float(s_small[i] << 16);
             const uint32_t w = cweight(l, M, a.k1);
-            w1 += w;
+            w1 += (uint64_t)w - cweight(0.0f, M, a.k1);
             tie |= l < vb && w == wmin;
             atomicAdd((unsigned long long*)&s_seg[s_small[i] >> 16],
-                      (unsigned long long)cweight(l, guess, a.kT));
+                      (unsigned long long)((uint64_t)cweight(l, guess, a.kT) -
+                                           cweight(0.0f, guess, a.kT)));
         }
         // two different logits of the list that share its last weight
         if (tid < kk) {
@@ -628,55 +649,86 @@ __global__ __launch_bounds__(NTX, 4) void k_dense_row(RowArgs) {
         }
         if (__ballot(tie) != 0ull && lane == 0) s_flag = 1;
     };
-    if (NB <= 4) totals(std::integral_constant<int, 4>());
-    else totals(std::integral_constant<int, ROW_BATCHES>());
+    if (ns <= HIST_SMALL) {
+        if (NB <= 4) totals(std::integral_constant<int, 4>());
+        else totals(std::integral_constant<int, ROW_BATCHES>());
+    }
     // x_1..x_kk by (w1 desc, id asc): ranks among the top kk by logit
     if (tid < kk) {
         const uint32_t w = cweight(key_value(s_top[tid]), M, a.k1);
         s_rk[tid] = ((uint64_t)w << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)key_id(s_top[tid]));
+        if (w == wmin) atomicMax(&s_idmax, key_id(s_top[tid]));
     }
     __syncthreads();
-    bool counted = s_n == (uint64_t)(NB * NTX) * (EBATCH * 8);
-    if (!s_flag && counted) {                    // (uncounted values may tie unseen)
-        if (tid < kk) {
-            const uint64_t k = s_rk[tid];
-            int rk = 0;
-            for (int q = 0; q < kk; ++q) rk += (int)(s_rk[q] > k);
-            s_x[rk] = s_top[tid];
-            s_xw[rk] = (uint32_t)(k >> 32);
-        }
-    } else {
-        ranks_by_weight<1, NTX>(rd.base, V, M, a.k1, kk, s_top, s_rk, s_x, s_xw, s_red);
-    }
-    __syncthreads();
-    const float ref_t = key_value(s_x[m]);
-    if (tid == 0 && !(ref_t > -INFINITY)) atomicOr(t.err, 512);   // x_{m+1} is -inf
+    bool counted = ns <= HIST_SMALL && s_n == (uint64_t)(NB * NTX) * (EBATCH * 8);
     uint64_t S1 = s_w1;
-    if (!counted || ref_t != guess) {
-        // every element's own weights
-        counted = false;
-        S1 = 0;
-        for (int s = 0; s < NB; ++s) {
-            uint64_t w1 = 0, zq = 0;
-            uint4 next = load_row_vec<1>(rd.base, rd.vidx(s * EBATCH), V);
+    float ref_t = guess;
+    for (bool direct = !counted;;) {
+        if (direct) {
+            // every element's own weights, relative to M and to ref_t, and whether one
+            // past the top kk ties the last construction weight with a smaller id
+            const int idmax = s_idmax;
+            bool tie = false;
+            S1 = 0;
+            for (int s = 0; s < NB; ++s) {
+                uint64_t w1 = 0, zq = 0;
+                uint4 next = dload_vec<1>(rd.base, rd.vidx(s * EBATCH), V);
 #pragma unroll 1
-            for (int q = s * EBATCH; q < (s + 1) * EBATCH; ++q) {
-                const uint4 x = next;
-                const int e0 = rd.vidx(q) * 8;
-                if (q + 1 < (s + 1) * EBATCH) next = load_row_vec<1>(rd.base, rd.vidx(q + 1), V);
+                for (int q = s * EBATCH; q < (s + 1) * EBATCH; ++q) {
+                    const uint4 x = next;
+                    const int e0 = rd.vidx(q) * 8;
+                    if (q + 1 < (s + 1) * EBATCH)
+                        next = dload_vec<1>(rd.base, rd.vidx(q + 1), V);
+                    if (e0 >= V) continue;
+                    uint32_t hit = 0;
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const float l = elem<1>(x, k);
-                    w1 += (e0 + k < V) ? cweight_below(l, M, a.k1) : 0u;
-                    zq += (e0 + k < V) ? cweight(l, ref_t, a.kT) : 0u;
+                    for (int k = 0; k < 8; k += 2) {
+                        // (elements past V read as -inf: weight 0 on both counts)
+                        const float la = elem<1>(x, k), lb = elem<1>(x, k + 1);
+                        const uint32_t wa = cweight_below(la, M, a.k1);
+                        const uint32_t wb = cweight_below(lb, M, a.k1);
+                        w1 += (uint64_t)(wa + wb);
+                        zq += (uint64_t)(cweight(la, ref_t, a.kT) + cweight(lb, ref_t, a.kT));
+                        hit |= (uint32_t)(wa == wmin) << k;
+                        hit |= (uint32_t)(wb == wmin) << (k + 1);
+                    }
+                    if (hit) {
+#pragma unroll
+                        for (int k = 0; k < 8; ++k)
+                            tie |= ((hit >> k) & 1u) && e0 + k < idmax &&
+                                   logit_key(elem<1>(x, k), (uint32_t)(e0 + k)) < kb;
+                    }
                 }
+                S1 += block_sum_u64<NTX>(w1, s_red);
+                zq = block_sum_u64<NTX>(zq, s_red);
+                if (tid == 0) s_seg[s] = zq;
             }
-            S1 += block_sum_u64<NTX>(w1, s_red);
-            zq = block_sum_u64<NTX>(zq, s_red);
-            if (tid == 0) s_seg[s] = zq;
+            if (tid == 0) s_flag = 0;            // (what incomplete counts may have set)
+            __syncthreads();
+            if (__ballot(tie) != 0ull && lane == 0) s_flag = 1;
+            __syncthreads();
+            if (ref_t != guess) break;           // (the ranks are known)
+        }
+        if (!s_flag) {
+            if (tid < kk) {
+                const uint64_t k = s_rk[tid];
+                int rk = 0;
+                for (int q = 0; q < kk; ++q) rk += (int)(s_rk[q] > k);
+                s_x[rk] = s_top[tid];
+                s_xw[rk] = (uint32_t)(k >> 32);
+            }
+        } else {
+            ranks_by_weight<1, NTX>(rd.base, V, M, a.k1, kk, s_top, s_rk, s_x, s_xw, s_red);
         }
         __syncthreads();
+        const float ref = key_value(s_x[m]);
+        if (ref == guess) break;
+        // the guess of x_{m+1} was wrong (construction-weight ties): the sums again
+        ref_t = ref;
+        counted = false;
+        direct = true;
     }
+    if (tid == 0 && !(ref_t > -INFINITY)) atomicOr(t.err, 512);   // x_{m+1} is -inf
 
     // ---- Y ~ q~_T: the leads leave the tail; the batch that holds
     //      t = floor(U64 Zq / 2^64), then the 64-vector slot, then the token
@@ -715,8 +767,9 @@ __global__ __launch_bounds__(NTX, 4) void k_dense_row(RowArgs) {
             const uint32_t* w = &r[e].x;
             sq[e] = 0;
             if (counted) {
-                // the value's weight from the tables (word 0 is 0: values below
-                // 2^-11 follow; past the row NaN words, of no weight)
+                // the value's weight from the tables (word 0: that of zeros, which
+                // other values below 2^-11 put right; past the row NaN words, of
+                // no weight)
                 hist_u16x2 least = {0xFFFF, 0xFFFF};
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
@@ -728,13 +781,15 @@ __global__ __launch_bounds__(NTX, 4) void k_dense_row(RowArgs) {
                     sq[e] += (uint64_t)(*(const uint32_t*)((const uint8_t*)tab + i.x) +
                                         *(const uint32_t*)((const uint8_t*)tab + i.y));
                 }
-                if (__ballot(least.x == 0 || least.y == 0) != 0ull) {
+                if (__ballot(least.x == 0 || least.y == 0) != 0ull &&
+                    __ballot(hist_has_small(hist_least_less_1(r[e]))) != 0ull) {
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
                         for (int k = 0; k < 2; ++k) {
                             const uint32_t bits = (w[c] >> (16 * k)) & 0xFFFFu;
-                            if ((bits & 0x7FFFu) <= HIST_BASE)
-                                sq[e] += cweight(__uint_as_float(bits << 16), ref_t, a.kT);
+                            if ((bits & 0x7FFFu) - 1u < HIST_BASE)
+                                sq[e] += (uint64_t)cweight(__uint_as_float(bits << 16), ref_t, a.kT) -
+                                         tab[0];
                         }
                 }
             } else {

@@ -624,7 +624,7 @@ __device__ __forceinline__ void select_block(const TreeDev& t, const LevelArgs& 
                     else s_keys[pos] = logit_key(v, (uint32_t)id);
                 }
             },
-            s_redi, s_scr);
+            &s_cnt, s_redi, s_scr);
         cnt = min(fallback_count(&s_cnt), CAPC);
     }
 
@@ -685,6 +685,7 @@ __global__ __launch_bounds__(NTB, 4) void k_expand_row(RowArgs) {
         // overflow), no value of 2^9 or more, and none at or below -2^9 unless
         // its weight is 0
         uint64_t w = 0, n = 0;
+        const uint64_t w0 = cweight(0.0f, rt.vmax, a.k1);
         const uint32_t* tab = (const uint32_t*)s_tab;
         for (int i = tid; i < HIST_WORDS; i += NTB) {
             const uint32_t c0 = tab[i], c1v = tab[HIST_WORDS + i];
@@ -693,14 +694,16 @@ __global__ __launch_bounds__(NTB, 4) void k_expand_row(RowArgs) {
             if (i >= 1 && i < HIST_OUT) {
                 const float l = hist_value(i);
                 w += (uint64_t)pos * cweight(l, rt.vmax, a.k1) + (uint64_t)neg * cweight(-l, rt.vmax, a.k1);
-            } else if (i >= HIST_OUT) {
+            } else if (i == 0) {
+                w += (uint64_t)(pos + neg) * w0;     // (the listed ones put right below)
+            } else {
                 if (pos != 0 || (neg != 0 && cweight(-512.0f, rt.vmax, a.k1) != 0u)) n += 1ull << 40;
             }
         }
         const int ns = rs.nsmall;
         if (ns > HIST_SMALL) n += 1ull << 40;
         for (int i = tid; i < min(ns, HIST_SMALL); i += NTB)
-            w += cweight(__uint_as_float(s_small[i] << 16), rt.vmax, a.k1);
+            w += cweight(__uint_as_float(s_small[i] << 16), rt.vmax, a.k1) - w0;
         w = wave_sum_u64(w);
         n = wave_sum_u64(n);
         if (lane == 0) {

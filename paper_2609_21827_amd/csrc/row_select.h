@@ -244,21 +244,21 @@ __device__ __forceinline__ void count_digit(int* s_hist, uint32_t d, bool in) {
 // push(v, id) records an element.  It re-reads the range, four vectors at a
 // time, once per pass.
 //
-// bf16: count the elements whose code lies above the threshold code h; if the
-// nsel-th largest element has code h, x = h; if it lies above h and the
-// elements above h fit (at most cap), take those.  Otherwise, and for fp32, x
+// bf16: count the elements whose code lies above the threshold code h, and those
+// at it; if the nsel-th largest element has code h, x = h; if it lies above h
+// and the elements above h fit (at most cap), take those.  Otherwise, and for fp32, x
 // = the nsel-th largest code (bf16: the 16-bit order code, fp32: the 32-bit
 // one) by its digits from the top, 8 bits a pass, each from a histogram of
 // the elements that share the digits before.  Then everything above x and the
 // smallest ids among those at x (ranks of the ties in id order from per-wave
-// counts and wave scans).  By bisection of the 64-bit key, in 64 passes, a level of
+// counts and wave scans), until `taken` says that nsel are pushed.  By bisection of the 64-bit key, in 64 passes, a level of
 // 1000 bf16 elements at support 128 took 197 us, of 2500 fp32 elements at
 // support 1024 180; so they take 33 and 53.
 //
 // s_scr holds max(256, NQ * NT / WAVE) ints.  Ends with a barrier.
 template <int DT, int NT, int NQ, typename Push>
 __device__ void exact_select_fallback(const char* base, int V, int vfirst, uint32_t h, int nsel,
-                                      int cap, Push push, int* s_redi, int* s_scr) {
+                                      int cap, Push push, int* taken, int* s_redi, int* s_scr) {
     constexpr int VEC = DT ? 8 : 4;
     constexpr int NW = NT / WAVE;
     static_assert(NQ % 4 == 0 && NQ <= 64, "re-read in groups of four vectors");
@@ -279,10 +279,10 @@ __device__ void exact_select_fallback(const char* base, int V, int vfirst, uint3
         for (int q = 0; q < 4; ++q) w[q] = load_row_vec<DT>(base, vf + (q0 + q) * NT + tid, V);
     };
     auto code = [](float v) { return DT ? ord32(v) >> 16 : ord32(v); };
-    uint32_t x = h;                              // the nsel-th largest code
-    int need = 0;                                // elements to take at it
-    bool found = false;
-    if (DT) {
+    // (past the row bf16 elements read as code 0, below every x; fp32 ones as -inf)
+    auto inside = [&](int e) { return DT || e < V; };
+    // elements at x in every vector, per wave; and those above it, in all
+    auto count_ties = [&](uint32_t x) {
         int ngt = 0;
 #pragma unroll 1
         for (int q0 = 0; q0 < nq; q0 += 4) {
@@ -291,16 +291,30 @@ __device__ void exact_select_fallback(const char* base, int V, int vfirst, uint3
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int e0 = (vfirst + (q0 + q) * NT + tid) * VEC;
+                int nt = 0;
 #pragma unroll
-                for (int k = 0; k < VEC; ++k)
-                    ngt += (e0 + k < V && code(elem<DT>(w[q], k)) > h) ? 1 : 0;
+                for (int k = 0; k < VEC; ++k) {
+                    const uint32_t c = code(elem<DT>(w[q], k));
+                    ngt += (int)(inside(e0 + k) && c > x);
+                    nt += (int)(inside(e0 + k) && c == x);
+                }
+                const int tot = wave_sum_i32(nt);
+                if (lane == 0) s_tie[q0 + q][wid] = tot;
             }
         }
-        ngt = block_sum_i32<NT>(ngt, s_redi);
+        return block_sum_i32<NT>(ngt, s_redi);
+    };
+    uint32_t x = h;                              // the nsel-th largest code
+    int need = 0;                                // elements to take at it
+    bool found = false;
+    if (DT) {
+        x = max(h, 1u);
+        const int ngt = count_ties(x);
         need = nsel - ngt;
         found = need > 0;
         if (!found && ngt <= cap) {
             need = 0;                            // (all above h, none at it)
+            nsel = ngt;
             found = true;
         }
     }
@@ -323,7 +337,7 @@ __device__ void exact_select_fallback(const char* base, int V, int vfirst, uint3
                     for (int k = 0; k < VEC; ++k) {
                         const uint32_t c = code(elem<DT>(w[q], k));
                         count_digit(s_scr, (c >> sh) & 255u,
-                                    e0 + k < V && ((c ^ x) >> sh) >> 8 == 0u);
+                                    (DT ? c != 0u : e0 + k < V) && ((c ^ x) >> sh) >> 8 == 0u);
                     }
                 }
             }
@@ -353,29 +367,15 @@ __device__ void exact_select_fallback(const char* base, int V, int vfirst, uint3
             need = (int)lane_u32((uint32_t)left, l);
         }
         __syncthreads();
+        (void)count_ties(x);
     }
-    // ties at x, in id order: vector q, then thread, then element
-    if (need > 0) {
-#pragma unroll 1
-        for (int q0 = 0; q0 < nq; q0 += 4) {
-            uint4 w[4];
-            group(q0, w);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int e0 = (vfirst + (q0 + q) * NT + tid) * VEC;
-                int nt = 0;
-#pragma unroll
-                for (int k = 0; k < VEC; ++k)
-                    nt += (e0 + k < V && code(elem<DT>(w[q], k)) == x) ? 1 : 0;
-                const int tot = wave_sum_i32(nt);
-                if (lane == 0) s_tie[q0 + q][wid] = tot;
-            }
-        }
-        __syncthreads();
-    }
+    __syncthreads();
+    // ties at x are taken in id order: vector q, then thread, then element
     int prior = 0;                               // ties in the vectors before q, all threads
 #pragma unroll 1
     for (int q0 = 0; q0 < nq; q0 += 4) {
+        const int n = __hip_atomic_load(taken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (__builtin_amdgcn_readfirstlane(n) >= nsel) break;
         uint4 w[4];
         group(q0, w);
 #pragma unroll
@@ -386,7 +386,7 @@ __device__ void exact_select_fallback(const char* base, int V, int vfirst, uint3
                 int nt = 0;
 #pragma unroll
                 for (int k = 0; k < VEC; ++k)
-                    nt += (e0 + k < V && code(elem<DT>(w[q], k)) == x) ? 1 : 0;
+                    nt += (int)(inside(e0 + k) && code(elem<DT>(w[q], k)) == x);
                 rk = prior + wave_excl_scan(nt);
 #pragma unroll
                 for (int ww = 0; ww < NW; ++ww) {
@@ -398,7 +398,7 @@ __device__ void exact_select_fallback(const char* base, int V, int vfirst, uint3
             for (int k = 0; k < VEC; ++k) {
                 const float v = elem<DT>(w[q], k);
                 const uint32_t cd = code(v);
-                if (e0 + k < V) {
+                if (inside(e0 + k)) {
                     if (cd > x) {
                         push(v, e0 + k);
                     } else if (cd == x) {
@@ -859,7 +859,7 @@ __device__ __forceinline__ RowTop row_top(const TreeDev& t, const LevelArgs& a, 
                 const int pos = atomicAdd(cntp, 1);
                 if (pos < CC) s_keys[pos] = logit_key(v, (uint32_t)id);
             },
-            rs.red, (int*)(lds + L.start));
+            &rs.cnt, rs.red, (int*)(lds + L.start));
         cnt = min(fallback_count(&rs.cnt), CC);
     }
 

@@ -59,6 +59,17 @@ def _shape(kind, x, rng):
         x *= 1e-5
     elif kind == "large":                   # the top of the row above 2^9
         x = x * 3 + 515
+    elif kind == "zeros":                   # a padded vocabulary's columns, and scattered ones
+        x[:, V - V // 16:] = 0.0
+        x[rng.random((n, V)) < 0.05] = -0.0
+    elif kind == "zeros_small":             # both, and values below 2^-11 that are listed
+        x[rng.random((n, V)) < 0.05] = 0.0
+        x[:, rng.integers(0, V, 60)] = 1e-4
+        x[:, rng.integers(0, V, 60)] = -2e-5
+    elif kind == "half_zeros":              # lanes that meet on a word
+        x[rng.random((n, V)) < 0.5] = 0.0
+    elif kind == "few_values":
+        x = np.round(x / 3) * 3
     elif kind == "zero_cross":              # the support spans zero
         x = x * 0.01
     return x
@@ -301,3 +312,14 @@ def test_dense_sizes(dev, dtype, V):
 ])
 def test_short_rows(dev, kind, dtype, V, support, env):
     _check(V, dtype, support, kind, 17, depth=2, env=env)
+
+
+# rows that the counts of the dense and the whole-vocabulary kernels cover only
+# in part or not at all, on one, five and eight batches of 32768
+@pytest.mark.parametrize("kind", ["zeros", "zeros_small", "half_zeros", "few_values", "small", "large",
+                                  "edges", "const"])
+@pytest.mark.parametrize("V,support,full", [(9001, 0, False), (140001, 0, False), (262143, 0, False),
+                                            (9001, 64, True), (140001, 300, True)])
+def test_uncounted_rows(dev, kind, V, support, full):
+    _check(V, "bf16", support, kind, 18, m=2, depth=2, T=0.9, full=full,
+           env={"RHEO_EXPAND_ROW": "1"})

@@ -139,3 +139,27 @@ def test_short_rows(dev, dtype, V, ref, support):
     us = {v: Levels(5, v, 8, 4, support, dtype=dtype).time() for v in (V, ref)}
     print(us)
     assert us[V] < 3 * us[ref]
+
+
+def _columns(n):
+    def shape(x):
+        x[..., x.shape[-1] - n:] = 0
+    return shape
+
+
+def _share(p):
+    def shape(x):
+        x[torch.rand(x.shape, device=x.device) < p] = 0
+    return shape
+
+
+# rows with zeros (a padded vocabulary's columns; scattered), whose values the counts
+# list or leave out, against rows without: 300 columns took 17 times as long in dense
+# mode, half zeros 16 times
+@pytest.mark.parametrize("B,V,support,full", [(64, 128256, 0, False), (8, 32000, 0, False),
+                                              (32, 128256, 128, True)])
+@pytest.mark.parametrize("shape,bound", [(_columns(300), 1.4), (_share(0.02), 2.2), (_share(0.5), 4.5)])
+def test_rows_with_zeros(dev, B, V, support, full, shape, bound):
+    us = [Levels(B, V, 8, 3, support, shape=s, full=full).time() for s in (None, shape)]
+    print(us)
+    assert us[1] < bound * us[0]
