@@ -105,16 +105,31 @@ int check_T(float T) {
     return RHEO_OK;
 }
 
-// Dense bf16 levels run one block per row (k_dense_row) but for two kinds that
-// the chunked kernels run faster: a few long rows, which share a row over many
-// blocks (whole steps, by rows against chunked: 7 rows of 130670 211 and 192
-// us, 32 of 128133 383 and 341, 48 of 250708 510 and 498; 9 of 34571 116 and
-// 134), and many short rows, whose own elements are fewer than the values the
-// counts have to be weighted for (520 rows of 12902 442 and 380 us, 1200 of
-// 18349 372 and 348, 55 of 11720 186 and 188).
+// Which kernels a dense bf16 level runs: one block per row (k_dense_row) or
+// the three chunked kernels.  us per level, by rows / chunked:
+//
+//   V        8 rows    64        96        256       512        1024
+//   8192     28 / 28   28 / 28   27 / 28   28 / 29   34 / 32    63 / 41
+//   16384    27 / 26   27 / 26   27 / 27   28 / 28   34 / 32    66 / 42
+//   24576    27 / 28   27 / 28   27 / 29   27 / 31   34 / 41    65 / 62
+//   32768    25 / 27   25 / 27   25 / 28   28 / 32   33 / 43    64 / 62
+//   49152    30 / 27   31 / 28   30 / 30   32 / 37   44 / 52    78 / 79
+//   65536    29 / 27   28 / 28   28 / 31   32 / 42   44 / 62    79 / 98
+//   131072   35 / 28   35 / 32   37 / 38   40 / 62   59 / 100   105 / 175
+//   262143   49 / 31   52 / 45   53 / 58   55 / 114  107 / 197
+//
+// While every row has a compute unit of its own (256 rows), the level by rows
+// takes as long as one row, and the chunked one as long as all of them over the
+// whole chip: both in proportion to V past 27 us, and equal at some 80 rows
+// whatever V.  A row of one batch (32768) adds nothing to the chains on either
+// side; by rows is then one launch for three.  With two blocks a unit (512 rows)
+// and more rounds of them, each costs its chain of some 30 us again, which the
+// chunked kernels' time for the elements has to exceed.
 bool dense_by_rows(const TreeDev& d, int P) {
     const int rows = d.B * P;
-    return d.V <= 65536 ? rows < 256 || d.V >= 24576 : rows >= 64;
+    if (rows > 512) return d.V >= 40960;
+    if (rows > 256) return d.V >= 20480;
+    return d.V <= 32768 || rows >= 80;
 }
 
 // Every call of one step takes the step's temperature and key: the stored
