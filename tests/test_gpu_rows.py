@@ -283,20 +283,32 @@ def test_prune_piles(dev, kind, K, depth):
             assert list(tok[b]) == [-1] + [n["token"][u] for u in order[1:R + 1]], (b, R)
 
 
-# dense mode's row kernel: the counts' edges as above, ties of the last listed
-# construction weight, the draw's batch and slot, the longest row
+# dense mode on both of its routes, one block a row (bf16: on one, two and more
+# batches of 32768, up to the longest row) and the chunked kernels: the counts'
+# edges as above, ties of the last listed construction weight, the draw's batch
+# and slot
+@pytest.mark.parametrize("row", ["1", "0"])
 @pytest.mark.parametrize("kind", ["plain", "edges", "small", "large", "const", "sorted", "sorted_up",
                                   "ties", "signed_zeros", "zero_cross"])
 @pytest.mark.parametrize("V,m,K,T,method", [(9001, 1, 5, 1.0, "rheo"), (32769, 0, 12, 0.7, "rrsw"),
-                                            (70000, 3, 4, 1.5, "topk")])
-def test_dense_rows(dev, kind, V, m, K, T, method):
-    _check(V, "bf16", 0, kind, 14, m=m, K=K, depth=2, T=T, method=method)
+                                            (70000, 3, 4, 1.5, "topk"), (163841, 2, 4, 1.0, "rheo")])
+def test_dense_rows(dev, kind, V, m, K, T, method, row):
+    _check(V, "bf16", 0, kind, 14, m=m, K=K, depth=2, T=T, method=method,
+           env={"RHEO_EXPAND_ROW": row})
 
 
+@pytest.mark.parametrize("row", ["1", "0"])
 @pytest.mark.parametrize("dtype,V", [("bf16", 32760), ("bf16", 32768), ("bf16", 131073),
                                      ("bf16", 262143), ("bf16", 300), ("f32", 5003)])
-def test_dense_sizes(dev, dtype, V):
-    _check(V, dtype, 0, "plain", 15, depth=2)
+def test_dense_sizes(dev, dtype, V, row):
+    _check(V, dtype, 0, "plain", 15, depth=2, env={"RHEO_EXPAND_ROW": row})
+
+
+# the route that the sizes choose: few rows of one batch and a little more, by rows
+# and chunked
+@pytest.mark.parametrize("V", [32768, 32776])
+def test_dense_route(dev, V):
+    _check(V, "bf16", 0, "plain", 16, depth=3)
 
 
 # rows of hardly more elements than the support, of more elements than a block
