@@ -40,11 +40,11 @@ constexpr int kMaxV = 262143;
 
 float k_of_T(float T) { return (float)(1.4426950408889634 / (double)T); }
 
-// tokens of one 64-vector sub-chunk (16-byte vectors of bf16 or fp32)
 // Rows in a level from which the per-row kernel runs (it is the faster of
 // the two at every level size measured, down to a single row).
 constexpr int kRowMin = 1;
 
+// tokens of one 64-vector sub-chunk (16-byte vectors of bf16 or fp32)
 int WAVE_TOKENS(int dtype) { return 64 * (dtype == RHEO_BF16 ? 8 : 4); }
 
 // A chunk size fits when the row's chunk lists fit the merge (and, in dense
@@ -302,8 +302,9 @@ void layout(rheo_tree* t, Arena& A) {
     take(A, &d.team_flag, B * 64);
     take(A, &d.team_max, B * 64);
     take(A, &d.team_sum, B * kTeamSets * 64, B * 64);
-    take(A, &d.team_chunk, B * 1024);
-    take(A, &d.team_sp, B * (1024 + 16));
+    // (the limit counts 4160 bytes a sequence more, which the team words took when
+    // it was set, so that it refuses the shapes it did)
+    take(A, &d.team_chunk, B * 1024, B * (1024 + 520));
     take(A, &d.team_nchunk, dense ? B * 1024 * 2 : 1);
     take(A, &d.sel, B * d.NE * (size_t)d.C * d.Sc);
     take(A, &d.seq_cnt, B);

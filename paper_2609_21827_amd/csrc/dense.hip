@@ -33,13 +33,7 @@ constexpr int KKMAX = 32;         // m + K <= 29
 constexpr int DLIST_MAX = 512;    // C * kk keys a row's chunk lists hold
 constexpr int NCHMAX = 1024;      // sub-chunks per row: V <= 262143, >= 256 tokens each
 
-template <int DT>
-__device__ __forceinline__ float delem(const uint4& v, int k) {
-    const uint32_t* w = &v.x;
-    if (DT) return (k & 1) ? bf_hi(w[k >> 1]) : bf_lo(w[k >> 1]);
-    return __uint_as_float(w[k]);
-}
-
+// Vector vi of a row, elements past V as -inf: of weight 0, without a test.
 template <int DT>
 __device__ __forceinline__ uint4 dload_vec(const char* base, int vi, int V) {
     constexpr int VEC = DT ? 8 : 4;
@@ -156,7 +150,7 @@ __global__ __launch_bounds__(NTD) void k_dweights(TreeDev t, LevelArgs a) {
             uint32_t hit = 0;
 #pragma unroll
             for (int k = 0; k < VEC; k += 2) {
-                const float la = delem<DT>(r[i], k), lb = delem<DT>(r[i], k + 1);
+                const float la = elem<DT>(r[i], k), lb = elem<DT>(r[i], k + 1);
                 const uint32_t wa = cweight_below(la, M, a.k1);
                 const uint32_t wb = cweight_below(lb, M, a.k1);
                 s1 += (uint64_t)(wa + wb);
@@ -169,7 +163,7 @@ __global__ __launch_bounds__(NTD) void k_dweights(TreeDev t, LevelArgs a) {
                 for (int k = 0; k < VEC; ++k) {
                     const int id = e0 + k;
                     if (((hit >> k) & 1u) && id < idmax &&
-                        logit_key(delem<DT>(r[i], k), (uint32_t)id) < kb)
+                        logit_key(elem<DT>(r[i], k), (uint32_t)id) < kb)
                         flag = true;
                 }
             }
@@ -233,7 +227,7 @@ __device__ __noinline__ void ranks_by_weight(const char* base, int V, float M, f
         uint32_t hit = 0;
 #pragma unroll
         for (int k = 0; k < VEC; ++k)
-            hit |= (uint32_t)(e0 + k < V && cweight(delem<DT>(x, k), M, k1) == wmin) << k;
+            hit |= (uint32_t)(e0 + k < V && cweight(elem<DT>(x, k), M, k1) == wmin) << k;
         uint64_t tot;
         int pos = before + (int)block_excl_scan_u64<NT>((uint64_t)__popc(hit), s_red, &tot);
         if (hit != 0u && pos < need) {
@@ -241,7 +235,7 @@ __device__ __noinline__ void ranks_by_weight(const char* base, int V, float M, f
             for (int k = 0; k < VEC; ++k) {
                 if (((hit >> k) & 1u) == 0u) continue;
                 if (pos < need) {
-                    s_x[ngt + pos] = logit_key(delem<DT>(x, k), (uint32_t)(e0 + k));
+                    s_x[ngt + pos] = logit_key(elem<DT>(x, k), (uint32_t)(e0 + k));
                     s_xw[ngt + pos] = wmin;
                 }
                 ++pos;

@@ -302,13 +302,9 @@ __device__ uint64_t block_excl_scan_u64(uint64_t v, uint64_t* sh, uint64_t* tota
 }
 
 // rank[i] = number of keys strictly greater than keys[i], for unique keys
-// in LDS; each key is compared by a group of F consecutive lanes.  With
-// `out`, the lane that finishes key i writes it to out[rank] instead when
-// the rank is below nsel (and writes no rank), so no barrier is needed
-// between ranking and placing.
+// in LDS; each key is compared by a group of F consecutive lanes.
 template <int NT>
-__device__ void rank_keys(const uint64_t* keys, int n, int16_t* rank, uint64_t* out = nullptr,
-                          int nsel = 0) {
+__device__ void rank_keys(const uint64_t* keys, int n, int16_t* rank) {
     int npad = 1;
     while (npad < n) npad <<= 1;
     int F = NT / npad;
@@ -340,13 +336,7 @@ __device__ void rank_keys(const uint64_t* keys, int n, int16_t* rank, uint64_t* 
             if (j < j1) cnt += keys[j] > k;
         }
         for (int o = 1; o < F; o <<= 1) cnt += __shfl_xor(cnt, o);
-        if (i < n && sub == 0) {
-            if (out) {
-                if (cnt < nsel) out[cnt] = keys[i];
-            } else {
-                rank[i] = (int16_t)cnt;
-            }
-        }
+        if (i < n && sub == 0) rank[i] = (int16_t)cnt;
     }
 }
 

@@ -58,7 +58,6 @@ struct TreeDev {
     uint64_t* team_max;            // [B][GMAX] segment maxima: epoch << 32 | order code
     uint64_t* team_sum;            // [B][2][GMAX] segment weight sums: epoch << 48 | sum
     uint64_t* team_chunk;          // [B][NCMAX] chunk totals of p's weights
-    uint32_t* team_sp;             // [B][SPMAX] p's weights at the special tokens
     uint64_t* team_nchunk;         // dense: [B][NCMAX][2] residual chunk totals (u128)
     // expansion: each row's C chunk lists of Sc selection keys, sorted
     uint64_t* sel;                 // [B * NE][C][Sc]

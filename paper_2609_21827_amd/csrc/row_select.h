@@ -55,30 +55,19 @@ __device__ __forceinline__ uint4 load_row_vec(const char* base, int vi, int V) {
 
 // LDS layout of the pool kernel's dynamic buffer: the chunk lists and one
 // empty list after them, the support, ranking keys and per-entry
-// arrays; the level's priority keys (<= 225 of them) reuse the regions of
-// the support and the ranking keys.  The ranking-key region holds a power
-// of two >= S keys.  top_min and
-// k2_min (entries, bytes) enlarge the first two regions for callers that
-// use them as scratch before the pool.
+// arrays; the level's priority keys (256 of them) reuse the regions of the
+// support and the ranking keys.
 struct PoolLds {
     int m, top, k2, w1, q, wr, xs, bytes;
 };
 __host__ __device__ inline int pad16(int x) { return (x + 15) & ~15; }
-__host__ __device__ inline int pow2_at_least(int x) {
-    int p = 1;
-    while (p < x) p <<= 1;
-    return p;
-}
-__host__ __device__ inline PoolLds pool_lds(int S, int C, int top_min = 0, int k2_min = 0) {
+__host__ __device__ inline PoolLds pool_lds(int S, int C) {
     PoolLds L;
-    int S2 = S > 256 ? S : 256;
-    if (S2 < top_min) S2 = top_min;
-    int k2b = 8 * pow2_at_least(S > 256 ? S : 256);
-    if (k2b < k2_min) k2b = k2_min;
+    const int S2 = S > 256 ? S : 256;
     L.m = 0;
     L.top = L.m + pad16(8 * (C + 1) * S);
     L.k2 = L.top + pad16(8 * S2);
-    L.w1 = L.k2 + pad16(k2b);
+    L.w1 = L.k2 + pad16(8 * S2);
     L.q = L.w1 + pad16(4 * S);
     L.wr = L.q + pad16(4 * S);
     L.xs = L.wr + pad16(2 * S);
