@@ -20,12 +20,13 @@
 //
 // Lanes that meet on a word wait for each other, some five cycles each, so rows of
 // few values (512 constant rows of 128256: 553 us a level, counted) are better
-// not counted: eight probes a batch tell how many lanes share a word with the
-// first.  160 of 512 (a value that half of the row has) mark the list as full,
+// not counted: four probes a batch tell how many lanes share a word with the
+// first.  96 of 256 (a value that half of the row has) mark the list as full,
 // which leaves the row to the caller's pass over its elements, and the batch is
-// left out; at 64 a batch is left out if the list is full already.  (A quarter of
-// the row at one value reaches 128 at most, and counting is the faster there:
-// logits rounded to halves 80 us a level, by their elements 115.)
+// left out; at 48 a batch is left out if the list is full already.  (A quarter of
+// the row at one value reaches 64 at most, and counting is the faster there:
+// logits rounded to halves 80 us a level, by their elements 115.)  Eight probes
+// cost a common row 2 % of its level.
 #pragma once
 
 #include "rheo_device.h"
@@ -70,14 +71,14 @@ __device__ __forceinline__ void hist_add(uint8_t* tables, uint32_t at, const uin
     const hist_u16x2 off = {(unsigned short)at, (unsigned short)at};
     int meet = 0;
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
+    for (int p = 0; p < 2; ++p) {
         const hist_u16x2 i = __builtin_elementwise_min(
-            __builtin_elementwise_sub_sat(hist_mags((&r[p * NVB / 4].x)[p]), base), lim);
+            __builtin_elementwise_sub_sat(hist_mags((&r[p * NVB / 2].x)[2 * p]), base), lim);
         const uint32_t lo = i.x, hi = i.y;
         meet += __popcll(__ballot(lo == lane_u32(lo, 0))) + __popcll(__ballot(hi == lane_u32(hi, 0)));
     }
-    if (meet >= WAVE) {
-        if (meet >= 5 * WAVE / 2) {
+    if (meet >= 3 * WAVE / 4) {
+        if (meet >= 3 * WAVE / 2) {
             if (threadIdx.x % WAVE == 0) atomicAdd(small_n, HIST_SMALL + 1);
             return;
         }
