@@ -650,7 +650,15 @@ __device__ __forceinline__ RowTop row_top(const TreeDev& t, const LevelArgs& a, 
 #pragma unroll
         for (int e = 0; e < EBATCH; e += 2) {
             const uint32_t lo = vec_max_raw<DT>(r[e]), hi = vec_max_raw<DT>(r[e + 1]);
-            const rs_ushort2 cq = bf16x2_codes(__builtin_amdgcn_perm(hi, lo, 0x07060302u));
+            rs_ushort2 cq = bf16x2_codes(__builtin_amdgcn_perm(hi, lo, 0x07060302u));
+            // fp32 vectors past the row hold -inf: code 0 instead, as bf16 ones have,
+            // or short rows would list thousands of them as candidates (400 to 900
+            // elements at support 128: 29 us a level against 16)
+            if (DT == 0 && NTB * (bt + 1) * EBATCH > rd.NVF) {
+                const int q = bt * EBATCH + e;
+                if (rd.vidx(q) * VEC >= V) cq.x = 0;
+                if (rd.vidx(q + 1) * VEC >= V) cq.y = 0;
+            }
             cw[e / 2] = __builtin_bit_cast(uint32_t, cq);
             if (LS) p2 = __builtin_elementwise_max(p2, __builtin_elementwise_min(p1, cq));
             p1 = __builtin_elementwise_max(p1, cq);
@@ -697,7 +705,7 @@ __device__ __forceinline__ RowTop row_top(const TreeDev& t, const LevelArgs& a, 
 
     // ---- threshold: every wave's ceil(S / NW)-th largest offered code, and the
     //      least of them: at least S vectors reach it.  (Vectors past the row
-    //      have code 0 (bf16) or that of -inf, at most every element's.)
+    //      have code 0, below every element's.)
     const uint32_t c1 = p1.x, c2 = p1.y, c3 = p2.x, c4 = p2.y;
     const uint32_t wh = wave_kth_code<LS>(c1, c2, c3, c4, (S + NW - 1) / NW);
     const uint32_t wm = wave_max_u32(max(c1, c2));
