@@ -109,6 +109,7 @@ int check_T(float T) {
 // the three chunked kernels.  us per level, by rows / chunked:
 //
 //   V        8 rows    64        96        256       512        1024
+//   2048     30 / 29   29 / 29   29 / 29   30 / 30   36 / 33    68 / 41
 //   8192     28 / 28   28 / 28   27 / 28   28 / 29   34 / 32    63 / 41
 //   16384    27 / 26   27 / 26   27 / 27   28 / 28   34 / 32    66 / 42
 //   24576    27 / 28   27 / 28   27 / 29   27 / 31   34 / 41    65 / 62
@@ -122,14 +123,15 @@ int check_T(float T) {
 // takes as long as one row, and the chunked one as long as all of them over the
 // whole chip: both in proportion to V past 27 us, and equal at some 80 rows
 // whatever V.  A row of one batch (32768) adds nothing to the chains on either
-// side; by rows is then one launch for three.  With two blocks a unit (512 rows)
+// side; by rows is then one launch for three (but the values' tables take longer
+// than the elements of the shortest rows).  With two blocks a unit (512 rows)
 // and more rounds of them, each costs its chain of some 30 us again, which the
 // chunked kernels' time for the elements has to exceed.
 bool dense_by_rows(const TreeDev& d, int P) {
     const int rows = d.B * P;
     if (rows > 512) return d.V >= 40960;
     if (rows > 256) return d.V >= 20480;
-    return d.V <= 32768 || rows >= 80;
+    return d.V <= 32768 ? d.V >= 4096 : rows >= 80;
 }
 
 // Every call of one step takes the step's temperature and key: the stored
