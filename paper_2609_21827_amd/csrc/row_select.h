@@ -862,12 +862,15 @@ __device__ __forceinline__ RowTop row_top(const TreeDev& t, const LevelArgs& a, 
 
     // ---- the support: the top S candidates in (logit desc, id asc) order ----
     // Bins linear in the value over [tau, the row maximum] (a monotone map:
-    // one rounded subtraction, one rounded product); from the least finite
-    // candidate up when tau is -inf (short rows: by the order code's high bits
-    // instead, an octave a bin, a level of 2000 elements, all of them candidates at
-    // support 512, took 85 us; so it takes 18).
-    float low = tau;
-    if (!(tau > -INFINITY)) {
+    // one rounded subtraction, one rounded product).  When tau is -inf (short
+    // rows, few finite logits), the upper half of the bins from the least finite
+    // candidate up and the lower half linear in the id for those at -inf: by the
+    // order code's high bits, an octave a bin, a level of 2000 elements, all of
+    // them candidates at support 512, took 85 us, so it takes 18; with all of -inf
+    // in one bin one of 1700, nine tenths masked, 100, so 20.
+    const bool bounded = tau > -INFINITY;
+    float low = tau, off = 0.0f;
+    if (!bounded) {
         float neg = -INFINITY;                   // the largest negated value
 #pragma unroll
         for (int r = 0; r < KPT; ++r) {
@@ -881,8 +884,10 @@ __device__ __forceinline__ RowTop row_top(const TreeDev& t, const LevelArgs& a, 
 #pragma unroll
         for (int w = 0; w < NW; ++w) neg = fmaxf(neg, __int_as_float(rs.red[w]));
         low = fminf(-neg, vmax);
+        off = (float)(NBIN / 2);
     }
-    const float scale = (float)NBIN / (vmax - low);
+    const float scale = fminf(((float)NBIN - off) / (vmax - low), 3e38f);
+    const float per_id = (float)(NBIN / 2) / (float)V;
     uint64_t key[KPT];
     int kbin[KPT], kslot[KPT];
 #pragma unroll
@@ -893,7 +898,9 @@ __device__ __forceinline__ RowTop row_top(const TreeDev& t, const LevelArgs& a, 
         kslot[r] = 0;
         if (i < cnt) {
             key[r] = s_keys[i];
-            const float x = (key_value(key[r]) - low) * scale;   // (NaN: bin 0)
+            float x = (key_value(key[r]) - low) * scale + off;
+            if (!bounded && !(key_value(key[r]) > -INFINITY))
+                x = fminf(off - 1.0f, (float)(V - key_id(key[r])) * per_id);
             kbin[r] = (int)fminf(fmaxf(x, 0.0f), (float)(NBIN - 1));
             kslot[r] = atomicAdd(&s_hist[kbin[r]], 1);
         }

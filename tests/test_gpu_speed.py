@@ -171,3 +171,17 @@ def test_rows_shorter_than_a_block(dev):
     us = {d: Levels(16, 700, 8, 6, 128, dtype=d).time() for d in ("bf16", "f32")}
     print(us)
     assert us["f32"] < 1.4 * us["bf16"]
+
+
+def _mask(p):
+    def shape(x):
+        x[torch.rand((x.shape[0], 1, x.shape[2]), device=x.device).expand(x.shape) < p] = -float("inf")
+    return shape
+
+
+# a support that holds most of a masked row's -inf: three times the levels of
+# the row unmasked with all of them in one bin
+def test_supports_of_masked_rows(dev):
+    us = [Levels(20, 1700, 8, 4, 512, shape=s).time() for s in (None, _mask(0.9))]
+    print(us)
+    assert us[1] < 1.7 * us[0]
