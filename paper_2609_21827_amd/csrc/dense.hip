@@ -2,8 +2,9 @@
 // of V; Sec. 3.2 before its sparse approximation).
 //
 // bf16: one kernel per level, k_dense_row (described at the kernel), which
-// reads each row once.  fp32, whose values hardly repeat, and on request
-// bf16: three kernels per level:
+// reads each row once.  fp32, whose values hardly repeat, bf16 levels that it
+// does not pay for (dense_by_rows in api.hip), and on request all: three
+// kernels per level:
 //  * k_select (expand.hip) with list length kk = min(V, m + K): the exact
 //    top-kk of every chunk by (logit desc, id asc).
 //  * k_dweights, one 256-thread block per (chunk, row): merges the row's
@@ -506,7 +507,7 @@ __global__ __launch_bounds__(NTD) void k_dpool(TreeDev t, LevelArgs a) {
 //
 // Evaluating both weights of every element in a pass of its own bound the
 // level (30 vector instructions an element): at 512 rows of 128256, 34 us to
-// select, 60 for the weights and 15 for the pools, against 61 here.
+// select, 60 for the weights and 15 for the pools, against 56 here.
 // ---------------------------------------------------------------------------
 constexpr int NTX = 512;
 

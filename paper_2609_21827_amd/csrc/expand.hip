@@ -3,8 +3,8 @@
 // and true probabilities, and the parent each row belongs to.
 //
 // One kernel per level, k_expand_row: one block per row (described at the
-// kernel).  Where a row's LDS does not fit it (fp32 rows above 131072 elements
-// with wide supports), or on request, two kernels:
+// kernel).  Where a row's LDS does not fit it (fp32 rows of some 230,000 elements
+// and more with supports above some 290), or on request, two kernels:
 //  * k_select, one 256-thread block per (chunk, row): the chunk is streamed
 //    from HBM into registers with 16-byte loads and its exact top-Sc by
 //    (logit desc, id asc) is written, sorted, to the tree's selection
@@ -650,7 +650,7 @@ __device__ __forceinline__ void select_block(const TreeDev& t, const LevelArgs& 
 // the construction weights are summed over the whole vocabulary (relative to
 // the row maximum): for bf16 from counts of the row's values, taken as it
 // streams (V = 128256, 256 rows: 32 us a level where a pass of its own for the
-// totals took 91 us before the 23 us of the row kernel); for fp32, whose
+// totals took 91 us before the 23 us of the row kernel; 30 now); for fp32, whose
 // values hardly repeat, and for rows the counts do not cover, in a second
 // pass over the row.
 // ---------------------------------------------------------------------------

@@ -16,7 +16,6 @@ constexpr int NTE = 512;      // threads per k_expand_row block
 constexpr int EBATCH = 8;     // 16-byte vectors per thread and batch of k_expand_row
 constexpr int kLargeSupport = 256;  // supports above it: the large class of k_expand_row
 
-
 template <int DT>
 __device__ __forceinline__ float elem(const uint4& v, int k) {
     const uint32_t* w = &v.x;
@@ -497,6 +496,45 @@ __device__ __forceinline__ uint32_t wave_kth_code(uint32_t c1, uint32_t c2, uint
     return h;
 }
 
+// The largest code that S of the row's vector codes reach, at most NBIN - 1 above
+// h, which S of them reach (returned where fewer do: codes of two vectors).
+// s_hist holds zeros, and does again; *s_at is any word.  All threads of the block
+// call it.
+template <int NTB, int NBIN>
+__device__ __forceinline__ uint32_t codes_threshold(const uint32_t* codes, int words, uint32_t h,
+                                                    int S, int* s_hist, int* s_red, int* s_at) {
+    constexpr int BPT = NBIN > NTB ? NBIN / NTB : 1;
+    const int tid = threadIdx.x, lane = tid % WAVE, wid = tid / WAVE;
+    if (tid == 0) *s_at = 0;
+#pragma unroll 1
+    for (int i = tid; i < words; i += NTB) {
+        const uint32_t w = codes[i], lo = w & 0xFFFFu, hi = w >> 16;
+        if (lo >= h) atomicAdd(&s_hist[min(lo - h, (uint32_t)(NBIN - 1))], 1);
+        if (hi >= h) atomicAdd(&s_hist[min(hi - h, (uint32_t)(NBIN - 1))], 1);
+    }
+    __syncthreads();
+    const int top_bin = NBIN - 1 - tid * BPT;
+    int hv[BPT], tot = 0;
+#pragma unroll
+    for (int r = 0; r < BPT; ++r) {
+        hv[r] = top_bin - r >= 0 ? s_hist[top_bin - r] : 0;
+        tot += hv[r];
+    }
+    int st = wave_excl_scan(tot);
+    if (lane == WAVE - 1) s_red[wid] = st + tot;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NTB / WAVE; ++w) st += (w < wid) ? s_red[w] : 0;
+#pragma unroll
+    for (int r = 0; r < BPT; ++r) {
+        if (st < S && st + hv[r] >= S) *s_at = top_bin - r;
+        st += hv[r];
+        if (top_bin - r >= 0) s_hist[top_bin - r] = 0;
+    }
+    __syncthreads();
+    return h + (uint32_t)*s_at;
+}
+
 // The maximum of a vector, exact in its high 16 bits (fp32: truncated).
 template <int DT>
 __device__ __forceinline__ uint32_t vec_max_raw(const uint4& v) {
@@ -839,9 +877,11 @@ __device__ __forceinline__ RowTop row_top(const TreeDev& t, const LevelArgs& a, 
         cnt = rs.cnt;
         if (cnt <= CC || again) break;
         // Too many candidates: the row's large values are unevenly spread
-        // over the waves (sorted rows, say).  Once more with the threshold
-        // that S of the whole block's offers reach.
-        h = max(h, offer_threshold<NTB>(c1, c2, c3, c4, LS, S, rs.thr));
+        // over the lanes (sorted rows, say, or at S = 1024 one row in a hundred
+        // of a Zipf prior over the ids: 2300 candidates, where S of all its
+        // vectors reach a threshold of 1200).  Once more with that.
+        h = codes_threshold<NTB, NBIN>((const uint32_t*)(lds + L.codes), NB * NTB * (PAIR ? 2 : 4),
+                                       h, S, s_hist, rs.red, rs.thr);
         if (tid == 0) rs.cnt = 0;
         __syncthreads();
     }
