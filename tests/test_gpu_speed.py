@@ -126,7 +126,7 @@ def test_prune_of_piled_scores(dev, kind):
 def test_frontier_of_many_children(dev):
     us = {K: Levels(2, 32000, K, 7, 0, dtype="f32").time() for K in (10, 12)}
     print(us)
-    assert us[12] < 1.17 * us[10]
+    assert us[12] < 1.2 * us[10]
 
 
 # rows whose threshold bounds nothing, against rows of one candidate list: 1000
@@ -138,7 +138,7 @@ def test_frontier_of_many_children(dev):
 def test_short_rows(dev, dtype, V, ref, support):
     us = {v: Levels(5, v, 8, 4, support, dtype=dtype).time() for v in (V, ref)}
     print(us)
-    assert us[V] < 3 * us[ref]
+    assert us[V] < 4 * us[ref]
 
 
 def _columns(n):
